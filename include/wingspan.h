@@ -82,7 +82,8 @@ typedef struct {
     int32_t validate;       /* 1: check A and B are canonical (and, in numeric, that
                                C.row_ptr matches the product) on the device */
     int32_t max_lds_slots;  /* cap on LDS hash-table slots per row (power of two,
-                               64..16384); longer rows use the dense or spill tier */
+                               64..16384); longer rows use the dense or spill tier. When
+                               given, no rows are merged instead (see WINGSPAN_TIER_HASH) */
     int32_t force_spill;    /* 1: every row above the register tier uses the global
                                hash spill tier */
     int32_t window_cols;    /* dense-window width in columns: 1024, 4096, 8192 or 16384 */
@@ -112,7 +113,8 @@ typedef struct {
 /* Tiers a row can be assigned to. */
 enum {
     WINGSPAN_TIER_TINY = 0,   /* one wave segment per row, register bitonic sort */
-    WINGSPAN_TIER_HASH = 1,   /* one workgroup per row, LDS hash table + LDS sort */
+    WINGSPAN_TIER_HASH = 1,   /* one workgroup per row, LDS hash table + LDS sort, or, for rows
+                                 of few A entries, the selected rows of B merged in LDS */
     WINGSPAN_TIER_DENSE = 2,  /* one workgroup per row, LDS bitmap (symbolic) or dense
                                  LDS column windows (numeric) */
     WINGSPAN_TIER_SPILL = 3,  /* persistent workgroups, global-memory hash + merge sort */

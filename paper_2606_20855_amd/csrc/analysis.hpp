@@ -187,6 +187,9 @@ struct BinCfg {
     int32_t force_spill;
     int32_t dense_ok;       // the dense tier can take rows of this problem
     int32_t numeric;        // 0: symbolic bins, 1: numeric bins
+    int32_t merge_runs;     // rows of at most this many A entries ...
+    int32_t merge_places;   // ... and this many places in LDS are merged (0: none),
+    int32_t merge_over_dense;   // rows the dense tier would take up to this many places
 };
 
 __device__ __forceinline__ int class_of(int64_t f) {
@@ -197,9 +200,9 @@ __device__ __forceinline__ int class_of(int64_t f) {
     return kNumClasses - 1 - c;
 }
 
-// f: products of the row; c: output entries (numeric only); bound: out, the
-// hash-table bound when the row spills.
-__device__ __forceinline__ int choose_bin(int64_t f, int64_t c, const BinCfg &cfg, int64_t *bound) {
+// f: products of the row; k: its A entries; c: output entries (numeric only);
+// bound: out, the hash-table bound when the row spills.
+__device__ __forceinline__ int choose_bin(int64_t f, int k, int64_t c, const BinCfg &cfg, int64_t *bound) {
     *bound = 0;
     if (f == 0) return kBinEmpty;
     if (cfg.numeric && c == 0) return kBinEmpty;
@@ -220,6 +223,12 @@ __device__ __forceinline__ int choose_bin(int64_t f, int64_t c, const BinCfg &cf
     // entries has at least c products, so every row the numeric phase will prefer dense goes through the
     // symbolic bitmap kernel and leaves its column set in the structure cache)
     const bool dense_pref = cfg.dense_ok && (cfg.numeric ? c : f) >= cfg.dense_min_nnz;
+    // merge rows, by the places they take in LDS
+    const int64_t places = f + int64_t(cfg.numeric ? kMergePadNum : kMergePadSym) * k;
+    if (k <= cfg.merge_runs && places <= (dense_pref ? cfg.merge_over_dense : cfg.merge_places)) {
+        const int lm = ceil_log2(places);
+        return kBinMerge0 + (lm < kMergeLog2Min ? 0 : lm - kMergeLog2Min);
+    }
     if (!cfg.force_spill && l <= cfg.hash_log2_max && !dense_pref) return kBinHash0 + (l - kHashLog2Min);
     if (!cfg.force_spill && cfg.dense_ok) return kBinDense0 + class_of(f);
     *bound = cfg.numeric ? c : (f < cfg.ncols ? f : cfg.ncols);
@@ -246,7 +255,7 @@ __global__ void __launch_bounds__(256) bin_count(const int32_t *__restrict__ a_r
         const int64_t f = row_products_of(a_rp, pref, i);
         const int64_t c = cfg.numeric ? (c_rp[i + 1] - c_rp[i]) : 0;
         int64_t bound;
-        const int b = choose_bin(f, c, cfg, &bound);
+        const int b = choose_bin(f, a1 - a0, c, cfg, &bound);
         atomicAdd(&s_cnt[b], 1);
         atomicAdd(&s_prod[b], static_cast<unsigned long long>(f));
         atomicAdd(&s_annz[b], static_cast<unsigned long long>(a1 - a0));
@@ -293,7 +302,7 @@ __global__ void __launch_bounds__(256) bin_scatter(const int32_t *__restrict__ a
         const int64_t f = row_products_of(a_rp, pref, i);
         const int64_t c = cfg.numeric ? (c_rp[i + 1] - c_rp[i]) : 0;
         int64_t bound;
-        b = choose_bin(f, c, cfg, &bound);
+        b = choose_bin(f, a_rp[i + 1] - a_rp[i], c, cfg, &bound);
         if (b != kBinEmpty) r = atomicAdd(&s_cnt[b], 1);
     }
     __syncthreads();

@@ -24,10 +24,16 @@ constexpr int kBinHash0 = 5;      // 5..13: table sizes 2^6 .. 2^14
 constexpr int kHashLog2Min = 6;
 constexpr int kHashLog2Max = 14;
 constexpr int kNumHash = kHashLog2Max - kHashLog2Min + 1;
+constexpr int kBinMerge0 = kBinHash0 + kNumHash;       // 14..19: merge rows of up to 2^8 .. 2^13 places
+constexpr int kMergeLog2Min = 8;
+constexpr int kMergeLog2Max = 13;
+constexpr int kMergePadNum = 7, kMergePadSym = 15;     // places each run's padding takes at most (merge.hpp)
+constexpr int kNumMerge = kMergeLog2Max - kMergeLog2Min + 1;
+constexpr int kMergeMaxRuns = kWave;                   // A entries of a merge row at most (a wave holds them)
 constexpr int kNumClasses = 16;
-constexpr int kBinDense0 = kBinHash0 + kNumHash;       // 14..29
-constexpr int kBinSpill0 = kBinDense0 + kNumClasses;   // 30..45
-constexpr int kNumBins = kBinSpill0 + kNumClasses;     // 46
+constexpr int kBinDense0 = kBinMerge0 + kNumMerge;     // 20..35
+constexpr int kBinSpill0 = kBinDense0 + kNumClasses;   // 36..51
+constexpr int kNumBins = kBinSpill0 + kNumClasses;     // 52
 constexpr int kMaxBins = 64;
 
 enum : int32_t {
@@ -53,7 +59,8 @@ struct Stamp {
     // settings are the same.
     int64_t num_bins, wtab;
     int64_t nb_dense_min_nnz;
-    int32_t nb_tiny_max, nb_hash_log2_max, nb_force_spill, nb_dense_ok;
+    int32_t nb_tiny_max, nb_hash_log2_max, nb_force_spill, nb_dense_ok, nb_merge_runs, nb_merge_places,
+        nb_merge_over_dense, nb_pad;
 };
 constexpr uint64_t kStampMagic = 0x57535f5354525543ull;
 

@@ -22,6 +22,7 @@
 #include "analysis.hpp"
 #include "device_common.hpp"
 #include "tiers.hpp"
+#include "merge.hpp"
 #include "elementwise.hpp"
 #include "spmspv.hpp"
 #include "outer.hpp"
@@ -101,6 +102,7 @@ struct Opts {
     bool timing = false;
     bool wide_offsets = false;
     bool dense_disabled = false;
+    bool lds_explicit = false;     // max_lds_slots given: rows up to it take the hash tables (no merge rows)
     int hash_log2_max_sym = kHashLog2MaxSym;
     int hash_log2_max_num = kHashLog2MaxNum;
     int wcols = kDefaultWindow;
@@ -127,6 +129,7 @@ wingspan_status parse_opts(const wingspan_options *o, Opts *out) {
                 return fail(WINGSPAN_ERR_INVALID_ARGUMENT,
                             "options->max_lds_slots must be a power of two in [64, 16384], got %d", s);
             const int l = ceil_log2(s);
+            r.lds_explicit = true;
             r.hash_log2_max_sym = std::min(r.hash_log2_max_sym, l);
             r.hash_log2_max_num = std::min(r.hash_log2_max_num, l);
         }
@@ -331,6 +334,26 @@ Stamp make_stamp(const Ctx &c, const wingspan_csr *A, const wingspan_csr *B, int
     return t;
 }
 
+// Which rows are merged (merge.hpp): those of up to 64 A entries whose
+// products fit 2^13 places of LDS, unless the options ask for the hash tables
+// (max_lds_slots) or the spill tier. They beat the hash tables at every number
+// of runs up to 64 (up to 4 runs, 16, 64 merged on the R-MAT graph of 2.5 M
+// vertices: the tier 11.5, 6.0 and 5.5 ms). Rows the dense tier would take
+// stay there where B's columns fit one region of the rank kernel (R-MAT 18,
+// rows up to 4096 places merged: 10.63 ms a step against 10.62, up to 8192:
+// 11.5), and are merged where a row takes several (R-MAT graph of 1 M vertices:
+// step 21.1 ms with none, 18.2 up to 4096, 15.9 up to 8192). The symbolic phase
+// merges them up to 4096 places where its bitmap covers B's columns, which
+// then costs less (0.7 + 2.5 ms; up to 8192: 1.7 + 1.6 ms).
+constexpr int kMergeOverBitmap = 4096;
+void set_merge(const Ctx &c, const wingspan_csr *B, BinCfg *cfg) {
+    const bool on = !c.o.force_spill && !c.o.lds_explicit;
+    const bool over = on && !c.o.dense_min_explicit && B->ncols > RankShape<float>::REGION_COLS;
+    cfg->merge_runs = on ? kMergeMaxRuns : 0;
+    cfg->merge_places = on ? 1 << kMergeLog2Max : 0;
+    cfg->merge_over_dense = over ? (cfg->numeric ? 1 << kMergeLog2Max : kMergeOverBitmap) : 0;
+}
+
 // How the numeric phase bins rows (by C's exact row counts).
 BinCfg numeric_bin_cfg(const Ctx &c, const wingspan_csr *B) {
     BinCfg cfg{};
@@ -341,6 +364,7 @@ BinCfg numeric_bin_cfg(const Ctx &c, const wingspan_csr *B) {
     cfg.hash_log2_max = c.o.hash_log2_max_num;
     cfg.dense_min_nnz = c.o.dense_min_nnz;
     cfg.dense_ok = c.L.nwin > 0;
+    set_merge(c, B, &cfg);
     return cfg;
 }
 
@@ -352,6 +376,9 @@ void stamp_bins(Stamp &t, const BinCfg &cfg, bool wtab) {
     t.nb_hash_log2_max = cfg.hash_log2_max;
     t.nb_force_spill = cfg.force_spill;
     t.nb_dense_ok = cfg.dense_ok;
+    t.nb_merge_runs = cfg.merge_runs;
+    t.nb_merge_places = cfg.merge_places;
+    t.nb_merge_over_dense = cfg.merge_over_dense;
 }
 
 // Whether the numeric phase may use the structure cache: the stamp is valid,
@@ -477,7 +504,9 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
         const Stamp &h = c.host_stamp;
         if (stamp_matches(c, A, B) && h.num_bins == 1 && h.nb_dense_min_nnz == cfg.dense_min_nnz &&
             h.nb_tiny_max == cfg.tiny_max && h.nb_hash_log2_max == cfg.hash_log2_max &&
-            h.nb_force_spill == cfg.force_spill && h.nb_dense_ok == cfg.dense_ok) {
+            h.nb_force_spill == cfg.force_spill && h.nb_dense_ok == cfg.dense_ok &&
+            h.nb_merge_runs == cfg.merge_runs && h.nb_merge_places == cfg.merge_places &&
+            h.nb_merge_over_dense == cfg.merge_over_dense) {
             const uint64_t rp_sum = c.host.rp_sum;
             c.host = kept;
             c.host.rp_sum = rp_sum;
@@ -544,6 +573,7 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
     cfg.force_spill = c.o.force_spill;
     cfg.hash_log2_max = mode == kModeSymbolic ? c.o.hash_log2_max_sym : c.o.hash_log2_max_num;
     cfg.dense_min_nnz = c.o.dense_min_nnz;
+    set_merge(c, B, &cfg);
     if (mode == kModeNumeric) {
         cfg = numeric_bin_cfg(c, B);
     } else if (mode == kModeSymbolic) {
@@ -583,6 +613,7 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
 int tier_of_bin(int b) {
     if (b >= kBinTiny0 && b < kBinTiny0 + kNumTiny) return WINGSPAN_TIER_TINY;
     if (b >= kBinHash0 && b < kBinHash0 + kNumHash) return WINGSPAN_TIER_HASH;
+    if (b >= kBinMerge0 && b < kBinMerge0 + kNumMerge) return WINGSPAN_TIER_HASH;
     if (b >= kBinDense0 && b < kBinDense0 + kNumClasses) return WINGSPAN_TIER_DENSE;
     if (b >= kBinSpill0 && b < kBinSpill0 + kNumClasses) return WINGSPAN_TIER_SPILL;
     return -1;
@@ -674,6 +705,25 @@ void launch_hash(int log2t, unsigned grid, hipStream_t st, const Mats<V> &M, con
 #undef WS_HASH_CASE
 }
 
+// The merge rows, one launch per size.
+template <typename V, bool NUM>
+void launch_merge(const Ctx &c, hipStream_t st, const Mats<V> &M, const int32_t *perm, int32_t *row_nnz, RowSink out,
+                  int32_t *c_col, V *c_val, int32_t *launches) {
+#define WS_MERGE(L)                                                                                              \
+    if (const int32_t nb = c.host.bin_count[kBinMerge0 + L - kMergeLog2Min]; nb > 0) {                           \
+        merge_kernel<1 << L, V, NUM><<<static_cast<unsigned>(nb), (MergeShape<1 << L, NUM>::BLOCK), 0, st>>>(           \
+            M, perm + c.host.bin_offset[kBinMerge0 + L - kMergeLog2Min], row_nnz, out, c_col, c_val, c.ctrl);    \
+        ++*launches;                                                                                             \
+    }
+    WS_MERGE(8)
+    WS_MERGE(9)
+    WS_MERGE(10)
+    WS_MERGE(11)
+    WS_MERGE(12)
+    WS_MERGE(13)
+#undef WS_MERGE
+}
+
 void launch_bitmap(int64_t ncols, unsigned grid, hipStream_t st, const Mats<float> &M, const int32_t *rows,
                    int32_t *row_nnz, int32_t *slot_of_row, uint32_t *cache, int64_t row_words, int64_t cache_rows) {
     const int nwords = static_cast<int>((ncols + 31) / 32);
@@ -758,7 +808,7 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
     const bool wtab = caching && cnt_dense > 0 && c.L.nwin > 0;
     int32_t light = 0;
     for (int b = kBinTiny0; b < kBinTiny0 + kNumTiny; ++b) light += c.host.bin_count[b];
-    for (int b = kBinHash0; b < kBinHash0 + kNumHash; ++b) light += c.host.bin_count[b];
+    for (int b = kBinHash0; b < kBinMerge0 + kNumMerge; ++b) light += c.host.bin_count[b];
     // untimed, the tiny and hash tiers (and the window table) run on a side stream beside the dense kernel,
     // joined before the spill tier; timed, every tier runs in turn on the caller's stream
     SideStream *side = nullptr;
@@ -792,6 +842,8 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
                                       c.ctrl);
             stats.launches[WINGSPAN_TIER_HASH]++;
         }
+        launch_merge<float, false>(c, light_st, M, perm, c.row_nnz, RowSink{}, nullptr, nullptr,
+                                   &stats.launches[WINGSPAN_TIER_HASH]);
         LAUNCH_CHECK("hash symbolic");
         if ((s = timer_stop(c, WINGSPAN_TIER_HASH)) != WINGSPAN_OK) return s;
         if (wtab) {
@@ -891,7 +943,7 @@ wingspan_status numeric_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
     bin_range(c, kBinDense0, kNumClasses, &start, &cnt);
     int32_t light = 0;
     for (int b = kBinTiny0; b < kBinTiny0 + kNumTiny; ++b) light += c.host.bin_count[b];
-    for (int b = kBinHash0; b < kBinHash0 + kNumHash; ++b) light += c.host.bin_count[b];
+    for (int b = kBinHash0; b < kBinMerge0 + kNumMerge; ++b) light += c.host.bin_count[b];
     // untimed, the tiny and hash tiers run on a side stream beside the dense kernel (forked after the analysis,
     // joined before the spill tier); timed, every tier runs in turn on the caller's stream
     SideStream *side = nullptr;
@@ -924,6 +976,8 @@ wingspan_status numeric_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
                                  B->ncols, nullptr, sink, c_col, c_val, c.ctrl);
             stats.launches[WINGSPAN_TIER_HASH]++;
         }
+        launch_merge<V, true>(c, light_st, M, perm, nullptr, sink, c_col, c_val,
+                              &stats.launches[WINGSPAN_TIER_HASH]);
         LAUNCH_CHECK("hash numeric");
         if ((s = timer_stop(c, WINGSPAN_TIER_HASH)) != WINGSPAN_OK) return s;
         if (side) {
@@ -1033,6 +1087,7 @@ wingspan_status sharded_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
                              B->ncols, nullptr, sink, pool_col, pool_val, c.ctrl);
         stats.launches[WINGSPAN_TIER_HASH]++;
     }
+    launch_merge<V, true>(c, c.st, M, perm, nullptr, sink, pool_col, pool_val, &stats.launches[WINGSPAN_TIER_HASH]);
     LAUNCH_CHECK("hash single pass");
     if ((s = timer_stop(c, WINGSPAN_TIER_HASH)) != WINGSPAN_OK) return s;
 
