@@ -189,7 +189,8 @@ struct BinCfg {
     int32_t numeric;        // 0: symbolic bins, 1: numeric bins
     int32_t merge_runs;     // rows of at most this many A entries ...
     int32_t merge_places;   // ... and this many places in LDS are merged (0: none),
-    int32_t merge_over_dense;   // rows the dense tier would take up to this many places
+    int32_t merge_over_dense;   // rows the dense tier would take up to this many places;
+    int32_t merge_long;         // and up to this many products piece by piece (numeric)
 };
 
 __device__ __forceinline__ int class_of(int64_t f) {
@@ -230,6 +231,7 @@ __device__ __forceinline__ int choose_bin(int64_t f, int k, int64_t c, const Bin
         return kBinMerge0 + (lm < kMergeLog2Min ? 0 : lm - kMergeLog2Min);
     }
     if (!cfg.force_spill && l <= cfg.hash_log2_max && !dense_pref) return kBinHash0 + (l - kHashLog2Min);
+    if (k <= cfg.merge_runs && f <= cfg.merge_long) return kBinMergeLong;
     if (!cfg.force_spill && cfg.dense_ok) return kBinDense0 + class_of(f);
     *bound = cfg.numeric ? c : (f < cfg.ncols ? f : cfg.ncols);
     return kBinSpill0 + class_of(f);

@@ -24,16 +24,17 @@ constexpr int kBinHash0 = 5;      // 5..13: table sizes 2^6 .. 2^14
 constexpr int kHashLog2Min = 6;
 constexpr int kHashLog2Max = 14;
 constexpr int kNumHash = kHashLog2Max - kHashLog2Min + 1;
-constexpr int kBinMerge0 = kBinHash0 + kNumHash;       // 14..19: merge rows of up to 2^8 .. 2^13 places
+constexpr int kBinMerge0 = kBinHash0 + kNumHash;       // 14..19: merge rows of up to 2^8 .. 2^13 places, 20: longer
 constexpr int kMergeLog2Min = 8;
 constexpr int kMergeLog2Max = 13;
 constexpr int kMergePadNum = 7, kMergePadSym = 15;     // places each run's padding takes at most (merge.hpp)
-constexpr int kNumMerge = kMergeLog2Max - kMergeLog2Min + 1;
+constexpr int kNumMerge = kMergeLog2Max - kMergeLog2Min + 2;
+constexpr int kBinMergeLong = kBinMerge0 + kNumMerge - 1;
 constexpr int kMergeMaxRuns = kWave;                   // A entries of a merge row at most (a wave holds them)
 constexpr int kNumClasses = 16;
-constexpr int kBinDense0 = kBinMerge0 + kNumMerge;     // 20..35
-constexpr int kBinSpill0 = kBinDense0 + kNumClasses;   // 36..51
-constexpr int kNumBins = kBinSpill0 + kNumClasses;     // 52
+constexpr int kBinDense0 = kBinMerge0 + kNumMerge;     // 21..36
+constexpr int kBinSpill0 = kBinDense0 + kNumClasses;   // 37..52
+constexpr int kNumBins = kBinSpill0 + kNumClasses;     // 53
 constexpr int kMaxBins = 64;
 
 enum : int32_t {
@@ -60,7 +61,7 @@ struct Stamp {
     int64_t num_bins, wtab;
     int64_t nb_dense_min_nnz;
     int32_t nb_tiny_max, nb_hash_log2_max, nb_force_spill, nb_dense_ok, nb_merge_runs, nb_merge_places,
-        nb_merge_over_dense, nb_pad;
+        nb_merge_over_dense, nb_merge_long;
 };
 constexpr uint64_t kStampMagic = 0x57535f5354525543ull;
 

@@ -54,38 +54,34 @@ struct MergeItem<false> {
     __device__ static __forceinline__ int32_t make(int key, int) { return key; }
 };
 
-template <int CAP, typename V, bool NUM>
-__global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP, NUM>::WAVES)) merge_kernel(Mats<V> M, const int32_t *__restrict__ rows,
-                                                                       int32_t *__restrict__ row_nnz, RowSink out,
-                                                                       int32_t *__restrict__ c_col,
-                                                                       V *__restrict__ c_val, Control *ctrl) {
+template <int CAP, bool NUM>
+struct MergeLds {
     using S = MergeShape<CAP, NUM>;
+    __align__(16) typename MergeItem<NUM>::type item[S::ITEMS];
+    uint64_t head[NUM ? CAP / kWave + 1 : 1];   // where runs of equal columns start, a bit per place
+    double av[NUM ? kMergeMaxRuns : 1];
+    int32_t boff[NUM ? kMergeMaxRuns : 1];
+    int32_t pre[kMergeMaxRuns + 1];
+    int32_t scratch[S::BLOCK / kWave];
+};
+
+// Merges the runs the lanes of every wave hold alike (lane l: B's entries
+// [bs, bs + len) times av; together at most CAP places) and returns their
+// entries of C. The numeric kernels write them: place(entries) gives where the
+// first goes and how many may be written. All threads of the workgroup call it;
+// a barrier must come before L is used again.
+template <int CAP, bool NUM, typename V, typename Place>
+__device__ __forceinline__ int merge_runs(const Mats<V> &M, MergeLds<CAP, NUM> &L, int bs, int len, double av,
+                                          Place place, int32_t *__restrict__ c_col, V *__restrict__ c_val) {
+    using S = MergeShape<CAP, NUM>;
+    using I = MergeItem<NUM>;
+    using T = typename I::type;
     constexpr int BLOCK = S::BLOCK;
     constexpr int VT = S::VT;
     constexpr int NW = BLOCK / kWave;
-    using I = MergeItem<NUM>;
-    using T = typename I::type;
-    __shared__ __align__(16) T s_item[S::ITEMS];
-    __shared__ uint64_t s_head[NUM ? CAP / kWave + 1 : 1];   // where runs of equal columns start, a bit per place
-    __shared__ double s_av[NUM ? kMergeMaxRuns : 1];
-    __shared__ int32_t s_boff[NUM ? kMergeMaxRuns : 1];
-    __shared__ int32_t s_pre[kMergeMaxRuns + 1];
-    __shared__ int32_t scratch[NW];
-    __shared__ int64_t s_claim[2];   // pool output: the row's first entry and writable length
     const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
     const int ln = lane_id();
-    const int row = rows[blockIdx.x];
-    const int a_lo = M.a_rp[row], k = M.a_rp[row + 1] - a_lo;
-
-    // lane l: run l (the selected row of B and A's value), runs without entries moved behind the others
-    int bs = 0, len = 0;
-    double av = 0.0;
-    if (ln < k) {
-        const int32_t j = M.a_col[a_lo + ln];
-        if (NUM) av = to_d(M.a_val[a_lo + ln]);
-        bs = M.b_rp[j];
-        len = M.b_rp[j + 1] - bs;
-    }
+    // runs without entries moved behind the others
     const uint64_t full = ballot(len > 0);
     const int nr = __popcll(full);
     {
@@ -99,31 +95,13 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
     }
     const int incl = wave_incl_sum(len);
     const int f = __builtin_amdgcn_readlane(incl, kWave - 1);
-    int total;   // the row's entries
-
-    // the row's place: from C.row_ptr, or claimed from the pool by its entry count
-    int64_t cb = 0, seg = 0;
-    auto place = [&]() __attribute__((always_inline)) {
-        if (!out.pooled()) {
-            cb = out.c_rp[row];
-            seg = out.c_rp[row + 1] - cb;
-            if (threadIdx.x == 0 && total != seg) atomicOr(&ctrl->error_flags, kErrRowMismatch);
-        } else {
-            if (threadIdx.x == 0) s_claim[0] = out.claim(row, total, &s_claim[1]);
-            __syncthreads();
-            cb = uniform(s_claim[0]);
-            seg = uniform(s_claim[1]);
-        }
-    };
-
+    int total;   // the runs' entries of C
     if (nr <= 1) {
         // one run: the row of B, scaled
         total = f;
-        if (!NUM) {
-            if (threadIdx.x == 0) row_nnz[row] = total;
-            return;
-        }
-        place();
+        if (!NUM) return total;
+        const longlong2 at = place(total);
+        const int64_t cb = at.x, seg = at.y;
         const int lim = total < seg ? total : static_cast<int>(seg);
         const int b0 = __builtin_amdgcn_readlane(bs, 0);
         const double a = readlane_d(av, 0);
@@ -131,7 +109,7 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
             __builtin_nontemporal_store(M.b_col[b0 + i], &c_col[cb + i]);
             __builtin_nontemporal_store(static_cast<V>(a * to_d(M.b_val[b0 + i])), &c_val[cb + i]);
         }
-        return;
+        return total;
     }
 
     const int excl = incl - len;
@@ -147,13 +125,13 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
     const int shift = (ln & 1) ? excl + pincl - 1 : first - excl;
     const T pad = I::make(kPadKey, -1);
     if (wv == 0) {
-        s_pre[ln] = first;
-        if (ln == 0) s_pre[kMergeMaxRuns] = n;
+        L.pre[ln] = first;
+        if (ln == 0) L.pre[kMergeMaxRuns] = n;
         if (NUM) {
-            s_av[ln] = av;
-            s_boff[ln] = boff;
+            L.av[ln] = av;
+            L.boff[ln] = boff;
         }
-        for (int p = excl + len; p < excl + plen; ++p) s_item[S::at((ln & 1) ? shift - p : shift + p)] = pad;
+        for (int p = excl + len; p < excl + plen; ++p) L.item[S::at((ln & 1) ? shift - p : shift + p)] = pad;
     }
     // product p of the row (wave w takes [w VT 64, (w + 1) VT 64)): its run, its entry of B and its place
     const int wbase = wv * VT * kWave;
@@ -187,7 +165,7 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
         }
 #pragma unroll
         for (int u = 0; u < VT; ++u)
-            if (wbase + u * kWave + ln < f) s_item[S::at(to[u])] = I::make(c[u], from[u]);
+            if (wbase + u * kWave + ln < f) L.item[S::at(to[u])] = I::make(c[u], from[u]);
     }
     __syncthreads();
     // Merge passes: groups of s runs pairwise, in place. A pair's left group ascends and its right group
@@ -199,30 +177,30 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
     int r0 = 0;   // the run that held place d0
 #pragma unroll
     for (int step = kMergeMaxRuns / 2; step >= 1; step >>= 1)
-        if (s_pre[r0 + step] <= d0) r0 += step;
+        if (L.pre[r0 + step] <= d0) r0 += step;
     for (int s = 1; s < nr; s <<= 1) {
         T x[VT];
         int to = 0;   // where place d0 goes: d0, or mirrored in its pair
         if (d0 < n) {
             const int g = r0 & ~(2 * s - 1);
-            const int lo0 = s_pre[g], mid = s_pre[g + s], end = s_pre[g + 2 * s];
+            const int lo0 = L.pre[g], mid = L.pre[g + s], end = L.pre[g + 2 * s];
             const int d = d0 - lo0, na = mid - lo0, nb = end - mid;
             int lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
             while (lo < hi) {
                 const int m = (lo + hi) >> 1;
-                if (I::key(s_item[S::at(lo0 + m)]) <= I::key(s_item[S::at(end - d + m)])) lo = m + 1;
+                if (I::key(L.item[S::at(lo0 + m)]) <= I::key(L.item[S::at(end - d + m)])) lo = m + 1;
                 else hi = m;
             }
             int i = lo0 + lo, j = end - 1 - d + lo;
             to = (g & (2 * s)) ? lo0 + end - 1 - d0 : d0;
-            T xl = s_item[S::at(i)], xr = s_item[S::at(j)];
+            T xl = L.item[S::at(i)], xr = L.item[S::at(j)];
 #pragma unroll
             for (int u = 0; u < VT; ++u) {
                 const bool left = xl <= xr;   // (equal columns: the earlier run's, whichever end holds it)
                 x[u] = left ? xl : xr;
                 i += left ? 1 : 0;
                 j -= left ? 0 : 1;
-                const T nx = s_item[S::at(left ? i : j)];
+                const T nx = L.item[S::at(left ? i : j)];
                 xl = left ? nx : xl;
                 xr = left ? xr : nx;
             }
@@ -232,10 +210,10 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
             // (d0 and a mirrored d0 + 1 are multiples of VT: no gap inside the VT places)
             if (to == d0) {
 #pragma unroll
-                for (int u = 0; u < VT; ++u) s_item[S::at(d0) + u] = x[u];
+                for (int u = 0; u < VT; ++u) L.item[S::at(d0) + u] = x[u];
             } else {
 #pragma unroll
-                for (int u = 0; u < VT; ++u) s_item[S::at(to) - u] = x[u];
+                for (int u = 0; u < VT; ++u) L.item[S::at(to) - u] = x[u];
             }
         }
         __syncthreads();
@@ -250,14 +228,14 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
         x[u] = pad;
         bool head = false;
         if (p < f) {
-            x[u] = s_item[S::at(p)];
-            head = p == 0 || I::key(s_item[S::at(p - 1)]) != I::key(x[u]);
+            x[u] = L.item[S::at(p)];
+            head = p == 0 || I::key(L.item[S::at(p - 1)]) != I::key(x[u]);
         }
         heads[u] = ballot(head);
         cnt += __popcll(heads[u]);
-        if (NUM && ln == 0) s_head[wv * VT + u] = heads[u];
+        if (NUM && ln == 0) L.head[wv * VT + u] = heads[u];
     }
-    if (ln == 0) scratch[wv] = cnt;
+    if (ln == 0) L.scratch[wv] = cnt;
     if constexpr (NUM) {
         // the products, in column order
         double v[VT];
@@ -267,8 +245,8 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
             for (int u = 0; u < VT; ++u) {
                 const int p = wbase + u * kWave + ln;
                 const int from = p < f ? static_cast<int>(x[u] & 0xffffffffu) : 0;
-                b[u] = M.b_val[s_boff[from >> 16] + (from & 0xffff)];
-                v[u] = s_av[from >> 16];
+                b[u] = M.b_val[L.boff[from >> 16] + (from & 0xffff)];
+                v[u] = L.av[from >> 16];
             }
 #pragma unroll
             for (int u = 0; u < VT; ++u) v[u] *= to_d(b[u]);
@@ -278,19 +256,20 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
         total = 0;
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
-            const int t = scratch[i];
+            const int t = L.scratch[i];
             before += i < wv ? t : 0;
             total += t;
         }
         total = uniform(total);
-        place();
+        const longlong2 at = place(total);
+        const int64_t cb = at.x, seg = at.y;
         if (total < f) {
             // equal columns: the head adds the products after it (in the order of A's entries), which take the
             // items' place in LDS
-            double *s_prod = reinterpret_cast<double *>(s_item);
+            double *s_prod = reinterpret_cast<double *>(L.item);
 #pragma unroll
             for (int u = 0; u < VT; ++u) s_prod[S::at(wbase + u * kWave + ln)] = v[u];
-            if (threadIdx.x == 0) s_head[CAP / kWave] = 0;
+            if (threadIdx.x == 0) L.head[CAP / kWave] = 0;
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < VT; ++u) {
@@ -300,7 +279,7 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
                     const uint64_t here = ln < kWave - 1 ? heads[u] >> (ln + 1) : 0ull;
                     int eq = here ? __ffsll(static_cast<long long>(here)) : 0;
                     if (eq == 0) {
-                        const uint64_t next = s_head[wv * VT + u + 1];
+                        const uint64_t next = L.head[wv * VT + u + 1];
                         eq = kWave - ln + (next ? __ffsll(static_cast<long long>(next)) - 1 : kWave);
                     }
                     eq = eq < f - p ? eq : f - p;
@@ -323,9 +302,156 @@ __global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP
         __syncthreads();
         total = 0;
 #pragma unroll
-        for (int i = 0; i < NW; ++i) total += scratch[i];
-        if (threadIdx.x == 0) row_nnz[row] = total;
+        for (int i = 0; i < NW; ++i) total += L.scratch[i];
+        total = uniform(total);
     }
+    return total;
+}
+
+template <int CAP, typename V, bool NUM>
+__global__ void __launch_bounds__((MergeShape<CAP, NUM>::BLOCK), (MergeShape<CAP, NUM>::WAVES)) merge_kernel(
+    Mats<V> M, const int32_t *__restrict__ rows, int32_t *__restrict__ row_nnz, RowSink out,
+    int32_t *__restrict__ c_col, V *__restrict__ c_val, Control *ctrl) {
+    __shared__ MergeLds<CAP, NUM> L;
+    __shared__ int64_t s_claim[2];   // pool output: the row's first entry and writable length
+    const int ln = lane_id();
+    const int row = rows[blockIdx.x];
+    const int a_lo = M.a_rp[row], k = M.a_rp[row + 1] - a_lo;
+    // lane l: run l, the selected row of B and A's value
+    int bs = 0, len = 0;
+    double av = 0.0;
+    if (ln < k) {
+        const int32_t j = M.a_col[a_lo + ln];
+        if (NUM) av = to_d(M.a_val[a_lo + ln]);
+        bs = M.b_rp[j];
+        len = M.b_rp[j + 1] - bs;
+    }
+    // the row's place: from C.row_ptr, or claimed from the pool by its entry count
+    auto place = [&](int total) __attribute__((always_inline)) {
+        longlong2 at;
+        if (!out.pooled()) {
+            at.x = out.c_rp[row];
+            at.y = out.c_rp[row + 1] - at.x;
+            if (threadIdx.x == 0 && total != at.y) atomicOr(&ctrl->error_flags, kErrRowMismatch);
+        } else {
+            if (threadIdx.x == 0) s_claim[0] = out.claim(row, total, &s_claim[1]);
+            __syncthreads();
+            at.x = uniform(s_claim[0]);
+            at.y = uniform(s_claim[1]);
+        }
+        return at;
+    };
+    const int total = merge_runs<CAP, NUM, V>(M, L, bs, len, av, place, c_col, c_val);
+    if (!NUM && threadIdx.x == 0) row_nnz[row] = total;
+}
+
+// Longer rows of at most kMergeMaxRuns A entries, CSR output only: merged piece
+// by piece, a piece being a range of columns whose part of the row fits the
+// places in LDS. The window table gives the row's products before every window
+// boundary, and a piece takes as many whole windows as fit; a window that does
+// not fit alone is cut at a column found by halving (a column holds at most one
+// product per run).
+//
+// For C of several regions of the rank kernel, where such a row pays the rank
+// kernel's fixed work (about 20 K cycles) per region for a few thousand
+// entries. Measured on an R-MAT graph of 2.5 M vertices (10 regions; 19.6 K rows
+// of 8 K to 20 K products, float): 6.2 ms in the rank kernel, 3.7 ms here; on 1 M
+// vertices (4 regions, double) 3.3 ms against 9.5 ms, so there they stay.
+constexpr int kMergeLongCap = 1 << kMergeLog2Max;
+template <typename V>
+__global__ void __launch_bounds__((MergeShape<kMergeLongCap, true>::BLOCK), (MergeShape<kMergeLongCap, true>::WAVES))
+merge_long_kernel(Mats<V> M, const int32_t *__restrict__ rows, const int32_t *__restrict__ wtab, int nwin, int wcols,
+                  RowSink out, int32_t *__restrict__ c_col, V *__restrict__ c_val, Control *ctrl) {
+    constexpr int CAP = kMergeLongCap;
+    constexpr int BLOCK = MergeShape<CAP, true>::BLOCK;
+    constexpr int VT = MergeShape<CAP, true>::VT;
+    constexpr int NW = BLOCK / kWave;
+    __shared__ MergeLds<CAP, true> L;
+    __shared__ int32_t s_before[2 * kWave + 1];   // the row's products before window w
+    const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
+    const int ln = lane_id();
+    const int row = rows[blockIdx.x];
+    const int a_lo = M.a_rp[row], k = M.a_rp[row + 1] - a_lo;
+    // lane l: run l, from entry `cur` of B on, to `stop`
+    int cur = 0, stop = 0, j = 0;
+    double av = 0.0;
+    if (ln < k) {
+        j = M.a_col[a_lo + ln];
+        av = to_d(M.a_val[a_lo + ln]);
+        cur = M.b_rp[j];
+        stop = M.b_rp[j + 1];
+    }
+    const int64_t trow = static_cast<int64_t>(j) * (nwin + 1);
+    for (int w = threadIdx.x; w <= nwin; w += BLOCK) s_before[w] = 0;
+    __syncthreads();
+    for (int r = wv; r < k; r += NW) {
+        const int32_t *t = wtab + static_cast<int64_t>(__builtin_amdgcn_readlane(j, r)) * (nwin + 1);
+        const int first = __builtin_amdgcn_readlane(cur, r);
+        for (int w = ln; w <= nwin; w += kWave) {
+            const int n = t[w] - first;
+            if (n > 0) atomicAdd(&s_before[w], n);
+        }
+    }
+    __syncthreads();
+    const int b0 = ln <= nwin ? s_before[ln] : 0x7fffffff;
+    const int b1 = ln + kWave <= nwin ? s_before[ln + kWave] : 0x7fffffff;
+    const int b2 = nwin == 2 * kWave ? s_before[nwin] : 0x7fffffff;
+    const int f = uniform(s_before[nwin]);
+    const int room = CAP - (VT - 1) * k;   // products that fit, every run's end padded
+    const int64_t cb = out.c_rp[row];
+    const int64_t seg = out.c_rp[row + 1] - cb;
+    int taken = 0;        // products of the pieces so far
+    int64_t done = 0;     // their entries of C
+    int64_t col = 0;      // the next piece's first column
+    while (taken < f) {
+        // the last window boundary the piece reaches
+        const int most = taken + room;
+        const int w1 = __popcll(ballot(b0 <= most)) + __popcll(ballot(b1 <= most)) + (b2 <= most ? 1 : 0) - 1;
+        const int before1 = w1 < kWave ? __builtin_amdgcn_readlane(b0, w1)
+                                       : (w1 < 2 * kWave ? __builtin_amdgcn_readlane(b1, w1 - kWave) : b2);
+        int end = cur;
+        if (before1 > taken) {
+            if (ln < k) end = w1 == nwin ? stop : wtab[trow + w1];
+            col = static_cast<int64_t>(w1) * wcols;
+        } else {
+            int64_t lo = static_cast<int64_t>(w1) * wcols, hi = lo + wcols;
+            lo = lo > col ? lo : col;
+            const int lim = ln < k ? wtab[trow + w1 + 1] : cur;
+            while (hi - lo > 1) {
+                const int64_t x = lo + (hi - lo) / 2;
+                int p = cur, q = lim;
+                while (p < q) {
+                    const int m = p + ((q - p) >> 1);
+                    if (M.b_col[m] < x) p = m + 1;
+                    else q = m;
+                }
+                const int n = uniform(wave_sum(p - cur));
+                end = p;
+                col = x;
+                if (n > 0 && n <= room) break;
+                if (n > 0) hi = x;
+                else lo = x;
+            }
+        }
+        const int len = end > cur ? end - cur : 0;
+        const int n = uniform(wave_sum(len));
+        if (n <= 0 || n > room) {
+            // only where B's rows are not sorted
+            if (threadIdx.x == 0) atomicOr(&ctrl->error_flags, kErrRowMismatch);
+            break;
+        }
+        auto place = [&](int) __attribute__((always_inline)) {
+            longlong2 at;
+            at.x = cb + done;
+            at.y = seg - done;
+            return at;
+        };
+        done += merge_runs<CAP, true, V>(M, L, cur, len, av, place, c_col, c_val);
+        taken += n;
+        cur = end > cur ? end : cur;
+        __syncthreads();   // L is used again
+    }
+    if (threadIdx.x == 0 && done != seg) atomicOr(&ctrl->error_flags, kErrRowMismatch);
 }
 
 }  // namespace wsp

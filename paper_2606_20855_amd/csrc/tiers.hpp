@@ -629,6 +629,61 @@ __global__ void __launch_bounds__(BLOCK) bitmap_sym_kernel(Mats<float> M,
     if (threadIdx.x == 0) row_nnz[row] = total;
 }
 
+// The same for C of more columns than one bitmap holds: the row's columns are
+// taken in regions of kWideSymWords * 32, each marked from the window table's
+// slices of the row's B rows and counted. Measured against the spill tier's
+// global hash tables on a 2.5 M-vertex R-MAT graph (27 K rows, 567 M products):
+// 31.7 ms, here 3.1 ms.
+constexpr int kWideSymWords = 16384;
+constexpr int kWideSymBlock = 1024;
+__global__ void __launch_bounds__(kWideSymBlock) bitmap_sym_wide_kernel(
+    Mats<float> M, const int32_t *__restrict__ rows, const int32_t *__restrict__ wtab, int nwin, int wcols,
+    int64_t ncols, int32_t *__restrict__ row_nnz, int32_t *__restrict__ slot_of_row, uint32_t *__restrict__ cache,
+    int64_t row_words, int64_t cache_rows) {
+    constexpr int BLOCK = kWideSymBlock;
+    constexpr int NW = BLOCK / kWave;
+    __shared__ __align__(16) uint32_t bm[kWideSymWords];
+    __shared__ int32_t scratch[NW];
+    __shared__ int32_t marks[NW * kMarkIntsLong];
+    __shared__ int32_t ctot[kCtotInts];
+    __shared__ int32_t e_col[kCacheEntries], e_bs[kCacheEntries], e_len[kCacheEntries];
+    const int row = rows[blockIdx.x];
+    uint4 *const bq = reinterpret_cast<uint4 *>(bm);
+    for (int i = threadIdx.x; i < kWideSymWords / 4; i += BLOCK) bq[i] = make_uint4(0u, 0u, 0u, 0u);
+    const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
+    int32_t *mark = marks + wv * kMarkIntsLong;
+    init_marks(mark, kMarkIntsLong);
+    const int64_t stride = static_cast<int64_t>(nwin) + 1;
+    const int rwins = kWideSymWords * 32 / wcols;
+    const bool caching = cache != nullptr && blockIdx.x < cache_rows;
+    uint32_t *const dst = caching ? cache + static_cast<int64_t>(blockIdx.x) * row_words : nullptr;
+    EntryCache ecache{e_col, e_bs, e_len, nullptr, false};
+    int cnt = 0;
+    for (int rg0 = 0; rg0 < nwin; rg0 += rwins) {
+        const int rg1 = nwin - rg0 < rwins ? nwin : rg0 + rwins;
+        const int64_t col0 = static_cast<int64_t>(rg0) * wcols;
+        const int64_t left = ncols - col0;
+        const int nwords = static_cast<int>(((left < kWideSymWords * 32 ? left : kWideSymWords * 32) + 31) >> 5);
+        for_each_product_wg<BLOCK, float, false, true, true>(
+            M.a_col, nullptr, M.a_rp[row], M.a_rp[row + 1], BWindowRange{wtab, stride, rg0, rg1}, M.b_col, nullptr,
+            mark, ctot, BitmapMark<1>{{}, bm, static_cast<int>(col0)}, ecache);
+        ecache.col_ready = true;
+        // (for_each_product_wg ends with a barrier, and marks only after one: each thread counts and clears its
+        // words in between)
+        for (int i = threadIdx.x; i < (nwords + 3) >> 2; i += BLOCK) {
+            const uint4 q = bq[i];
+            bq[i] = make_uint4(0u, 0u, 0u, 0u);
+            cnt += __popc(q.x) + __popc(q.y) + __popc(q.z) + __popc(q.w);
+            if (caching)
+                __builtin_nontemporal_store(u32x4{q.x, q.y, q.z, q.w},
+                                            reinterpret_cast<u32x4 *>(dst + (col0 >> 5) + 4 * i));
+        }
+    }
+    if (caching && threadIdx.x == 0) slot_of_row[row] = static_cast<int32_t>(blockIdx.x);
+    const int total = block_sum<BLOCK>(cnt, scratch);
+    if (threadIdx.x == 0) row_nnz[row] = total;
+}
+
 // ---------------------------------------------------------------------------
 // Dense tier, numeric: the row's columns are swept in windows of WV columns.
 // For each window the workgroup accumulates every product whose column falls
@@ -781,7 +836,7 @@ __global__ void __launch_bounds__(DenseShape<WV>::BLOCK) dense_num_kernel(Mats<V
 }
 
 // ---------------------------------------------------------------------------
-// Dense tier, numeric, rank-indexed (default when ncols <= 128 * 8192).
+// Dense tier, numeric, rank-indexed (default when ncols <= 128 * 8192, or 128 wider windows (WIDE)).
 //
 // The row is processed in regions of REGION_COLS columns. For a region:
 //  1. a structure pass marks every column the row touches in an LDS bitmap;
@@ -978,9 +1033,12 @@ __device__ __forceinline__ int opaque_zero() {
 // the sink (compiled apart, so the CSR kernel carries none of the pool state).
 // OFF32: B's offsets in the value passes' general steps are formed in 32 bits,
 // for B with nnz * sizeof(V) <= 2^32 (the launch checks).
-template <typename V, bool POOL, bool OFF32>
+// WIDE: the windows hold win_words * 32 columns (a region of whole windows)
+// instead of kRankWinCols, for C of more than 128 * kRankWinCols columns.
+template <typename V, bool POOL, bool OFF32, bool WIDE>
 __global__ void __launch_bounds__(RankShape<V>::BLOCK) dense_rank_kernel(
-    Mats<V> M, const RankRow *__restrict__ rr, int nrows, const int32_t *__restrict__ wtab, int nwin, int64_t ncols,
+    Mats<V> M, const RankRow *__restrict__ rr, int nrows, const int32_t *__restrict__ wtab, int nwin, int win_words,
+    int64_t ncols,
     RowSink out, int32_t *__restrict__ c_col, V *__restrict__ c_val, Control *ctrl,
     const uint32_t *__restrict__ cache, int64_t row_words) {
     using SH = RankShape<V>;
@@ -988,7 +1046,8 @@ __global__ void __launch_bounds__(RankShape<V>::BLOCK) dense_rank_kernel(
     constexpr int NW = BLOCK / kWave;
     constexpr int RW = SH::REGION_WORDS;
     constexpr int WROWS = RW / NW / kWave;   // 64-word rows per wave in the prefix scan
-    constexpr int WIN_WORDS = kRankWinCols / 32;
+    const int WIN_WORDS = WIDE ? win_words : kRankWinCols / 32;
+    const int REGION_WINS = WIDE ? RW / win_words : SH::REGION_WINS;
     constexpr int CAP = SH::CAP;
     __shared__ uint2 bw[RW];                 // x: column bits, y: exclusive prefix within the region
     __shared__ __align__(16) double acc[CAP];
@@ -1004,7 +1063,7 @@ __global__ void __launch_bounds__(RankShape<V>::BLOCK) dense_rank_kernel(
     const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
     const int ln = lane_id();
     const int64_t stride = static_cast<int64_t>(nwin) + 1;
-    const int rg1_first = nwin < SH::REGION_WINS ? nwin : SH::REGION_WINS;   // end of the first region
+    const int rg1_first = nwin < REGION_WINS ? nwin : REGION_WINS;   // end of the first region
     int32_t *mark = marks + wv * kMarkIntsLong;
     init_marks(mark, kMarkIntsLong);
     for (int i = threadIdx.x; i < CAP; i += BLOCK) acc[i] = 0.0;
@@ -1082,13 +1141,13 @@ __global__ void __launch_bounds__(RankShape<V>::BLOCK) dense_rank_kernel(
         // Pool output needs the row's entry count before its first write. A row of one region claims once that
         // region's count is known (below); a row spanning several regions counts its entries first, region by
         // region (a structure pass and a popcount each), and claims the total here.
-        const bool multi_region = nwin > SH::REGION_WINS;
+        const bool multi_region = nwin > REGION_WINS;
         if constexpr (POOL) {
             if (multi_region) {
                 int total = 0;
-                for (int rg0 = 0; rg0 < nwin; rg0 += SH::REGION_WINS) {
-                    const int rg1 = nwin - rg0 < SH::REGION_WINS ? nwin : rg0 + SH::REGION_WINS;
-                    const int64_t col0 = static_cast<int64_t>(rg0) * kRankWinCols;
+                for (int rg0 = 0; rg0 < nwin; rg0 += REGION_WINS) {
+                    const int rg1 = nwin - rg0 < REGION_WINS ? nwin : rg0 + REGION_WINS;
+                    const int64_t col0 = static_cast<int64_t>(rg0) * WIN_WORDS * 32;
                     const int ncw =
                         static_cast<int>(ncols - col0 < SH::REGION_COLS ? ncols - col0 : SH::REGION_COLS);
                     const int nwords = (ncw + 31) >> 5;
@@ -1110,9 +1169,9 @@ __global__ void __launch_bounds__(RankShape<V>::BLOCK) dense_rank_kernel(
             }
         }
         int64_t done = 0;   // entries of the row emitted in earlier regions
-        for (int rg0 = 0; rg0 < nwin; rg0 += SH::REGION_WINS) {
-            const int rg1 = nwin - rg0 < SH::REGION_WINS ? nwin : rg0 + SH::REGION_WINS;
-            const int64_t col0 = static_cast<int64_t>(rg0) * kRankWinCols;
+        for (int rg0 = 0; rg0 < nwin; rg0 += REGION_WINS) {
+            const int rg1 = nwin - rg0 < REGION_WINS ? nwin : rg0 + REGION_WINS;
+            const int64_t col0 = static_cast<int64_t>(rg0) * WIN_WORDS * 32;
             const int ncw = static_cast<int>(ncols - col0 < SH::REGION_COLS ? ncols - col0 : SH::REGION_COLS);
             const int nwords = (ncw + 31) >> 5;
             // 1. structure: the cached bitmap, or a structure pass (a region covering every column takes whole
@@ -1163,7 +1222,7 @@ __global__ void __launch_bounds__(RankShape<V>::BLOCK) dense_rank_kernel(
                 __syncthreads();
                 // (the .x words of bw, two words apart)
                 const BitmapMark<2> mark_col{{}, &bw[0].x, static_cast<int>(col0)};
-                if (nwin <= SH::REGION_WINS)
+                if (nwin <= REGION_WINS)
                     for_each_product_wg<BLOCK, V, false, true, true>(M.a_col, M.a_val, a_lo, a_hi,
                                                                      BRowRange{M.b_rp}, M.b_col, M.b_val, mark,
                                                                      ctot, mark_col, ecache);

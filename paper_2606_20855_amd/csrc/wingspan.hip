@@ -54,6 +54,8 @@ constexpr int64_t kShardedDenseMin = 2048;
 // this many products up to the bitmap kernel: below kCachedDenseMin they go back to the LDS hash in the
 // numeric phase, but counting them in a bitmap costs less than in a hash table of 2^11 slots or more.
 constexpr int64_t kSymbolicDenseMin = 1024;
+constexpr int64_t kRankRegionCols = RankShape<float>::REGION_COLS;
+constexpr int64_t kWideTableBytes = int64_t(4) << 30;   // window table of a C of more than 128 * 8192 columns at most
 constexpr int kDefaultWindow = 16384;         // 16K doubles = 128 KB of LDS
 constexpr int64_t kPoolBytes = int64_t(1) << 30;   // spill pool: at most this, unless one table needs more
 constexpr int64_t kMaxSlabCap = int64_t(1) << 27;
@@ -196,6 +198,7 @@ struct Layout {
     int nwin;          // numeric dense windows per row (0: dense numeric tier unavailable)
     int wcols;         // columns per window of the window table
     bool rank_mode;    // dense numeric rows use the rank-indexed kernel
+    bool wide;         // ... with windows of more than kRankWinCols columns
     int64_t slab_cap;    // slots of the largest spill table (a row beyond slab_cap / 2 entries is refused)
     int64_t pool_bytes;  // the spill pool
 };
@@ -233,6 +236,16 @@ Layout plan(const wingspan_csr *A, const wingspan_csr *B, const Opts &o, size_t 
         L.rank_mode = true;
         L.wcols = kRankWinCols;
     }
+    // Past 128 windows of 8192 columns the windows grow, up to a whole region of the rank kernel, while the window
+    // table stays within its budget; not for the static scratch, which is too small for such tables.
+    L.wide = false;
+    for (int64_t w = 2 * kRankWinCols; !o.wcols_explicit && !L.rank_mode && budget == 0 && w <= kRankRegionCols;
+         w *= 2) {
+        if (windows(w) > kMaxWindows) continue;
+        if (int64_t(sizeof(int32_t)) * B->nrows * (windows(w) + 1) > kWideTableBytes) continue;
+        L.rank_mode = L.wide = true;
+        L.wcols = static_cast<int>(w);
+    }
     const int64_t nwin = windows(L.wcols);
     L.nwin = (!o.dense_disabled && nwin <= kMaxWindows) ? static_cast<int>(nwin) : 0;
     if (L.nwin > 0) off += align_up(sizeof(int32_t) * B->nrows * (L.nwin + 1) + sizeof(int32_t));
@@ -249,7 +262,8 @@ Layout plan(const wingspan_csr *A, const wingspan_csr *B, const Opts &o, size_t 
     // kernel; rows beyond the budget (options.cache_mib) run their own structure pass
     L.cache_rows = 0;
     L.row_words = 0;
-    if (budget == 0 && L.rank_mode && L.nwin > 0 && !o.dense_disabled && n > 0 && n <= kBitmapMaxCols && m > 0) {
+    if (budget == 0 && L.rank_mode && L.nwin > 0 && !o.dense_disabled && n > 0 &&
+        (n <= kBitmapMaxCols || L.wide) && m > 0) {
         L.row_words = (n + 31) / 32;
         L.row_words = (L.row_words + 63) / 64 * 64;
         L.cache_rows = std::min<int64_t>(m, o.cache_bytes / (L.row_words * 4));
@@ -338,20 +352,35 @@ Stamp make_stamp(const Ctx &c, const wingspan_csr *A, const wingspan_csr *B, int
 // products fit 2^13 places of LDS, unless the options ask for the hash tables
 // (max_lds_slots) or the spill tier. They beat the hash tables at every number
 // of runs up to 64 (up to 4 runs, 16, 64 merged on the R-MAT graph of 2.5 M
-// vertices: the tier 11.5, 6.0 and 5.5 ms). Rows the dense tier would take
-// stay there where B's columns fit one region of the rank kernel (R-MAT 18,
-// rows up to 4096 places merged: 10.63 ms a step against 10.62, up to 8192:
-// 11.5), and are merged where a row takes several (R-MAT graph of 1 M vertices:
-// step 21.1 ms with none, 18.2 up to 4096, 15.9 up to 8192). The symbolic phase
-// merges them up to 4096 places where its bitmap covers B's columns, which
-// then costs less (0.7 + 2.5 ms; up to 8192: 1.7 + 1.6 ms).
+// vertices: the tier 11.5, 6.0 and 5.5 ms).
+//
+// Rows the dense tier would take stay there where B's columns fit one region of
+// the rank kernel (R-MAT 18, rows up to 4096 places merged: 10.63 ms a step
+// against 10.62, up to 8192: 11.5). A row of several regions costs the rank
+// kernel about 29 ns per region whatever it holds (7.5 us on one of 256 CUs),
+// merging about 15 ps per product, so rows of up to 2048 products per region
+// are merged (whole products at 1024, 2048 and 3000 per region: 400 K vertices,
+// 2 regions, double, 10.0, 9.26, 9.14 ms; 1 M, 4 regions, 18.0, 14.9, 15.5; 2.5 M,
+// 10 regions, 20.2, 18.7, 18.8).
+// The symbolic phase merges them up to 4096 places where its bitmap covers B's
+// columns, which then costs less (1 M vertices: 0.7 + 2.5 ms; up to 8192: 1.7 +
+// 1.6 ms), never piece by piece (2.5 M vertices: 4.7 ms in all either way).
 constexpr int kMergeOverBitmap = 4096;
+constexpr int kMergePerRegion = 2048;
 void set_merge(const Ctx &c, const wingspan_csr *B, BinCfg *cfg) {
     const bool on = !c.o.force_spill && !c.o.lds_explicit;
-    const bool over = on && !c.o.dense_min_explicit && B->ncols > RankShape<float>::REGION_COLS;
+    constexpr int most = 1 << kMergeLog2Max;
     cfg->merge_runs = on ? kMergeMaxRuns : 0;
-    cfg->merge_places = on ? 1 << kMergeLog2Max : 0;
-    cfg->merge_over_dense = over ? (cfg->numeric ? 1 << kMergeLog2Max : kMergeOverBitmap) : 0;
+    cfg->merge_places = on ? most : 0;
+    cfg->merge_over_dense = cfg->merge_long = 0;
+    const int64_t regions = (B->ncols + kRankRegionCols - 1) / kRankRegionCols;
+    if (!on || c.o.dense_min_explicit || regions < 2) return;
+    const int64_t limit = std::min<int64_t>(regions * kMergePerRegion, INT32_MAX);
+    if (!cfg->numeric)
+        cfg->merge_over_dense = B->ncols > kBitmapMaxCols ? most : kMergeOverBitmap;
+    else
+        cfg->merge_over_dense = static_cast<int32_t>(std::min<int64_t>(limit, most));
+    if (cfg->numeric && limit > most && c.L.rank_mode && c.L.nwin > 0) cfg->merge_long = static_cast<int32_t>(limit);
 }
 
 // How the numeric phase bins rows (by C's exact row counts).
@@ -379,6 +408,7 @@ void stamp_bins(Stamp &t, const BinCfg &cfg, bool wtab) {
     t.nb_merge_runs = cfg.merge_runs;
     t.nb_merge_places = cfg.merge_places;
     t.nb_merge_over_dense = cfg.merge_over_dense;
+    t.nb_merge_long = cfg.merge_long;
 }
 
 // Whether the numeric phase may use the structure cache: the stamp is valid,
@@ -464,6 +494,15 @@ wingspan_status run_scan(Ctx &c, In in, int64_t n, int64_t *out) {
 
 unsigned blocks_for(int64_t n, int per) { return static_cast<unsigned>((n + per - 1) / per); }
 
+// B's column-window table for the layout's windows.
+wingspan_status launch_window_table(Ctx &c, const wingspan_csr *B, hipStream_t st) {
+    const int64_t entries = B->nrows * static_cast<int64_t>(c.L.nwin + 1);
+    build_window_table<<<blocks_for(entries, 256), 256, 0, st>>>(B->row_ptr, B->col_idx, B->nrows, c.L.nwin, c.L.wcols,
+                                                                 c.wtab);
+    LAUNCH_CHECK("build_window_table");
+    return WINGSPAN_OK;
+}
+
 // Product counts, optional validation, and binning. Ends with the control
 // block on the host.
 // What the analysis prepares: the symbolic phase (bins by products, LDS
@@ -506,7 +545,7 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
             h.nb_tiny_max == cfg.tiny_max && h.nb_hash_log2_max == cfg.hash_log2_max &&
             h.nb_force_spill == cfg.force_spill && h.nb_dense_ok == cfg.dense_ok &&
             h.nb_merge_runs == cfg.merge_runs && h.nb_merge_places == cfg.merge_places &&
-            h.nb_merge_over_dense == cfg.merge_over_dense) {
+            h.nb_merge_over_dense == cfg.merge_over_dense && h.nb_merge_long == cfg.merge_long) {
             const uint64_t rp_sum = c.host.rp_sum;
             c.host = kept;
             c.host.rp_sum = rp_sum;
@@ -577,8 +616,8 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
     if (mode == kModeNumeric) {
         cfg = numeric_bin_cfg(c, B);
     } else if (mode == kModeSymbolic) {
-        cfg.dense_ok = !c.o.dense_disabled && B->ncols <= kBitmapMaxCols;
-        if (!c.o.dense_min_explicit && c.L.cache_rows > 0 && B->ncols <= RankShape<float>::REGION_COLS)
+        cfg.dense_ok = !c.o.dense_disabled && (B->ncols <= kBitmapMaxCols || c.L.wide);
+        if (!c.o.dense_min_explicit && c.L.cache_rows > 0 && B->ncols <= kRankRegionCols)
             cfg.dense_min_nnz = kSymbolicDenseMin;
     } else {
         // the rank kernel writes a pool row once its count is known (a row of several regions counts them
@@ -586,7 +625,7 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
         cfg.dense_ok = c.L.rank_mode && c.L.nwin > 0;
         cfg.dense_min_nnz = c.o.dense_min_explicit
                                 ? c.o.dense_min_nnz
-                                : (B->ncols <= RankShape<float>::REGION_COLS ? kShardedDenseMin : INT64_MAX);
+                                : (B->ncols <= kRankRegionCols ? kShardedDenseMin : INT64_MAX);
     }
     if (m > 0) {
         bin_count<<<blocks_for(m, 256), 256, 0, c.st>>>(A->row_ptr, c.pref, c_rp, m, cfg, c.ctrl,
@@ -722,10 +761,23 @@ void launch_merge(const Ctx &c, hipStream_t st, const Mats<V> &M, const int32_t 
     WS_MERGE(12)
     WS_MERGE(13)
 #undef WS_MERGE
+    if constexpr (NUM) {
+        if (const int32_t nb = c.host.bin_count[kBinMergeLong]; nb > 0) {
+            merge_long_kernel<V><<<static_cast<unsigned>(nb), (MergeShape<kMergeLongCap, true>::BLOCK), 0, st>>>(
+                M, perm + c.host.bin_offset[kBinMergeLong], c.wtab, c.L.nwin, c.L.wcols, out, c_col, c_val, c.ctrl);
+            ++*launches;
+        }
+    }
 }
 
 void launch_bitmap(int64_t ncols, unsigned grid, hipStream_t st, const Mats<float> &M, const int32_t *rows,
-                   int32_t *row_nnz, int32_t *slot_of_row, uint32_t *cache, int64_t row_words, int64_t cache_rows) {
+                   int32_t *row_nnz, int32_t *slot_of_row, uint32_t *cache, int64_t row_words, int64_t cache_rows,
+                   const int32_t *wtab, int nwin, int wcols) {
+    if (ncols > kBitmapMaxCols) {
+        bitmap_sym_wide_kernel<<<grid, kWideSymBlock, 0, st>>>(M, rows, wtab, nwin, wcols, ncols, row_nnz, slot_of_row,
+                                                               cache, row_words, cache_rows);
+        return;
+    }
     const int nwords = static_cast<int>((ncols + 31) / 32);
 #define WS_BITMAP(NW, BL) \
     bitmap_sym_kernel<NW, BL><<<grid, BL, 0, st>>>(M, rows, nwords, row_nnz, slot_of_row, cache, row_words, cache_rows)
@@ -760,6 +812,24 @@ void launch_dense(int wcols, bool sentinel, unsigned grid, hipStream_t st, const
         launch_dense_w<8192, V>(sentinel, grid, st, M, rows, wtab, nwin, ncols, c_rp, c_col, c_val, ctrl);
     else
         launch_dense_w<16384, V>(sentinel, grid, st, M, rows, wtab, nwin, ncols, c_rp, c_col, c_val, ctrl);
+}
+
+// The rank kernel over the cnt rows described in c.rrows.
+template <typename V, bool POOL>
+void launch_rank(const Ctx &c, const Mats<V> &M, const wingspan_csr *B, int32_t cnt, const RowSink &sink, int32_t *c_col,
+                 V *c_val, const uint32_t *cache) {
+    const bool off32 = !c.o.wide_offsets && offsets_fit_32<V>(B);
+#define WS_RANK(OFF32, WIDE)                                                                                      \
+    dense_rank_kernel<V, POOL, OFF32, WIDE><<<rank_grid(cnt), RankShape<V>::BLOCK, 0, c.st>>>(                    \
+        M, c.rrows, cnt, c.wtab, c.L.nwin, c.L.wcols / 32, B->ncols, sink, c_col, c_val, c.ctrl, cache, c.L.row_words)
+    if (c.L.wide) {
+        if (off32) WS_RANK(true, true);
+        else WS_RANK(false, true);
+    } else {
+        if (off32) WS_RANK(true, false);
+        else WS_RANK(false, false);
+    }
+#undef WS_RANK
 }
 
 // The spill tier, one launch per size class (heaviest first). Class k holds
@@ -806,6 +876,9 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
     const int64_t cnt_dense = cnt;
     // B's window table for the numeric phase's dense rows (it depends on B only)
     const bool wtab = caching && cnt_dense > 0 && c.L.nwin > 0;
+    // the symbolic bitmap kernel needs it first where it works region by region
+    const bool wtab_first = cnt_dense > 0 && B->ncols > kBitmapMaxCols;
+    if (wtab_first && (s = launch_window_table(c, B, c.st)) != WINGSPAN_OK) return s;
     int32_t light = 0;
     for (int b = kBinTiny0; b < kBinTiny0 + kNumTiny; ++b) light += c.host.bin_count[b];
     for (int b = kBinHash0; b < kBinMerge0 + kNumMerge; ++b) light += c.host.bin_count[b];
@@ -846,12 +919,7 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
                                    &stats.launches[WINGSPAN_TIER_HASH]);
         LAUNCH_CHECK("hash symbolic");
         if ((s = timer_stop(c, WINGSPAN_TIER_HASH)) != WINGSPAN_OK) return s;
-        if (wtab) {
-            const int64_t entries = B->nrows * static_cast<int64_t>(c.L.nwin + 1);
-            build_window_table<<<blocks_for(entries, 256), 256, 0, light_st>>>(B->row_ptr, B->col_idx, B->nrows,
-                                                                               c.L.nwin, c.L.wcols, c.wtab);
-            LAUNCH_CHECK("build_window_table");
-        }
+        if (wtab && !wtab_first && (s = launch_window_table(c, B, light_st)) != WINGSPAN_OK) return s;
         if (side) HIP_TRY(hipEventRecord(side->join, side->st));
         return WINGSPAN_OK;
     };
@@ -865,7 +933,7 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
     if (cnt) {
         launch_bitmap(B->ncols, static_cast<unsigned>(cnt), c.st, M, perm + start, c.row_nnz,
                       caching ? c.slot_of_row : nullptr, caching ? c.cache : nullptr, c.L.row_words,
-                      c.L.cache_rows);
+                      c.L.cache_rows, c.wtab, c.L.nwin, c.L.wcols);
         stats.launches[WINGSPAN_TIER_DENSE]++;
         LAUNCH_CHECK("bitmap symbolic");
     }
@@ -944,6 +1012,9 @@ wingspan_status numeric_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
     int32_t light = 0;
     for (int b = kBinTiny0; b < kBinTiny0 + kNumTiny; ++b) light += c.host.bin_count[b];
     for (int b = kBinHash0; b < kBinMerge0 + kNumMerge; ++b) light += c.host.bin_count[b];
+    if ((cnt || c.host.bin_count[kBinMergeLong] > 0) && !c.wtab_ready &&
+        (s = launch_window_table(c, B, c.st)) != WINGSPAN_OK)
+        return s;
     // untimed, the tiny and hash tiers run on a side stream beside the dense kernel (forked after the analysis,
     // joined before the spill tier); timed, every tier runs in turn on the caller's stream
     SideStream *side = nullptr;
@@ -987,12 +1058,6 @@ wingspan_status numeric_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
     };
     if (!side && (s = light_tiers()) != WINGSPAN_OK) return s;
 
-    if (cnt && !c.wtab_ready) {
-        const int64_t entries = B->nrows * static_cast<int64_t>(c.L.nwin + 1);
-        build_window_table<<<blocks_for(entries, 256), 256, 0, c.st>>>(B->row_ptr, B->col_idx, B->nrows, c.L.nwin,
-                                                                       c.L.wcols, c.wtab);
-        LAUNCH_CHECK("build_window_table");
-    }
     // the dense tier's time covers its one kernel launch only
     if ((s = timer_start(c, WINGSPAN_TIER_DENSE)) != WINGSPAN_OK) return s;
     if (cnt && c.L.rank_mode) {
@@ -1003,12 +1068,7 @@ wingspan_status numeric_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
                                                                 cached ? c.slot_of_row : nullptr, c.rrows);
         LAUNCH_CHECK("rank rows");
         const uint32_t *cache = cached ? c.cache : nullptr;
-        if (!c.o.wide_offsets && offsets_fit_32<V>(B))
-            dense_rank_kernel<V, false, true><<<rank_grid(cnt), RankShape<V>::BLOCK, 0, c.st>>>(
-                M, c.rrows, cnt, c.wtab, c.L.nwin, B->ncols, sink, c_col, c_val, c.ctrl, cache, c.L.row_words);
-        else
-            dense_rank_kernel<V, false, false><<<rank_grid(cnt), RankShape<V>::BLOCK, 0, c.st>>>(
-                M, c.rrows, cnt, c.wtab, c.L.nwin, B->ncols, sink, c_col, c_val, c.ctrl, cache, c.L.row_words);
+        launch_rank<V, false>(c, M, B, cnt, sink, c_col, c_val, cache);
         stats.launches[WINGSPAN_TIER_DENSE]++;
         LAUNCH_CHECK("dense rank numeric");
     } else if (cnt) {
@@ -1093,12 +1153,7 @@ wingspan_status sharded_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
 
     int32_t start, cnt;
     bin_range(c, kBinDense0, kNumClasses, &start, &cnt);
-    if (cnt) {
-        const int64_t entries = B->nrows * static_cast<int64_t>(c.L.nwin + 1);
-        build_window_table<<<blocks_for(entries, 256), 256, 0, c.st>>>(B->row_ptr, B->col_idx, B->nrows, c.L.nwin,
-                                                                       c.L.wcols, c.wtab);
-        LAUNCH_CHECK("build_window_table");
-    }
+    if (cnt && (s = launch_window_table(c, B, c.st)) != WINGSPAN_OK) return s;
     if ((s = timer_start(c, WINGSPAN_TIER_DENSE)) != WINGSPAN_OK) return s;
     if (cnt) {
         // binning sends dense rows here only in rank mode; the column bitmaps come from the kernel's own
@@ -1106,14 +1161,7 @@ wingspan_status sharded_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
         rank_rows<<<blocks_for(cnt, 256), 256, 0, c.st>>>(perm + start, cnt, A->row_ptr, nullptr, nullptr,
                                                             c.rrows);
         LAUNCH_CHECK("rank rows");
-        if (!c.o.wide_offsets && offsets_fit_32<V>(B))
-            dense_rank_kernel<V, true, true><<<rank_grid(cnt), RankShape<V>::BLOCK, 0, c.st>>>(
-                M, c.rrows, cnt, c.wtab, c.L.nwin, B->ncols, sink, pool_col, pool_val, c.ctrl, nullptr,
-                c.L.row_words);
-        else
-            dense_rank_kernel<V, true, false><<<rank_grid(cnt), RankShape<V>::BLOCK, 0, c.st>>>(
-                M, c.rrows, cnt, c.wtab, c.L.nwin, B->ncols, sink, pool_col, pool_val, c.ctrl, nullptr,
-                c.L.row_words);
+        launch_rank<V, true>(c, M, B, cnt, sink, pool_col, pool_val, nullptr);
         stats.launches[WINGSPAN_TIER_DENSE]++;
         LAUNCH_CHECK("dense rank single pass");
     }
