@@ -49,114 +49,255 @@ struct Mats {
 
 // ---------------------------------------------------------------------------
 // Tiny tier: rows with at most S products, one aligned segment of S lanes per
-// row. Lane l of the segment fetches product l into registers; the segment
-// bitonic-sorts (column, product) pairs with lane shuffles, sums runs of equal
-// columns with a segmented scan, and the last lane of each run emits.
+// row, R rows per segment at once. Lane l of the segment fetches product l into
+// registers; the segment bitonic-sorts (column, lane) keys, and the first lane
+// of each run of equal columns adds the run's products, in the order of A's
+// entries, and emits.
+//
+// Bound by B's gathers (short rows: 3.3 GB of lines fetched for 0.77 GB of
+// entries at the size below, 7 TB/s with C's writes) once the chain of dependent
+// loads (row, A.row_ptr, A.col, B.row_ptr, B) is hidden; the symbolic kernel by
+// VALU issue of the sort. R rows per segment put R chains in
+// flight; the sort moves keys alone, one register each, with DPP and permlane
+// swaps (no LDS crossbar), and the products follow with one permutation.
+// Measured on 1 M rows of 64 products (double, 8 A entries each): one row per
+// wave and (key, product) pairs through the LDS crossbar 1.09 ms numeric and
+// 0.55 ms symbolic; here 0.58 and 0.28 ms (one row per segment: 0.64 and 0.40).
 // ---------------------------------------------------------------------------
-template <int S, typename V, bool NUM>
+
+// The value of lane l ^ J, within every aligned group of 2J lanes.
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x, bool upper) {
+    const int v = static_cast<int>(x);
+    if constexpr (J == 1) return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, false));
+    if constexpr (J == 2) return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, false));
+    if constexpr (J == 4) {
+        // banks of four lanes within a row of 16: 0 and 2 read four lanes up, 1 and 3 four lanes down
+        const int t = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xf, 0x5, false);
+        return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false));
+    }
+    if constexpr (J == 8) return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, false));
+    if constexpr (J == 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return upper ? s[0] : s[1];
+    }
+    const auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return upper ? s[0] : s[1];
+}
+
+// One compare-exchange of the bitonic sort between lanes l and l ^ J; `keep_min`:
+// this lane keeps the smaller key.
+template <int J>
+__device__ __forceinline__ void bitonic_step(uint32_t &x, int ln, bool keep_min) {
+    const uint32_t o = lane_xor<J>(x, (ln & J) != 0);
+    const uint32_t lo = x < o ? x : o, hi = x < o ? o : x;
+    x = keep_min ? lo : hi;
+}
+template <int J>
+__device__ __forceinline__ void bitonic_step(uint64_t &x, int ln, bool keep_min) {
+    const bool upper = (ln & J) != 0;
+    const uint64_t o = static_cast<uint64_t>(lane_xor<J>(static_cast<uint32_t>(x >> 32), upper)) << 32 |
+                       lane_xor<J>(static_cast<uint32_t>(x), upper);
+    x = (o < x) == keep_min ? o : x;   // (keys are distinct, or pads)
+}
+// Merges sorted groups of K / 2 lanes into sorted groups of K (alternately
+// ascending and descending; the last ascends).
+template <int K, int J, int R, typename Key>
+__device__ __forceinline__ void bitonic_merge(Key (&x)[R], int ln) {
+    const bool keep_min = ((ln & J) == 0) == ((ln & K) == 0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) bitonic_step<J>(x[r], ln, keep_min);
+    if constexpr (J > 1) bitonic_merge<K, J / 2, R>(x, ln);
+}
+template <int S, int K, int R, typename Key>
+__device__ __forceinline__ void bitonic_sort(Key (&x)[R], int sl) {
+    bitonic_merge<K, K / 2, R>(x, sl);
+    if constexpr (K < S) bitonic_sort<S, 2 * K, R>(x, sl);
+}
+
+// Inclusive prefix sum within aligned groups of S lanes (VALU only).
+template <int S>
+__device__ __forceinline__ int seg_incl_sum(int x, int sl) {
+    if constexpr (S == 8) {
+        const int y1 = __builtin_amdgcn_update_dpp(0, x, kDppRowShr1, 0xf, 0xf, false);
+        x += sl >= 1 ? y1 : 0;
+        const int y2 = __builtin_amdgcn_update_dpp(0, x, kDppRowShr2, 0xf, 0xf, false);
+        x += sl >= 2 ? y2 : 0;
+        const int y4 = __builtin_amdgcn_update_dpp(0, x, kDppRowShr4, 0xf, 0xf, false);
+        x += sl >= 4 ? y4 : 0;
+        return x;
+    }
+    x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr1, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr2, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr4, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr8, 0xf, 0xf, false);
+    if constexpr (S >= 32) x += __builtin_amdgcn_update_dpp(0, x, kDppRowBcast15, 0xa, 0xf, false);
+    if constexpr (S >= 64) x += __builtin_amdgcn_update_dpp(0, x, kDppRowBcast31, 0xc, 0xf, false);
+    return x;
+}
+
+// Key: uint32_t where a column and a lane of the segment fit it (ncols <
+// 2^32 / S), else uint64_t. All lanes of a wave stay active throughout, as the
+// lane moves need.
+template <int S, int R, typename Key, typename V, bool NUM>
 __global__ void __launch_bounds__(256) tiny_kernel(Mats<V> M, const int32_t *__restrict__ rows,
                                                    int32_t nrows, int32_t *__restrict__ row_nnz, RowSink out,
                                                    int32_t *__restrict__ c_col, V *__restrict__ c_val,
                                                    Control *ctrl) {
-    constexpr int G = 256 / S;
+    constexpr int SEGS = kWave / S;        // rows of a wave side by side
+    constexpr int LOG2S = S == 8 ? 3 : (S == 16 ? 4 : (S == 32 ? 5 : 6));
+    constexpr Key kPad = ~Key(0);
+    __shared__ int32_t s_mark[256 / kWave][R][kWave];
     const int ln = lane_id();
     const int sl = ln & (S - 1);
-    const int gidx = blockIdx.x * G + static_cast<int>(threadIdx.x) / S;
-    if (gidx >= nrows) return;   // whole segment leaves together
-    const int row = rows[gidx];
-    const int a_lo = M.a_rp[row], a_hi = M.a_rp[row + 1];
-
-    int key = kPadKey;
-    double val = 0.0;
-    int base = 0;
-    for (int a0 = a_lo; a0 < a_hi; a0 += S) {
-        const int a = a0 + sl;
-        int bs = 0, len = 0;
-        double av = 0.0;
-        if (a < a_hi) {
-            const int32_t k = M.a_col[a];
-            bs = M.b_rp[k];
-            len = M.b_rp[k + 1] - bs;
-            if (NUM) av = to_d(M.a_val[a]);
-        }
-        const int incl = group_incl_scan<S>(len);
-        const int tot = __shfl(incl, S - 1, S);
-        if (tot > 0) {
-            const int p = sl - base;
-            const int q = p < 0 ? 0 : (p < tot ? p : tot - 1);
-            const int o = group_count_le<S>(incl, q);
-            const int bs_o = __shfl(bs, o, S);
-            const int ex_o = __shfl(incl - len, o, S);
-            double av_o = 0.0;
-            if (NUM) av_o = __shfl(av, o, S);
-            if (p >= 0 && p < tot) {
-                const int b = bs_o + (q - ex_o);
-                key = M.b_col[b];
-                if (NUM) val = av_o * to_d(M.b_val[b]);
-            }
-            base += tot;
-        }
-    }
-
-    // bitonic sort of the segment by column
-#pragma unroll
-    for (int k = 2; k <= S; k <<= 1) {
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const int ok = __shfl_xor(key, j, S);
-            double ov = 0.0;
-            if (NUM) ov = __shfl_xor(val, j, S);
-            const bool up = (sl & k) == 0;
-            const bool lower = (sl & j) == 0;
-            const bool take = (lower == up) ? (ok < key) : (ok > key);
-            if (take) {
-                key = ok;
-                if (NUM) val = ov;
-            }
-        }
-    }
-
-    const int prv = __shfl_up(key, 1, S);
-    const int nxt = __shfl_down(key, 1, S);
-    if (NUM) {
-        // segmented inclusive sum over runs of equal keys
-        int start = (sl == 0 || prv != key) ? sl : 0;
-#pragma unroll
-        for (int o = 1; o < S; o <<= 1) {
-            const int y = __shfl_up(start, o, S);
-            if (sl >= o) start = start > y ? start : y;
-        }
-#pragma unroll
-        for (int o = 1; o < S; o <<= 1) {
-            const double y = __shfl_up(val, o, S);
-            if (sl - o >= start) val += y;
-        }
-    }
-    const bool tail = key != kPadKey && (sl == S - 1 || nxt != key);
-    const uint64_t bal = ballot(tail);
     const int gbase = ln & ~(S - 1);
-    const uint64_t gmask = (S == 64) ? ~0ull : (((1ull << S) - 1ull) << gbase);
-    const uint64_t mine = bal & gmask;
-    const int count = __popcll(mine);
-    if (!NUM) {
-        if (sl == 0) row_nnz[row] = count;
-        return;
+    const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
+    const int g0 = (static_cast<int>(blockIdx.x) * (256 / kWave) + wv) * (R * SEGS) + gbase / S;
+    if (g0 - gbase / S >= nrows) return;   // the whole wave
+
+    int row[R], a_lo[R], a_hi[R];
+    int64_t cb[R], seg[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int g = g0 + r * SEGS;
+        row[r] = rows[g < nrows ? g : nrows - 1];
     }
-    const int rank = __popcll(mine & ((1ull << ln) - 1ull));
-    int64_t cb, seg;
-    if (!out.pooled()) {
-        cb = out.c_rp[row];
-        seg = out.c_rp[row + 1] - cb;
-        if (sl == 0 && count != seg) atomicOr(&ctrl->error_flags, kErrRowMismatch);
-    } else {
-        int64_t b = 0, l = 0;
-        if (sl == 0) b = out.claim(row, count, &l);
-        cb = shfl_i64(b, 0, S);
-        seg = shfl_i64(l, 0, S);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        a_lo[r] = M.a_rp[row[r]];
+        a_hi[r] = M.a_rp[row[r] + 1];
+        if (NUM) {
+            cb[r] = out.pooled() ? 0 : out.c_rp[row[r]];
+            seg[r] = out.pooled() ? 0 : out.c_rp[row[r] + 1] - cb[r];
+        }
+        if (g0 + r * SEGS >= nrows) a_hi[r] = a_lo[r];
     }
-    if (tail && rank < seg) {
-        c_col[cb + rank] = key;
-        c_val[cb + rank] = static_cast<V>(val);
+    // products, S A entries at a time (one round unless B rows are empty)
+    int32_t col[R];
+    double prod[R];
+    int base[R];   // the row's products of the rounds so far
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        col[r] = 0;
+        prod[r] = 0.0;
+        base[r] = 0;
+    }
+    for (int a0 = 0;; a0 += S) {
+        bool more = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) more |= a_lo[r] + a0 < a_hi[r];
+        if (ballot(more) == 0ull) break;
+        int k[R], bs[R], len[R], own[R], tot[R];
+        V av[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int a = a_lo[r] + a0 + sl;
+            k[r] = -1;
+            av[r] = V(0);
+            if (a < a_hi[r]) {
+                k[r] = M.a_col[a];
+                if (NUM) av[r] = M.a_val[a];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            bs[r] = 0;
+            len[r] = 0;
+            if (k[r] >= 0) {
+                bs[r] = M.b_rp[k[r]];
+                len[r] = M.b_rp[k[r] + 1] - bs[r];
+            }
+        }
+        // every A entry with products marks the lane of its first; the last mark at or before a lane is its owner
+#pragma unroll
+        for (int r = 0; r < R; ++r) s_mark[wv][r][ln] = 0;
+        wave_lds_fence();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int incl = seg_incl_sum<S>(len[r], sl);
+            tot[r] = __shfl(incl, S - 1, S);
+            bs[r] -= incl - len[r] + base[r];   // product p of the row: entry bs + p of B
+            const int at = base[r] + incl - len[r];
+            if (len[r] > 0 && at < S) s_mark[wv][r][gbase + at] = ln + 1;
+        }
+        wave_lds_fence();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            own[r] = wave_incl_max(s_mark[wv][r][ln]) - 1;
+            own[r] = own[r] > 0 ? own[r] : 0;
+        }
+        wave_lds_fence();
+        int at[R];
+        bool live[R];
+        V bv[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            live[r] = sl >= base[r] && sl < base[r] + tot[r];
+            at[r] = __shfl(bs[r], own[r], kWave) + sl;
+            base[r] += tot[r];
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            bv[r] = V(0);
+            if (live[r]) {
+                col[r] = M.b_col[at[r]];
+                if (NUM) bv[r] = M.b_val[at[r]];
+            }
+        }
+        if (NUM) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double a = to_d(static_cast<V>(__shfl(av[r], own[r], kWave)));
+                if (live[r]) prod[r] = a * to_d(bv[r]);
+            }
+        }
+    }
+
+    Key x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        x[r] = sl < base[r] ? static_cast<Key>(static_cast<uint32_t>(col[r])) << LOG2S | static_cast<Key>(sl) : kPad;
+    bitonic_sort<S, 2, R>(x, sl);
+
+    const uint64_t gmask = S == 64 ? ~0ull : ((1ull << (S & 63)) - 1ull) << gbase;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t c = static_cast<uint32_t>(x[r] >> LOG2S);
+        const uint32_t prev = static_cast<uint32_t>(
+            __builtin_amdgcn_update_dpp(0, static_cast<int>(c), kDppWaveShr1, 0xf, 0xf, false));
+        const bool head = sl < base[r] && (sl == 0 || prev != c);
+        const uint64_t mine = ballot(head) & gmask;
+        const int count = __popcll(mine);
+        const bool valid = g0 + r * SEGS < nrows;   // (a segment past the rows has no products and writes nothing)
+        if (!NUM) {
+            if (sl == 0 && valid) row_nnz[row[r]] = count;
+            continue;
+        }
+        double v = __shfl(prod[r], static_cast<int>(x[r]) & (S - 1), S);
+        if (ballot(sl < base[r] && !head) != 0ull) {
+            // the run's other products, one lane further each time
+            const uint64_t after = ln < kWave - 1 ? mine >> (ln + 1) : 0ull;
+            const int n = after ? __ffsll(static_cast<long long>(after)) : base[r] - sl;
+            double t = v;
+            for (int d = 1; ballot(head && d < n) != 0ull; ++d) {
+                t = __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(t), 0x130, 0xf, 0xf, false),
+                                     __builtin_amdgcn_update_dpp(0, __double2loint(t), 0x130, 0xf, 0xf, false));
+                if (head && d < n) v += t;
+            }
+        }
+        if (!out.pooled()) {
+            if (sl == 0 && valid && count != seg[r]) atomicOr(&ctrl->error_flags, kErrRowMismatch);
+        } else {
+            int64_t b = 0, l = 0;
+            if (sl == 0 && valid) b = out.claim(row[r], count, &l);
+            cb[r] = shfl_i64(b, 0, S);
+            seg[r] = shfl_i64(l, 0, S);
+        }
+        const int rank = __popcll(mine & ((1ull << ln) - 1ull));
+        if (head && rank < seg[r]) {
+            __builtin_nontemporal_store(static_cast<int32_t>(c), &c_col[cb[r] + rank]);
+            __builtin_nontemporal_store(static_cast<V>(v), &c_val[cb[r] + rank]);
+        }
     }
 }
 

@@ -61,6 +61,9 @@ constexpr int64_t kPoolBytes = int64_t(1) << 30;   // spill pool: at most this, 
 constexpr int64_t kMaxSlabCap = int64_t(1) << 27;
 constexpr int kMaxSlabs = 256;                      // largest tables the pool holds at once (at most)
 constexpr int64_t kMaxSpillGrid = 8192;             // spill workgroups per size class at most
+// Register tier: from this many rows a segment takes several at once (2 numeric, 4 symbolic: best of 1, 2, 4 on 1 M
+// rows); fewer rows are spread over more waves.
+constexpr int32_t kTinyManyRows = 32768;
 constexpr size_t kAlign = 256;
 
 thread_local std::string g_err;
@@ -705,14 +708,28 @@ void bin_range(const Ctx &c, int b0, int nb, int32_t *start, int32_t *count) {
 // ---------------------------------------------------------------------------
 // Kernel dispatch over compile-time shapes.
 // ---------------------------------------------------------------------------
+template <int S, typename V, bool NUM>
+void launch_tiny_s(hipStream_t st, int64_t ncols, const Mats<V> &M, const int32_t *rows, int32_t cnt,
+                   int32_t *row_nnz, RowSink out, int32_t *c_col, V *c_val, Control *ctrl) {
+#define WS_TINY(R, KEY) \
+    tiny_kernel<S, R, KEY, V, NUM><<<blocks_for(cnt, R * 256 / S), 256, 0, st>>>(M, rows, cnt, row_nnz, out, c_col, c_val, ctrl)
+    if (ncols < (int64_t(1) << 32) / S) {
+        if (cnt >= kTinyManyRows) WS_TINY((NUM ? 2 : 4), uint32_t);
+        else WS_TINY(1, uint32_t);
+    } else {
+        WS_TINY(1, uint64_t);
+    }
+#undef WS_TINY
+}
+
 template <typename V, bool NUM>
-void launch_tiny(int s_idx, unsigned grid, hipStream_t st, const Mats<V> &M, const int32_t *rows,
-                 int32_t cnt, int32_t *row_nnz, RowSink out, int32_t *c_col, V *c_val, Control *ctrl) {
+void launch_tiny(int s_idx, hipStream_t st, int64_t ncols, const Mats<V> &M, const int32_t *rows, int32_t cnt,
+                 int32_t *row_nnz, RowSink out, int32_t *c_col, V *c_val, Control *ctrl) {
     switch (s_idx) {
-        case 0: tiny_kernel<8, V, NUM><<<grid, 256, 0, st>>>(M, rows, cnt, row_nnz, out, c_col, c_val, ctrl); break;
-        case 1: tiny_kernel<16, V, NUM><<<grid, 256, 0, st>>>(M, rows, cnt, row_nnz, out, c_col, c_val, ctrl); break;
-        case 2: tiny_kernel<32, V, NUM><<<grid, 256, 0, st>>>(M, rows, cnt, row_nnz, out, c_col, c_val, ctrl); break;
-        default: tiny_kernel<64, V, NUM><<<grid, 256, 0, st>>>(M, rows, cnt, row_nnz, out, c_col, c_val, ctrl); break;
+        case 0: launch_tiny_s<8, V, NUM>(st, ncols, M, rows, cnt, row_nnz, out, c_col, c_val, ctrl); break;
+        case 1: launch_tiny_s<16, V, NUM>(st, ncols, M, rows, cnt, row_nnz, out, c_col, c_val, ctrl); break;
+        case 2: launch_tiny_s<32, V, NUM>(st, ncols, M, rows, cnt, row_nnz, out, c_col, c_val, ctrl); break;
+        default: launch_tiny_s<64, V, NUM>(st, ncols, M, rows, cnt, row_nnz, out, c_col, c_val, ctrl); break;
     }
 }
 
@@ -897,9 +914,8 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
             const int b = kBinTiny0 + i;
             const int32_t nb = c.host.bin_count[b];
             if (!nb) continue;
-            const int S = 8 << i;
-            launch_tiny<float, false>(i, blocks_for(int64_t(nb) * S, 256), light_st, M, perm + c.host.bin_offset[b],
-                                      nb, c.row_nnz, RowSink{}, nullptr, nullptr, c.ctrl);
+            launch_tiny<float, false>(i, light_st, B->ncols, M, perm + c.host.bin_offset[b], nb, c.row_nnz, RowSink{},
+                                      nullptr, nullptr, c.ctrl);
             stats.launches[WINGSPAN_TIER_TINY]++;
         }
         LAUNCH_CHECK("tiny symbolic");
@@ -1030,9 +1046,8 @@ wingspan_status numeric_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
             const int b = kBinTiny0 + i;
             const int32_t nb = c.host.bin_count[b];
             if (!nb) continue;
-            const int S = 8 << i;
-            launch_tiny<V, true>(i, blocks_for(int64_t(nb) * S, 256), light_st, M, perm + c.host.bin_offset[b], nb,
-                                 nullptr, sink, c_col, c_val, c.ctrl);
+            launch_tiny<V, true>(i, light_st, B->ncols, M, perm + c.host.bin_offset[b], nb, nullptr, sink, c_col, c_val,
+                                 c.ctrl);
             stats.launches[WINGSPAN_TIER_TINY]++;
         }
         LAUNCH_CHECK("tiny numeric");
@@ -1130,9 +1145,8 @@ wingspan_status sharded_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
         const int b = kBinTiny0 + i;
         const int32_t cnt = c.host.bin_count[b];
         if (!cnt) continue;
-        const int S = 8 << i;
-        launch_tiny<V, true>(i, blocks_for(int64_t(cnt) * S, 256), c.st, M, perm + c.host.bin_offset[b], cnt,
-                             nullptr, sink, pool_col, pool_val, c.ctrl);
+        launch_tiny<V, true>(i, c.st, B->ncols, M, perm + c.host.bin_offset[b], cnt, nullptr, sink, pool_col, pool_val,
+                             c.ctrl);
         stats.launches[WINGSPAN_TIER_TINY]++;
     }
     LAUNCH_CHECK("tiny single pass");
