@@ -76,11 +76,31 @@ __global__ void __launch_bounds__(1024) scan_partials(int64_t *partials, int64_t
     if (threadIdx.x == 0) partials[nb] = carry_s;
 }
 
-// out[i] = exclusive prefix for i < n, out[n] = total.
-template <typename In>
+// What a scan's output adds to a checksum of it: the sum of out[i] * (2i + 1)
+// for i <= n, modulo 2^64, one atomic per workgroup.
+template <int BLOCK>
+__device__ __forceinline__ void add_checksum(uint64_t acc, uint64_t *sum, int64_t *scratch) {
+    acc = static_cast<uint64_t>(block_sum<BLOCK>(static_cast<int64_t>(acc), scratch));
+    if (threadIdx.x == 0)
+        atomicAdd(reinterpret_cast<unsigned long long *>(sum), static_cast<unsigned long long>(acc));
+}
+
+// out[i] = exclusive prefix for i < n, out[n] = total. OWN: partials holds the
+// tile sums themselves, and each workgroup adds up those before its tile (a few
+// hundred numbers, in the L2: one launch less). csum (or null) receives out's
+// checksum.
+constexpr int64_t kScanOwnTiles = 1024;   // tiles a workgroup adds up by itself at most
+template <typename In, bool OWN>
 __global__ void __launch_bounds__(kScanBlock) scan_tiles(In in, int64_t n, const int64_t *partials,
-                                                         int64_t nb, int64_t *out) {
+                                                         int64_t nb, int64_t *out, uint64_t *csum) {
     __shared__ int64_t wsum[kScanBlock / kWave];
+    int64_t first = 0;
+    if constexpr (OWN) {
+        for (int64_t i = threadIdx.x; i < blockIdx.x; i += kScanBlock) first += partials[i];
+        first = block_sum<kScanBlock>(first, wsum);
+    } else {
+        first = partials[blockIdx.x];
+    }
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanTile + threadIdx.x * kScanItems;
     int64_t v[kScanItems];
     int64_t s = 0;
@@ -100,32 +120,120 @@ __global__ void __launch_bounds__(kScanBlock) scan_tiles(In in, int64_t n, const
     }
     if (ln == kWave - 1) wsum[w] = incl;
     __syncthreads();
-    int64_t run = partials[blockIdx.x];
+    int64_t run = first;
     for (int i = 0; i < kScanBlock / kWave; ++i) run += (i < w) ? wsum[i] : 0;
     run += incl - s;
+    uint64_t acc = 0;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         const int64_t idx = base + i;
-        if (idx < n) out[idx] = run;
+        if (idx < n) {
+            out[idx] = run;
+            acc += static_cast<uint64_t>(run) * static_cast<uint64_t>(2 * idx + 1);
+        }
         run += v[i];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = partials[nb];
+    // the last item of the last tile: run is the total
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanBlock - 1) {
+        out[n] = run;
+        acc += static_cast<uint64_t>(run) * static_cast<uint64_t>(2 * n + 1);
+    }
+    if (csum != nullptr) {
+        __syncthreads();
+        add_checksum<kScanBlock>(acc, csum, wsum);
+    }
 }
 
-// Products of row i of A: with pref the exclusive prefix of B-row lengths
-// over A's entries, the row's entries [a_rp[i], a_rp[i+1]) select B rows whose
-// lengths sum to pref[a_rp[i+1]] - pref[a_rp[i]].
-__device__ __forceinline__ int64_t row_products_of(const int32_t *__restrict__ a_rp,
-                                                   const int64_t *__restrict__ pref, int64_t i) {
-    return pref[a_rp[i + 1]] - pref[a_rp[i]];
+// ---------------------------------------------------------------------------
+// Row product counts. One pass over A's entries gathers the lengths of the B
+// rows they select: loc[i] is the exclusive prefix of the lengths within entry
+// i's tile of kScanTile entries, tile_sum[t] the tile's total. A row's products
+// are the difference of its ends' prefixes plus the totals of the tiles between
+// (none for nearly every row), so no second pass adds the tiles' offsets in
+// (the gather is what a pass costs: 8 M entries 47 us for the sums and 79 us for
+// the prefixes before, one pass of 51 us now). The first workgroup also clears the
+// control blocks and the stamp it is given, which nothing else touches meanwhile.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(kScanBlock) brow_tile_prefix(const int32_t *__restrict__ a_col,
+                                                               const int32_t *__restrict__ b_rp, int64_t nnz,
+                                                               int64_t *__restrict__ loc,
+                                                               int64_t *__restrict__ tile_sum, int32_t *clear0,
+                                                               int32_t *clear1, int clear_words, Stamp *stamp) {
+    // (a gap after every kScanItems items: threads walk kScanItems consecutive ones each)
+    constexpr int ITEM = kScanItems + 1;
+    __shared__ int64_t s_len[kScanBlock * ITEM];
+    __shared__ int64_t wsum[kScanBlock / kWave];
+    const BRowLenIn in{a_col, b_rp};
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanTile;
+    int64_t v[kScanItems];
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+        const int64_t idx = base + i * kScanBlock + threadIdx.x;
+        v[i] = idx < nnz ? in(idx) : 0;
+    }
+    if (blockIdx.x == 0) {
+        for (int i = threadIdx.x; i < clear_words; i += kScanBlock) {
+            if (clear0 != nullptr) clear0[i] = 0;
+            if (clear1 != nullptr) clear1[i] = 0;
+        }
+        if (stamp != nullptr && threadIdx.x == 0) *stamp = Stamp{};
+    }
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+        const int p = i * kScanBlock + threadIdx.x;
+        s_len[p + p / kScanItems] = v[i];
+    }
+    __syncthreads();
+    int64_t s = 0;
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+        v[i] = s_len[threadIdx.x * ITEM + i];
+        s += v[i];
+    }
+    const int ln = lane_id();
+    const int w = threadIdx.x / kWave;
+    int64_t incl = s;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t y = __shfl_up(incl, o, kWave);
+        if (ln >= o) incl += y;
+    }
+    if (ln == kWave - 1) wsum[w] = incl;
+    __syncthreads();
+    int64_t run = incl - s;
+    for (int i = 0; i < w; ++i) run += wsum[i];
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+        s_len[threadIdx.x * ITEM + i] = run;
+        run += v[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+        const int p = i * kScanBlock + threadIdx.x;
+        if (base + p <= nnz) loc[base + p] = s_len[p + p / kScanItems];
+    }
+    if (threadIdx.x == kScanBlock - 1) tile_sum[blockIdx.x] = run;
+}
+
+// Products of a row holding A's entries [lo, hi). An end at the very end of the
+// entries and of a tile has no prefix of its own: its tile begins there.
+__device__ __forceinline__ int64_t row_products_of(int lo, int hi, int64_t nnz, const int64_t *__restrict__ loc,
+                                                   const int64_t *__restrict__ tile_sum) {
+    if (lo >= hi) return 0;
+    const int ta = lo / kScanTile, tb = hi / kScanTile;
+    int64_t f = (hi == nnz && hi % kScanTile == 0 ? 0 : loc[hi]) - loc[lo];
+    for (int t = ta; t < tb; ++t) f += tile_sum[t];
+    return f;
 }
 
 // out[i] = products of row i, for every row (the counts the binning uses).
-__global__ void __launch_bounds__(256) row_products_kernel(const int32_t *__restrict__ a_rp,
-                                                           const int64_t *__restrict__ pref, int64_t m,
+__global__ void __launch_bounds__(256) row_products_kernel(const int32_t *__restrict__ a_rp, int64_t nnz,
+                                                           const int64_t *__restrict__ loc,
+                                                           const int64_t *__restrict__ tile_sum, int64_t m,
                                                            int64_t *__restrict__ out) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < m) out[i] = row_products_of(a_rp, pref, i);
+    if (i < m) out[i] = row_products_of(a_rp[i], a_rp[i + 1], nnz, loc, tile_sum);
 }
 
 // The same exclusive scan in one workgroup of 1024 threads, for short
@@ -134,7 +242,7 @@ __global__ void __launch_bounds__(256) row_products_kernel(const int32_t *__rest
 // share's prefixes. out[n] = total.
 
 template <typename In>
-__global__ void __launch_bounds__(1024) scan_one_block(In in, int64_t n, int64_t *out) {
+__global__ void __launch_bounds__(1024) scan_one_block(In in, int64_t n, int64_t *out, uint64_t *csum) {
     __shared__ int64_t wsum[16];
     const int64_t per = (n + 1023) / 1024;
     const int64_t b = static_cast<int64_t>(threadIdx.x) * per;
@@ -163,17 +271,28 @@ __global__ void __launch_bounds__(1024) scan_one_block(In in, int64_t n, int64_t
         tot += wsum[i];
     }
     run += incl - s;
+    uint64_t acc = 0;
     for (int64_t i0 = b; i0 < e; i0 += 8) {
         int64_t v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = i0 + u < e ? in(i0 + u) : 0;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            if (i0 + u < e) out[i0 + u] = run;
+            if (i0 + u < e) {
+                out[i0 + u] = run;
+                acc += static_cast<uint64_t>(run) * static_cast<uint64_t>(2 * (i0 + u) + 1);
+            }
             run += v[u];
         }
     }
-    if (threadIdx.x == 0) out[n] = tot;
+    if (threadIdx.x == 0) {
+        out[n] = tot;
+        acc += static_cast<uint64_t>(tot) * static_cast<uint64_t>(2 * n + 1);
+    }
+    if (csum != nullptr) {
+        __syncthreads();
+        add_checksum<1024>(acc, csum, wsum);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -237,13 +356,31 @@ __device__ __forceinline__ int choose_bin(int64_t f, int k, int64_t c, const Bin
     return kBinSpill0 + class_of(f);
 }
 
-// Counts rows per bin and accumulates per-bin statistics. In the symbolic
-// phase it also writes row_nnz = 0 for rows without products.
-__global__ void __launch_bounds__(256) bin_count(const int32_t *__restrict__ a_rp,
-                                                 const int64_t *__restrict__ pref,
-                                                 const int64_t *__restrict__ c_rp, int64_t m,
-                                                 BinCfg cfg, Control *ctrl,
-                                                 int32_t *__restrict__ row_nnz) {
+// Binning: at most kBinBlocks workgroups, each over a contiguous share of the
+// rows, so that few workgroups add to the shared statistics (with one per 256
+// rows the adds to one address took 40 us on a million rows) and rows of a bin
+// keep their order across shares. bin_count counts a workgroup's rows of every
+// bin into hist[bin][workgroup] and notes each row's bin; bin_scatter turns the
+// counts into places.
+constexpr int kBinBlocks = 256;
+constexpr int kBinBlock = 1024;
+
+// Where a row's product count comes from: the prefixes (kept in row_prod for the
+// later phases), or row_prod as an earlier binning left it.
+struct RowProducts {
+    const int64_t *loc;        // null: row_prod holds the counts
+    const int64_t *tile_sum;
+    int64_t nnz;
+    int64_t *row_prod;
+};
+
+// In the symbolic phase (and the single pass) it also writes row_nnz = 0 for
+// rows without products; slot_of_row (or null) is set to -1.
+__global__ void __launch_bounds__(kBinBlock) bin_count(const int32_t *__restrict__ a_rp, RowProducts rp,
+                                                       const int64_t *__restrict__ c_rp, int64_t m, BinCfg cfg,
+                                                       Control *ctrl, int32_t *__restrict__ row_nnz,
+                                                       int32_t *__restrict__ slot_of_row,
+                                                       uint8_t *__restrict__ bin, int32_t *__restrict__ hist) {
     __shared__ int32_t s_cnt[kMaxBins];
     __shared__ unsigned long long s_prod[kMaxBins], s_annz[kMaxBins], s_cnnz[kMaxBins];
     for (int i = threadIdx.x; i < kMaxBins; i += blockDim.x) {
@@ -251,23 +388,47 @@ __global__ void __launch_bounds__(256) bin_count(const int32_t *__restrict__ a_r
         s_prod[i] = s_annz[i] = s_cnnz[i] = 0;
     }
     __syncthreads();
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < m) {
+    const int64_t share = (m + gridDim.x - 1) / gridDim.x;
+    const int64_t i0 = share * blockIdx.x, i1 = i0 + share < m ? i0 + share : m;
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kBinBlock) {
         const int32_t a0 = a_rp[i], a1 = a_rp[i + 1];
-        const int64_t f = row_products_of(a_rp, pref, i);
+        int64_t f;
+        if (rp.loc != nullptr) {
+            f = row_products_of(a0, a1, rp.nnz, rp.loc, rp.tile_sum);
+            rp.row_prod[i] = f;
+        } else {
+            f = rp.row_prod[i];
+        }
         const int64_t c = cfg.numeric ? (c_rp[i + 1] - c_rp[i]) : 0;
         int64_t bound;
         const int b = choose_bin(f, a1 - a0, c, cfg, &bound);
-        atomicAdd(&s_cnt[b], 1);
-        atomicAdd(&s_prod[b], static_cast<unsigned long long>(f));
-        atomicAdd(&s_annz[b], static_cast<unsigned long long>(a1 - a0));
-        atomicAdd(&s_cnnz[b], static_cast<unsigned long long>(c));
+        // a whole wave of one bin (usual where rows are alike) adds its sums once instead of lane by lane to one
+        // address; sums of 64 numbers below 2^25 fit 32 bits
+        const bool small = f < (1 << 25) && a1 - a0 < (1 << 25);   // (c <= f)
+        if (ballot(small && b == __builtin_amdgcn_readfirstlane(b)) == ~0ull) {
+            const int sf = wave_incl_sum(static_cast<int>(f)), sa = wave_incl_sum(a1 - a0);
+            const int sc = wave_incl_sum(static_cast<int>(c));
+            if (lane_id() == kWave - 1) {
+                atomicAdd(&s_cnt[b], kWave);
+                atomicAdd(&s_prod[b], static_cast<unsigned long long>(sf));
+                atomicAdd(&s_annz[b], static_cast<unsigned long long>(sa));
+                if (cfg.numeric) atomicAdd(&s_cnnz[b], static_cast<unsigned long long>(sc));
+            }
+        } else {
+            atomicAdd(&s_cnt[b], 1);
+            atomicAdd(&s_prod[b], static_cast<unsigned long long>(f));
+            atomicAdd(&s_annz[b], static_cast<unsigned long long>(a1 - a0));
+            if (cfg.numeric) atomicAdd(&s_cnnz[b], static_cast<unsigned long long>(c));
+        }
         if (bound > 0) atomicMax(reinterpret_cast<unsigned long long *>(&ctrl->spill_max_bound),
                                  static_cast<unsigned long long>(bound));
         if (!cfg.numeric && b == kBinEmpty) row_nnz[i] = 0;
+        if (slot_of_row != nullptr) slot_of_row[i] = -1;
+        bin[i] = static_cast<uint8_t>(b);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < kNumBins; b += blockDim.x) {
+        hist[b * gridDim.x + blockIdx.x] = s_cnt[b];
         if (s_cnt[b]) {
             atomicAdd(&ctrl->bin_count[b], s_cnt[b]);
             atomicAdd(reinterpret_cast<unsigned long long *>(&ctrl->stat_products[b]), s_prod[b]);
@@ -277,41 +438,75 @@ __global__ void __launch_bounds__(256) bin_count(const int32_t *__restrict__ a_r
     }
 }
 
-__global__ void bin_offsets(Control *ctrl, const int64_t *pref, int64_t nnz_a) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        int32_t run = 0;
-        for (int b = 0; b < kMaxBins; ++b) {
-            ctrl->bin_offset[b] = run;
-            run += ctrl->bin_count[b];
+// Writes each non-empty row's id into its bin's range of perm (the grid of
+// bin_count); the first workgroup records the bins' offsets, and the stamp when
+// it is given one (stamp->rp_sum from the scan that wrote C.row_ptr).
+__global__ void __launch_bounds__(kBinBlock) bin_scatter(const uint8_t *__restrict__ bin, int64_t m,
+                                                         const int32_t *__restrict__ hist, Control *ctrl,
+                                                         int32_t *__restrict__ perm, Stamp *stamp, const Stamp value,
+                                                         const Control *sums) {
+    __shared__ int32_t s_tot[kMaxBins], s_next[kMaxBins];
+    const int wv = threadIdx.x / kWave, ln = lane_id();
+    const int nblk = static_cast<int>(gridDim.x), blk = static_cast<int>(blockIdx.x);
+    {
+        // a wave's bins, all their counts loaded before the first is summed
+        constexpr int NW = kBinBlock / kWave, PER = kMaxBins / NW, Q = kBinBlocks / kWave;
+        int n[PER][Q];
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int b = wv + i * NW, k = ln + q * kWave;
+                n[i][q] = b < kNumBins && k < nblk ? hist[b * nblk + k] : 0;
+            }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            int tot = 0, before = 0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                tot += n[i][q];
+                before += ln + q * kWave < blk ? n[i][q] : 0;
+            }
+            tot = wave_incl_sum(tot);
+            before = wave_incl_sum(before);
+            if (ln == kWave - 1) {
+                s_tot[wv + i * NW] = tot;
+                s_next[wv + i * NW] = before;
+            }
         }
-        ctrl->total_products = pref[nnz_a];
-    }
-}
-
-// Writes each non-empty row's id into its bin's range of perm.
-__global__ void __launch_bounds__(256) bin_scatter(const int32_t *__restrict__ a_rp,
-                                                   const int64_t *__restrict__ pref,
-                                                   const int64_t *__restrict__ c_rp, int64_t m,
-                                                   BinCfg cfg, Control *ctrl,
-                                                   int32_t *__restrict__ perm) {
-    __shared__ int32_t s_cnt[kMaxBins];
-    __shared__ int32_t s_base[kMaxBins];
-    for (int b = threadIdx.x; b < kMaxBins; b += blockDim.x) s_cnt[b] = 0;
-    __syncthreads();
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    int b = -1, r = 0;
-    if (i < m) {
-        const int64_t f = row_products_of(a_rp, pref, i);
-        const int64_t c = cfg.numeric ? (c_rp[i + 1] - c_rp[i]) : 0;
-        int64_t bound;
-        b = choose_bin(f, a_rp[i + 1] - a_rp[i], c, cfg, &bound);
-        if (b != kBinEmpty) r = atomicAdd(&s_cnt[b], 1);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < kNumBins; k += blockDim.x)
-        if (s_cnt[k]) s_base[k] = atomicAdd(&ctrl->bin_cursor[k], s_cnt[k]);
+    if (wv == 0) {
+        static_assert(kMaxBins == kWave, "a lane per bin");
+        const int first = wave_incl_sum(s_tot[ln]) - s_tot[ln];
+        s_next[ln] += first;
+        if (blockIdx.x == 0) {
+            ctrl->bin_offset[ln] = first;
+            if (stamp != nullptr && ln == 0) {
+                *stamp = value;
+                stamp->rp_sum = sums->rp_sum;
+                stamp->magic = kStampMagic;
+            }
+        }
+    }
     __syncthreads();
-    if (b > kBinEmpty) perm[ctrl->bin_offset[b] + s_base[b] + r] = static_cast<int32_t>(i);
+    const int64_t share = (m + gridDim.x - 1) / gridDim.x;
+    const int64_t i0 = share * blockIdx.x, i1 = i0 + share < m ? i0 + share : m;
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kBinBlock) {
+        const int b = bin[i];
+        // one claim for all of a wave's rows of a bin, which keep their order
+        uint64_t left = ballot(b != kBinEmpty);
+        while (left) {
+            const int first = __ffsll(static_cast<long long>(left)) - 1;
+            const int b0 = __builtin_amdgcn_readlane(b, first);
+            const uint64_t same = ballot(b == b0);
+            int at = 0;
+            if (ln == first) at = atomicAdd(&s_next[b0], static_cast<int>(__popcll(same)));
+            at = __builtin_amdgcn_readlane(at, first);
+            if (b == b0) perm[at + __popcll(same & ((1ull << ln) - 1ull))] = static_cast<int32_t>(i);
+            left &= ~same;
+        }
+    }
 }
 
 // Zero-fill of the control block (a kernel, not a memset, so the sequence can
@@ -412,25 +607,29 @@ __global__ void __launch_bounds__(256) gather_rows(int64_t nrows, const int64_t 
     }
 }
 
-// Position-weighted checksum of C.row_ptr[0..m]: sum of rp[i] * (2i + 1)
-// modulo 2^64, added into *out (which the caller zeroes).
-__global__ void __launch_bounds__(256) rowptr_checksum(const int64_t *__restrict__ rp, int64_t m, uint64_t *out) {
+// Checksum of C.row_ptr[0..m] (the sum of rp[i] * (2i + 1) modulo 2^64) in
+// kRpParts parts, one per workgroup, into ctrl->rp_part; the first workgroup
+// clears the rest of the control block.
+__global__ void __launch_bounds__(1024) rowptr_checksum(const int64_t *__restrict__ rp, int64_t m, Control *ctrl) {
+    __shared__ int64_t scratch[1024 / kWave];
     uint64_t acc = 0;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i <= m;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x)
         acc += static_cast<uint64_t>(rp[i]) * static_cast<uint64_t>(2 * i + 1);
-    acc = wave_sum(acc);
-    if (lane_id() == 0) atomicAdd(reinterpret_cast<unsigned long long *>(out), static_cast<unsigned long long>(acc));
+    acc = static_cast<uint64_t>(block_sum<1024>(static_cast<int64_t>(acc), scratch));
+    if (threadIdx.x == 0) ctrl->rp_part[blockIdx.x] = acc;
+    if (blockIdx.x == 0) {
+        int32_t *p = reinterpret_cast<int32_t *>(ctrl);
+        constexpr int lo = offsetof(Control, rp_part) / 4, hi = lo + kRpParts * 2;
+        for (int i = threadIdx.x; i < static_cast<int>(sizeof(Control) / 4); i += blockDim.x)
+            if (i < lo || i >= hi) p[i] = 0;
+    }
 }
 
-// Writes the stamp (one thread); magic 0 invalidates it.
-__global__ void write_stamp(Stamp *stamp, Stamp value) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *stamp = value;
-}
-
-// Marks a stamp complete once its checksum has been added (one thread).
-__global__ void seal_stamp(Stamp *stamp) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) stamp->magic = kStampMagic;
+// The numeric binning the stamp describes is no longer what the workspace
+// holds (one thread).
+__global__ void drop_kept_bins(Stamp *stamp) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) stamp->num_bins = 0;
 }
 
 // Flags values that could produce a zero product: exact zeros, and (for

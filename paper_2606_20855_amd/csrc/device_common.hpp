@@ -37,6 +37,8 @@ constexpr int kBinSpill0 = kBinDense0 + kNumClasses;   // 37..52
 constexpr int kNumBins = kBinSpill0 + kNumClasses;     // 53
 constexpr int kMaxBins = 64;
 
+constexpr int kRpParts = 64;
+
 enum : int32_t {
     kErrProbeExhausted = 1,   // a hash table filled up (structure larger than C.row_ptr says)
     kErrRowMismatch = 2,      // a row produced a different entry count than C.row_ptr
@@ -68,7 +70,6 @@ constexpr uint64_t kStampMagic = 0x57535f5354525543ull;
 // Device-side control block, zeroed at the start of each phase and copied to
 // the host once the rows have been binned.
 struct Control {
-    int64_t total_products;
     int64_t spill_max_bound;
     int64_t c_nnz;
     unsigned long long pool_claimed;   // single pass: pool entries the rows have claimed
@@ -76,10 +77,10 @@ struct Control {
     int32_t error_flags;
     int32_t has_zero_values;   // some A or B value could give a zero product
     int32_t rank_next;         // the rank kernel's row claims
-    uint64_t rp_sum;           // numeric: checksum of the C.row_ptr it was given
+    uint64_t rp_sum;           // symbolic: checksum of the C.row_ptr it wrote
+    uint64_t rp_part[kRpParts];   // numeric: the checksum of the C.row_ptr it was given, in parts
     int32_t bin_count[kMaxBins];
     int32_t bin_offset[kMaxBins];
-    int32_t bin_cursor[kMaxBins];
     int64_t stat_products[kMaxBins];
     int64_t stat_annz[kMaxBins];
     int64_t stat_cnnz[kMaxBins];

@@ -1704,7 +1704,7 @@ __device__ void merge_sort_segment(int32_t *__restrict__ col, V *__restrict__ va
 
 // One row of the spill tier, processed by the whole workgroup in its slab.
 template <typename V, bool NUM>
-__device__ __forceinline__ void spill_row(const Mats<V> &M, int row, const int64_t *__restrict__ pref,
+__device__ __forceinline__ void spill_row(const Mats<V> &M, int row, const int64_t *__restrict__ row_prod,
                                           int64_t ncols, int32_t *__restrict__ keys, double *__restrict__ vals,
                                           int32_t *__restrict__ row_nnz, const RowSink &out,
                                           int32_t *__restrict__ c_col, V *__restrict__ c_val, Control *ctrl,
@@ -1718,7 +1718,7 @@ __device__ __forceinline__ void spill_row(const Mats<V> &M, int row, const int64
     if (NUM && !out.pooled()) {
         bound = out.c_rp[row + 1] - out.c_rp[row];
     } else {
-        const int64_t f = pref[a_hi] - pref[a_lo];
+        const int64_t f = row_prod[row];
         bound = f < ncols ? f : ncols;
     }
     int log2t = ceil_log2(2 * (bound > 0 ? bound : 1));
@@ -1798,7 +1798,7 @@ __device__ __forceinline__ void spill_row(const Mats<V> &M, int row, const int64
 
 template <typename V, bool NUM>
 __global__ void __launch_bounds__(kSpillBlock) spill_kernel(
-    Mats<V> M, const int32_t *__restrict__ rows, int32_t nrows, const int64_t *__restrict__ pref,
+    Mats<V> M, const int32_t *__restrict__ rows, int32_t nrows, const int64_t *__restrict__ row_prod,
     int64_t ncols, char *__restrict__ pool, int64_t slab_cap, int32_t *__restrict__ row_nnz,
     RowSink out, int32_t *__restrict__ c_col, V *__restrict__ c_val,
     Control *ctrl, int32_t *next) {
@@ -1826,7 +1826,7 @@ __global__ void __launch_bounds__(kSpillBlock) spill_kernel(
         const int ri = uniform(s_row);
         __syncthreads();
         if (ri >= nrows) break;
-        spill_row<V, NUM>(M, rows[ri], pref, ncols, keys, vals, row_nnz, out, c_col, c_val, ctrl, scratch,
+        spill_row<V, NUM>(M, rows[ri], row_prod, ncols, keys, vals, row_nnz, out, c_col, c_val, ctrl, scratch,
                           s_keys, s_vals, mark, ctot, s_claim);
     }
 }

@@ -286,15 +286,19 @@ Layout plan(const wingspan_csr *A, const wingspan_csr *B, const Opts &o, size_t 
 // ---------------------------------------------------------------------------
 struct Ctx {
     hipStream_t st;
+    int64_t nrows_a = 0;
     int dtype_f64 = -1;   // numeric value type: 1 double, 0 float, -1 unknown (symbolic)
     Opts o;
     Layout L;
     char *ws;
     Control *ctrl;
-    int64_t *pref;
+    int64_t *loc;         // tile-local prefixes of B-row lengths over A's entries
     int32_t *row_nnz;
     int32_t *perm;
     RankRow *rrows;
+    int64_t *row_prod;    // products of every row, and each row's bin: in the rank rows' memory, which the dense
+    uint8_t *bin;         // rows' descriptions take over once the rows are binned
+    int32_t *hist;        // the binning's counts, in the spill pool's memory
     int64_t *partials;
     int32_t *wtab;
     char *pool;
@@ -314,10 +318,13 @@ struct Ctx {
 void carve(Ctx &c, void *ws) {
     c.ws = static_cast<char *>(ws);
     c.ctrl = reinterpret_cast<Control *>(c.ws + c.L.off_ctrl);
-    c.pref = reinterpret_cast<int64_t *>(c.ws + c.L.off_pref);
+    c.loc = reinterpret_cast<int64_t *>(c.ws + c.L.off_pref);
     c.row_nnz = reinterpret_cast<int32_t *>(c.ws + c.L.off_row_nnz);
     c.perm = reinterpret_cast<int32_t *>(c.ws + c.L.off_perm);
     c.rrows = reinterpret_cast<RankRow *>(c.ws + c.L.off_rrows);
+    c.row_prod = reinterpret_cast<int64_t *>(c.ws + c.L.off_rrows);
+    c.bin = reinterpret_cast<uint8_t *>(c.row_prod + c.nrows_a);
+    c.hist = reinterpret_cast<int32_t *>(c.ws + c.L.off_pool);
     c.partials = reinterpret_cast<int64_t *>(c.ws + c.L.off_partials);
     c.wtab = reinterpret_cast<int32_t *>(c.ws + c.L.off_wtab);
     c.pool = c.ws + c.L.off_pool;
@@ -485,12 +492,25 @@ wingspan_status side_stream(SideStream **out) {
     return WINGSPAN_OK;
 }
 
+// Exclusive scan of in(0 .. n - 1) into out[0 .. n]; csum (or null) receives the
+// output's checksum. One workgroup for short sequences (where `in` is cheap:
+// one_block), else two launches, three where the tiles number too many for each
+// to add up those before it.
+constexpr int64_t kScanOneBlock = 4096;
 template <typename In>
-wingspan_status run_scan(Ctx &c, In in, int64_t n, int64_t *out) {
+wingspan_status run_scan(Ctx &c, In in, int64_t n, int64_t *out, bool one_block = false, uint64_t *csum = nullptr) {
     const int64_t nb = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
-    scan_tile_sums<In><<<dim3(static_cast<unsigned>(nb)), kScanBlock, 0, c.st>>>(in, n, c.partials);
-    scan_partials<<<1, 1024, 0, c.st>>>(c.partials, nb);
-    scan_tiles<In><<<dim3(static_cast<unsigned>(nb)), kScanBlock, 0, c.st>>>(in, n, c.partials, nb, out);
+    const dim3 grid(static_cast<unsigned>(nb));
+    if (one_block && n <= kScanOneBlock) {
+        scan_one_block<In><<<1, 1024, 0, c.st>>>(in, n, out, csum);
+    } else if (nb <= kScanOwnTiles) {
+        if (nb > 1) scan_tile_sums<In><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials);
+        scan_tiles<In, true><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials, nb, out, csum);
+    } else {
+        scan_tile_sums<In><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials);
+        scan_partials<<<1, 1024, 0, c.st>>>(c.partials, nb);
+        scan_tiles<In, false><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials, nb, out, csum);
+    }
     LAUNCH_CHECK("scan");
     return WINGSPAN_OK;
 }
@@ -508,6 +528,19 @@ wingspan_status launch_window_table(Ctx &c, const wingspan_csr *B, hipStream_t s
 
 // Product counts, optional validation, and binning. Ends with the control
 // block on the host.
+// The rows into bins: counts, offsets (ctrl, cleared before) and perm. m > 0.
+wingspan_status launch_bins(Ctx &c, const int32_t *a_rp, const RowProducts &rp, const int64_t *c_rp, int64_t m,
+                            const BinCfg &cfg, Control *ctrl, int32_t *perm, int32_t *row_nnz, int32_t *slot_of_row,
+                            Stamp *stamp = nullptr, const Stamp &value = Stamp{}) {
+    int64_t nb = std::min<int64_t>((m + kBinBlock - 1) / kBinBlock, kBinBlocks);
+    nb = std::max<int64_t>(1, std::min<int64_t>(nb, c.L.pool_bytes / int64_t(sizeof(int32_t) * kNumBins)));
+    const unsigned grid = static_cast<unsigned>(nb);
+    bin_count<<<grid, kBinBlock, 0, c.st>>>(a_rp, rp, c_rp, m, cfg, ctrl, row_nnz, slot_of_row, c.bin, c.hist);
+    bin_scatter<<<grid, kBinBlock, 0, c.st>>>(c.bin, m, c.hist, ctrl, perm, stamp, value, c.ctrl);
+    LAUNCH_CHECK("binning");
+    return WINGSPAN_OK;
+}
+
 // What the analysis prepares: the symbolic phase (bins by products, LDS
 // tables of keys), the numeric phase (bins by C's exact row counts), or the
 // single pass with sharded output (bins by products, LDS tables of keys and
@@ -520,16 +553,18 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
     const bool numeric = mode == kModeNumeric;
     if ((s = timer_start(c, kSlotAnalysis)) != WINGSPAN_OK) return s;
     const int64_t m = A->nrows;
-    const int64_t words = sizeof(Control) / sizeof(int32_t);
-    zero_words<<<blocks_for(words, 256), 256, 0, c.st>>>(reinterpret_cast<int32_t *>(c.ctrl), words);
-    LAUNCH_CHECK("zero_words");
+    const int words = sizeof(Control) / sizeof(int32_t);
     c.bins = c.perm;
     c.wtab_ready = false;
     c.rrows_ready = false;
-    if (numeric && c.L.cache_rows > 0 && !c.o.validate) {
+    // after a symbolic phase in the same call row_prod holds the counts, unless the dense rows' descriptions of the
+    // kept binning took its place
+    if (c.L.cache_rows > 0) have_pref = false;
+    uint64_t rp_sum = 0;
+    if (numeric && c.L.cache_rows > 0) {
         // The symbolic phase on the same workspace may have binned the rows by this C.row_ptr already: check
         // its stamp (with C.row_ptr's checksum) and take its bins if they were made with these settings
-        rowptr_checksum<<<64, 256, 0, c.st>>>(c_rp, m, &c.ctrl->rp_sum);
+        rowptr_checksum<<<kRpParts, 1024, 0, c.st>>>(c_rp, m, c.ctrl);
         LAUNCH_CHECK("stamp");
         // the stamp, the control block and the kept binning, adjacent in the workspace, in one copy
         static_assert(sizeof(Stamp) <= kAlign * 2, "stamp region");
@@ -542,14 +577,16 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
         std::memcpy(&c.host_stamp, back.data(), sizeof(Stamp));
         std::memcpy(&c.host, back.data() + (c.L.off_ctrl - c.L.off_stamp), sizeof(Control));
         std::memcpy(&kept, back.data() + (c.L.off_ctrl_num - c.L.off_stamp), sizeof(Control));
+        for (uint64_t part : c.host.rp_part) rp_sum += part;
+        c.host.rp_sum = rp_sum;
         const BinCfg cfg = numeric_bin_cfg(c, B);
         const Stamp &h = c.host_stamp;
-        if (stamp_matches(c, A, B) && h.num_bins == 1 && h.nb_dense_min_nnz == cfg.dense_min_nnz &&
-            h.nb_tiny_max == cfg.tiny_max && h.nb_hash_log2_max == cfg.hash_log2_max &&
-            h.nb_force_spill == cfg.force_spill && h.nb_dense_ok == cfg.dense_ok &&
-            h.nb_merge_runs == cfg.merge_runs && h.nb_merge_places == cfg.merge_places &&
-            h.nb_merge_over_dense == cfg.merge_over_dense && h.nb_merge_long == cfg.merge_long) {
-            const uint64_t rp_sum = c.host.rp_sum;
+        const bool match = stamp_matches(c, A, B) && h.num_bins == 1;
+        if (match && !c.o.validate && h.nb_dense_min_nnz == cfg.dense_min_nnz && h.nb_tiny_max == cfg.tiny_max &&
+            h.nb_hash_log2_max == cfg.hash_log2_max && h.nb_force_spill == cfg.force_spill &&
+            h.nb_dense_ok == cfg.dense_ok && h.nb_merge_runs == cfg.merge_runs &&
+            h.nb_merge_places == cfg.merge_places && h.nb_merge_over_dense == cfg.merge_over_dense &&
+            h.nb_merge_long == cfg.merge_long) {
             c.host = kept;
             c.host.rp_sum = rp_sum;
             c.bins = c.perm_num;
@@ -563,18 +600,16 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
                             (long long)c.host.spill_max_bound, (long long)slab_limit);
             return WINGSPAN_OK;
         }
-        // not kept for this call: bin here (the checksum is added again below)
+        // not kept for this call: bin here, over the kept descriptions of the dense rows
+        if (h.num_bins == 1) {
+            drop_kept_bins<<<1, 1, 0, c.st>>>(c.stamp);
+            LAUNCH_CHECK("stamp");
+        }
+    } else if (c.o.validate || have_pref) {
+        // (otherwise brow_tile_prefix clears it)
         zero_words<<<blocks_for(words, 256), 256, 0, c.st>>>(reinterpret_cast<int32_t *>(c.ctrl), words);
         LAUNCH_CHECK("zero_words");
     }
-    if (mode == kModeSymbolic || mode == kModeSharded) {
-        // the structure cache (and what the symbolic phase keeps for the numeric one) is being rewritten:
-        // invalid until a symbolic phase completes
-        write_stamp<<<1, 1, 0, c.st>>>(c.stamp, Stamp{});
-    } else if (numeric && c.L.cache_rows > 0) {
-        rowptr_checksum<<<64, 256, 0, c.st>>>(c_rp, m, &c.ctrl->rp_sum);
-    }
-    LAUNCH_CHECK("stamp");
     if (c.o.validate) {
         if (A->nrows > 0)
             validate_csr<<<blocks_for(A->nrows * kWave, 256), 256, 0, c.st>>>(A->row_ptr, A->col_idx, A->nrows,
@@ -591,8 +626,12 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
             return fail(WINGSPAN_ERR_INVALID_MATRIX, "A or B is not canonical CSR");
     }
     if (!have_pref) {
-        s = run_scan(c, BRowLenIn{A->col_idx, B->row_ptr}, A->nnz, c.pref);
-        if (s != WINGSPAN_OK) return s;
+        // the lengths' prefixes; in the symbolic phase and the single pass the structure cache (and what the
+        // symbolic phase keeps for the numeric one) is being rewritten: invalid until a symbolic phase completes
+        brow_tile_prefix<<<blocks_for(std::max<int64_t>(A->nnz, 1), kScanTile), kScanBlock, 0, c.st>>>(
+            A->col_idx, B->row_ptr, A->nnz, c.loc, c.partials, reinterpret_cast<int32_t *>(c.ctrl),
+            numeric ? nullptr : reinterpret_cast<int32_t *>(c.ctrl_num), words, numeric ? nullptr : c.stamp);
+        LAUNCH_CHECK("row products");
     }
     if (numeric && c.dtype_f64 >= 0 && !c.L.rank_mode) {
         // only the column-window dense kernel's sentinel slots depend on it
@@ -631,19 +670,15 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
                                 : (B->ncols <= kRankRegionCols ? kShardedDenseMin : INT64_MAX);
     }
     if (m > 0) {
-        bin_count<<<blocks_for(m, 256), 256, 0, c.st>>>(A->row_ptr, c.pref, c_rp, m, cfg, c.ctrl,
-                                                         row_nnz_out ? row_nnz_out : c.row_nnz);
-        bin_offsets<<<1, 1, 0, c.st>>>(c.ctrl, c.pref, A->nnz);
-        bin_scatter<<<blocks_for(m, 256), 256, 0, c.st>>>(A->row_ptr, c.pref, c_rp, m, cfg, c.ctrl, c.perm);
-    } else {
-        bin_offsets<<<1, 1, 0, c.st>>>(c.ctrl, c.pref, A->nnz);
+        const RowProducts rp{have_pref ? nullptr : c.loc, c.partials, A->nnz, c.row_prod};
+        s = launch_bins(c, A->row_ptr, rp, c_rp, m, cfg, c.ctrl, c.perm, row_nnz_out ? row_nnz_out : c.row_nnz,
+                        mode == kModeSymbolic && c.L.cache_rows > 0 ? c.slot_of_row : nullptr);
+        if (s != WINGSPAN_OK) return s;
     }
-    LAUNCH_CHECK("binning");
     if ((s = timer_stop(c, kSlotAnalysis)) != WINGSPAN_OK) return s;
     HIP_TRY(hipMemcpyAsync(&c.host, c.ctrl, sizeof(Control), hipMemcpyDeviceToHost, c.st));
-    if (numeric && c.L.cache_rows > 0)
-        HIP_TRY(hipMemcpyAsync(&c.host_stamp, c.stamp, sizeof(Stamp), hipMemcpyDeviceToHost, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));
+    c.host.rp_sum = rp_sum;
     const int64_t slab_limit = c.L.slab_cap / 2;
     if (c.host.spill_max_bound > slab_limit)
         return fail(WINGSPAN_ERR_UNSUPPORTED,
@@ -672,7 +707,7 @@ void fill_stats(const Ctx &c, int phase) {
         st.products[t] += c.host.stat_products[b];
         st.c_nnz[t] += c.host.stat_cnnz[b];
     }
-    st.total_products = c.host.total_products;
+    for (int b = 0; b < kNumBins; ++b) st.total_products += c.host.stat_products[b];
 }
 
 // Whether every byte offset of B's columns and values fits in 32 bits, so the
@@ -866,7 +901,7 @@ wingspan_status launch_spill(Ctx &c, const Mats<V> &M, const int32_t *perm, int6
         const int64_t fits = c.L.pool_bytes / (slab * 12);
         const unsigned grid = static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>({int64_t(cnt), fits,
                                                                                              kMaxSpillGrid})));
-        spill_kernel<V, NUM><<<grid, kSpillBlock, 0, c.st>>>(M, perm + c.host.bin_offset[b], cnt, c.pref, ncols,
+        spill_kernel<V, NUM><<<grid, kSpillBlock, 0, c.st>>>(M, perm + c.host.bin_offset[b], cnt, c.row_prod, ncols,
                                                              c.pool, slab, row_nnz, out, c_col, c_val, c.ctrl,
                                                              &c.ctrl->spill_next[k]);
         ++*launches;
@@ -942,10 +977,6 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
     if (!side && (s = light_tiers()) != WINGSPAN_OK) return s;
 
     if ((s = timer_start(c, WINGSPAN_TIER_DENSE)) != WINGSPAN_OK) return s;
-    if (caching) {
-        fill_i32<<<blocks_for(A->nrows, 256), 256, 0, c.st>>>(c.slot_of_row, A->nrows, -1);
-        LAUNCH_CHECK("fill slots");
-    }
     if (cnt) {
         launch_bitmap(B->ncols, static_cast<unsigned>(cnt), c.st, M, perm + start, c.row_nnz,
                       caching ? c.slot_of_row : nullptr, caching ? c.cache : nullptr, c.L.row_words,
@@ -965,36 +996,25 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
     if (s != WINGSPAN_OK) return s;
     if ((s = timer_stop(c, WINGSPAN_TIER_SPILL)) != WINGSPAN_OK) return s;
 
-    s = run_scan(c, CountIn{c.row_nnz}, A->nrows, c_rp);
+    s = run_scan(c, CountIn{c.row_nnz}, A->nrows, c_rp, true, caching ? &c.ctrl->rp_sum : nullptr);
     if (s != WINGSPAN_OK) return s;
     if (caching) {
-        // C.row_ptr is known: bin the rows as the numeric phase does, and build B's window table for the dense
-        // rows (the numeric phase's dense rows are symbolic dense rows too: a row's entries never exceed its
-        // products), so a numeric phase on this workspace starts from them
+        // C.row_ptr is known: bin the rows as the numeric phase does (the dense rows' window table was built beside
+        // the tiers; the numeric phase's dense rows are symbolic dense rows too: a row's entries never exceed its
+        // products), so a numeric phase on this workspace starts from them; and stamp the cache with the inputs,
+        // the layout, the bins' settings and C.row_ptr's checksum
         const BinCfg ncfg = numeric_bin_cfg(c, B);
-        const int64_t words = sizeof(Control) / sizeof(int32_t);
-        zero_words<<<blocks_for(words, 256), 256, 0, c.st>>>(reinterpret_cast<int32_t *>(c.ctrl_num), words);
-        bin_count<<<blocks_for(A->nrows, 256), 256, 0, c.st>>>(A->row_ptr, c.pref, c_rp, A->nrows, ncfg, c.ctrl_num,
-                                                                 c.row_nnz);
-        bin_offsets<<<1, 1, 0, c.st>>>(c.ctrl_num, c.pref, A->nnz);
-        bin_scatter<<<blocks_for(A->nrows, 256), 256, 0, c.st>>>(A->row_ptr, c.pref, c_rp, A->nrows, ncfg,
-                                                                   c.ctrl_num, c.perm_num);
-        LAUNCH_CHECK("numeric binning");
+        Stamp t = make_stamp(c, A, B, std::min<int64_t>(cnt_dense, c.L.cache_rows));
+        stamp_bins(t, ncfg, wtab);
+        s = launch_bins(c, A->row_ptr, RowProducts{nullptr, nullptr, A->nnz, c.row_prod}, c_rp, A->nrows, ncfg,
+                        c.ctrl_num, c.perm_num, c.row_nnz, nullptr, c.stamp, t);
+        if (s != WINGSPAN_OK) return s;
         if (wtab) {
-            // (the window table was built beside the tiers) and the descriptions of the numeric phase's dense
-            // rows (their cache slots are this phase's)
+            // the descriptions of the numeric phase's dense rows (their cache slots are this phase's)
             rank_rows_of_bins<<<blocks_for(A->nrows, 256), 256, 0, c.st>>>(c.perm_num, c.ctrl_num, A->row_ptr, c_rp,
                                                                            c.slot_of_row, c.rrows);
             LAUNCH_CHECK("rank rows of bins");
         }
-        // the cache is complete: stamp it with the inputs, the layout, the bins' settings and C.row_ptr's
-        // checksum
-        Stamp t = make_stamp(c, A, B, std::min<int64_t>(cnt_dense, c.L.cache_rows));
-        stamp_bins(t, ncfg, wtab);
-        write_stamp<<<1, 1, 0, c.st>>>(c.stamp, t);
-        rowptr_checksum<<<64, 256, 0, c.st>>>(c_rp, A->nrows, &c.stamp->rp_sum);
-        seal_stamp<<<1, 1, 0, c.st>>>(c.stamp);
-        LAUNCH_CHECK("stamp");
     }
     int64_t total = 0;
     HIP_TRY(hipMemcpyAsync(&total, c_rp + A->nrows, sizeof(int64_t), hipMemcpyDeviceToHost, c.st));
@@ -1223,6 +1243,7 @@ wingspan_status setup(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, cons
     if (reinterpret_cast<uintptr_t>(ws) % kAlign != 0)
         return fail(WINGSPAN_ERR_INVALID_ARGUMENT, "workspace must be %zu-byte aligned", kAlign);
     c.st = static_cast<hipStream_t>(stream);
+    c.nrows_a = A->nrows;
     carve(c, ws);
     if (!c.o.dense_min_explicit && c.L.cache_rows > 0) c.o.dense_min_nnz = kCachedDenseMin;
     return WINGSPAN_OK;
@@ -1377,7 +1398,7 @@ wingspan_status ew_scan_tiles(Ctx &c, const EwLayout &L, const EwTiles &T) {
     // one workgroup scans a few thousand tile counts, the tiled scan more (measured: 25 us for 16 K counts in
     // one workgroup)
     if (L.ntiles <= 2048) {
-        scan_one_block<EwTileIn><<<1, 1024, 0, c.st>>>(EwTileIn{T.tile_cnt}, L.ntiles, T.tile_off);
+        scan_one_block<EwTileIn><<<1, 1024, 0, c.st>>>(EwTileIn{T.tile_cnt}, L.ntiles, T.tile_off, nullptr);
         LAUNCH_CHECK("elementwise tile scan");
         return WINGSPAN_OK;
     }
@@ -1527,7 +1548,7 @@ wingspan_status sv_impl(Ctx &c, const wingspan_csr *At, const SvLayout &L, const
             sv_place<<<grid, kSvBinBlock, 0, c.st>>>(tmp_row, tmp_val, pref, static_cast<int>(nnz_x), err, nr, nc,
                                                      tab, gpos, srt_row, srt_val);
             int64_t *piece_pre = reinterpret_cast<int64_t *>(c.ws + L.off_piece_pre);
-            scan_one_block<SvPiecesIn><<<1, 1024, 0, c.st>>>(SvPiecesIn{gpos, nc}, nr, piece_pre);
+            scan_one_block<SvPiecesIn><<<1, 1024, 0, c.st>>>(SvPiecesIn{gpos, nc}, nr, piece_pre, nullptr);
             const int64_t pieces = nr + (At->nnz + kSvPieceMax - 1) / kSvPieceMax;   // at most
             sv_accumulate<<<static_cast<unsigned>(std::min<int64_t>(pieces, kSvBucketGrid)), kSvAccBlock, 0, c.st>>>(
                 srt_row, srt_val, err, nr, nc, gpos, piece_pre, flag, yval);
@@ -1543,7 +1564,7 @@ wingspan_status sv_impl(Ctx &c, const wingspan_csr *At, const SvLayout &L, const
     // coalesce the map tile by tile: counts, their scan (the total lands next to the error word), then y
     const unsigned nt = static_cast<unsigned>(L.ntiles);
     sv_tile_count<<<nt, kSvTileBlock, 0, c.st>>>(reinterpret_cast<const uint32_t *>(flag), m, tiles);
-    scan_one_block<SvTileIn><<<1, 1024, 0, c.st>>>(SvTileIn{tiles}, L.ntiles, tile_pre);
+    scan_one_block<SvTileIn><<<1, 1024, 0, c.st>>>(SvTileIn{tiles}, L.ntiles, tile_pre, nullptr);
     sv_emit_tiles<V><<<nt, kSvTileBlock, 0, c.st>>>(flag, yval, tile_pre, m, y_cap, y_idx, y_val);
     LAUNCH_CHECK("spmspv emit");
     struct {
@@ -1912,8 +1933,10 @@ wingspan_status wingspan_spgemm_row_products(const wingspan_csr *A, const wingsp
     if ((s = setup(c, A, B, nullptr, workspace_dev, workspace_bytes, stream)) != WINGSPAN_OK) return s;
     if (A->nrows == 0) return WINGSPAN_OK;
     // the analysis pass of both phases: B-row lengths scanned over A's entries, then per-row differences
-    if ((s = run_scan(c, BRowLenIn{A->col_idx, B->row_ptr}, A->nnz, c.pref)) != WINGSPAN_OK) return s;
-    row_products_kernel<<<blocks_for(A->nrows, 256), 256, 0, c.st>>>(A->row_ptr, c.pref, A->nrows, row_products_dev);
+    brow_tile_prefix<<<blocks_for(std::max<int64_t>(A->nnz, 1), kScanTile), kScanBlock, 0, c.st>>>(
+        A->col_idx, B->row_ptr, A->nnz, c.loc, c.partials, nullptr, nullptr, 0, nullptr);
+    row_products_kernel<<<blocks_for(A->nrows, 256), 256, 0, c.st>>>(A->row_ptr, A->nnz, c.loc, c.partials, A->nrows,
+                                                                     row_products_dev);
     LAUNCH_CHECK("row products");
     return WINGSPAN_OK;
 }

@@ -1,0 +1,60 @@
+"""GPU tests of the row analysis: product counts around the tiles of A's entries
+(rows that end on, start on and span them), row counts around the binning's
+workgroups and the scan's forms, against numpy."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import matgen
+from gpu_util import gpu_row_products, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _a(lens, k, seed):
+    """Rows of the given lengths (columns distinct and sorted within a row)."""
+    rng = np.random.default_rng(seed)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.empty(rp[-1], np.int32)
+    for i in np.nonzero(lens)[0]:
+        n = int(lens[i])
+        ci[rp[i]:rp[i + 1]] = np.sort(rng.choice(k, size=n, replace=False)) if n > 1 else rng.integers(0, k)
+    return matgen.CSR(len(lens), k, rp, ci, np.ones(rp[-1]))
+
+
+@pytest.mark.parametrize("lens", [
+    [2048], [2048, 2048], [0, 2047, 1, 0, 2048, 0], [2049], [1, 2047, 2048, 0], [5000, 0, 1192], [100, 9000, 0, 3],
+    [0, 0, 0], [1], [4096, 4096, 1]], ids=str)
+def test_row_products_around_tiles(lens):
+    B = matgen.er(10_000, 50, 1, seed=2)
+    keep = np.random.default_rng(3).random(B.nrows) < 0.5   # half of B's rows are empty
+    bp = np.concatenate([[0], np.cumsum(keep)]).astype(np.int32)
+    B = matgen.CSR(B.nrows, 50, bp, B.col_idx[keep], B.val[keep])
+    A = _a(np.array(lens), B.nrows, 4)
+    want = np.add.reduceat(np.append(keep[A.col_idx].astype(np.int64), 0), A.row_ptr[:-1]) * (np.diff(A.row_ptr) > 0)
+    assert np.array_equal(gpu_row_products(A, B), want)
+    got, sym, _ = run_gpu(A, B)
+    assert sym["total_products"] == want.sum()
+    for i in range(A.nrows):
+        cols = np.unique(B.col_idx[bp[A.row(i)[0]][keep[A.row(i)[0]]]])
+        assert np.array_equal(got.col_idx[got.row_ptr[i]:got.row_ptr[i + 1]], cols)
+
+
+@pytest.mark.parametrize("m", [1, 1023, 1024, 1025, 4095, 4096, 4097, 262_143, 262_145, 2_097_152, 2_097_153])
+@pytest.mark.parametrize("opts", [None, dict(cache_mib=-1)], ids=["cache", "no cache"])
+def test_row_counts(m, opts):
+    # rows of 0 to 3 A entries, each selecting one entry of B: C is A with its columns renamed
+    rng = np.random.default_rng(m)
+    lens = rng.integers(0, 4, m)
+    lens[-1] = 2
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    off = np.arange(rp[-1]) - np.repeat(rp[:-1], lens)
+    ci = (rng.integers(0, 100, m).repeat(lens) + 100 * off).astype(np.int32)
+    A = matgen.CSR(m, 300, rp, ci, np.ones(rp[-1], np.float32))
+    B = matgen.CSR(300, 1000, np.arange(301, dtype=np.int32), (3 * np.arange(300)).astype(np.int32),
+                   np.full(300, 0.5, np.float32))
+    got, sym, num = run_gpu(A, B, opts)
+    assert np.array_equal(got.row_ptr, rp) and np.array_equal(got.col_idx, 3 * ci)
+    assert np.all(got.val == 0.5)
+    assert num["rows"]["tiny"] == int(np.sum(lens > 0)) and num["c_nnz_total"] == rp[-1]
