@@ -92,7 +92,8 @@ __device__ __forceinline__ void add_checksum(uint64_t acc, uint64_t *sum, int64_
 constexpr int64_t kScanOwnTiles = 1024;   // tiles a workgroup adds up by itself at most
 template <typename In, bool OWN>
 __global__ void __launch_bounds__(kScanBlock) scan_tiles(In in, int64_t n, const int64_t *partials,
-                                                         int64_t nb, int64_t *out, uint64_t *csum) {
+                                                         int64_t nb, int64_t *out, uint64_t *csum,
+                                                         int64_t *host_total) {
     __shared__ int64_t wsum[kScanBlock / kWave];
     int64_t first = 0;
     if constexpr (OWN) {
@@ -136,6 +137,7 @@ __global__ void __launch_bounds__(kScanBlock) scan_tiles(In in, int64_t n, const
     // the last item of the last tile: run is the total
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanBlock - 1) {
         out[n] = run;
+        if (host_total != nullptr) *host_total = run;
         acc += static_cast<uint64_t>(run) * static_cast<uint64_t>(2 * n + 1);
     }
     if (csum != nullptr) {
@@ -242,7 +244,8 @@ __global__ void __launch_bounds__(256) row_products_kernel(const int32_t *__rest
 // share's prefixes. out[n] = total.
 
 template <typename In>
-__global__ void __launch_bounds__(1024) scan_one_block(In in, int64_t n, int64_t *out, uint64_t *csum) {
+__global__ void __launch_bounds__(1024) scan_one_block(In in, int64_t n, int64_t *out, uint64_t *csum,
+                                                       int64_t *host_total) {
     __shared__ int64_t wsum[16];
     const int64_t per = (n + 1023) / 1024;
     const int64_t b = static_cast<int64_t>(threadIdx.x) * per;
@@ -287,6 +290,7 @@ __global__ void __launch_bounds__(1024) scan_one_block(In in, int64_t n, int64_t
     }
     if (threadIdx.x == 0) {
         out[n] = tot;
+        if (host_total != nullptr) *host_total = tot;
         acc += static_cast<uint64_t>(tot) * static_cast<uint64_t>(2 * n + 1);
     }
     if (csum != nullptr) {
@@ -440,11 +444,12 @@ __global__ void __launch_bounds__(kBinBlock) bin_count(const int32_t *__restrict
 
 // Writes each non-empty row's id into its bin's range of perm (the grid of
 // bin_count); the first workgroup records the bins' offsets, and the stamp when
-// it is given one (stamp->rp_sum from the scan that wrote C.row_ptr).
+// it is given one (stamp->rp_sum from the scan that wrote C.row_ptr), and copies
+// the control block to host_ctrl (host memory the device can write) when given.
 __global__ void __launch_bounds__(kBinBlock) bin_scatter(const uint8_t *__restrict__ bin, int64_t m,
                                                          const int32_t *__restrict__ hist, Control *ctrl,
                                                          int32_t *__restrict__ perm, Stamp *stamp, const Stamp value,
-                                                         const Control *sums) {
+                                                         const Control *sums, int32_t *host_ctrl) {
     __shared__ int32_t s_tot[kMaxBins], s_next[kMaxBins];
     const int wv = threadIdx.x / kWave, ln = lane_id();
     const int nblk = static_cast<int>(gridDim.x), blk = static_cast<int>(blockIdx.x);
@@ -490,6 +495,10 @@ __global__ void __launch_bounds__(kBinBlock) bin_scatter(const uint8_t *__restri
         }
     }
     __syncthreads();
+    if (blockIdx.x == 0 && host_ctrl != nullptr) {
+        const int32_t *p = reinterpret_cast<const int32_t *>(ctrl);
+        for (int i = threadIdx.x; i < static_cast<int>(sizeof(Control) / 4); i += kBinBlock) host_ctrl[i] = p[i];
+    }
     const int64_t share = (m + gridDim.x - 1) / gridDim.x;
     const int64_t i0 = share * blockIdx.x, i1 = i0 + share < m ? i0 + share : m;
     for (int64_t i = i0 + threadIdx.x; i < i1; i += kBinBlock) {
@@ -507,6 +516,11 @@ __global__ void __launch_bounds__(kBinBlock) bin_scatter(const uint8_t *__restri
             left &= ~same;
         }
     }
+}
+
+// Words from device memory to host memory the device can write.
+__global__ void copy_words(const int32_t *__restrict__ p, int32_t *__restrict__ host, int n) {
+    for (int i = threadIdx.x; i < n; i += blockDim.x) host[i] = p[i];
 }
 
 // Zero-fill of the control block (a kernel, not a memset, so the sequence can
@@ -609,15 +623,28 @@ __global__ void __launch_bounds__(256) gather_rows(int64_t nrows, const int64_t 
 
 // Checksum of C.row_ptr[0..m] (the sum of rp[i] * (2i + 1) modulo 2^64) in
 // kRpParts parts, one per workgroup, into ctrl->rp_part; the first workgroup
-// clears the rest of the control block.
-__global__ void __launch_bounds__(1024) rowptr_checksum(const int64_t *__restrict__ rp, int64_t m, Control *ctrl) {
+// clears the rest of the control block. With host (host memory the device can
+// write), the parts go to the control block's copy there instead, between the
+// copies of the stamp and of the kept binning's control block (from ctrl_num),
+// laid out as in the workspace from the stamp on.
+__global__ void __launch_bounds__(1024) rowptr_checksum(const int64_t *__restrict__ rp, int64_t m, Control *ctrl,
+                                                        const Stamp *stamp, const Control *ctrl_num, char *host,
+                                                        int64_t host_ctrl, int64_t host_ctrl_num) {
     __shared__ int64_t scratch[1024 / kWave];
     uint64_t acc = 0;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i <= m;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x)
         acc += static_cast<uint64_t>(rp[i]) * static_cast<uint64_t>(2 * i + 1);
     acc = static_cast<uint64_t>(block_sum<1024>(static_cast<int64_t>(acc), scratch));
-    if (threadIdx.x == 0) ctrl->rp_part[blockIdx.x] = acc;
+    if (threadIdx.x == 0)
+        (host != nullptr ? reinterpret_cast<Control *>(host + host_ctrl) : ctrl)->rp_part[blockIdx.x] = acc;
+    if (host != nullptr && blockIdx.x == 1) {
+        const int32_t *p = reinterpret_cast<const int32_t *>(stamp), *q = reinterpret_cast<const int32_t *>(ctrl_num);
+        for (int i = threadIdx.x; i < static_cast<int>(sizeof(Stamp) / 4); i += blockDim.x)
+            reinterpret_cast<int32_t *>(host)[i] = p[i];
+        for (int i = threadIdx.x; i < static_cast<int>(sizeof(Control) / 4); i += blockDim.x)
+            reinterpret_cast<int32_t *>(host + host_ctrl_num)[i] = q[i];
+    }
     if (blockIdx.x == 0) {
         int32_t *p = reinterpret_cast<int32_t *>(ctrl);
         constexpr int lo = offsetof(Control, rp_part) / 4, hi = lo + kRpParts * 2;

@@ -547,9 +547,12 @@ __global__ void __launch_bounds__(kSvTileBlock) sv_emit_tiles(const uint8_t *__r
                                                              const double *__restrict__ yval,
                                                              const int64_t *__restrict__ tile_pre, int64_t m,
                                                              int64_t cap, int32_t *__restrict__ y_idx,
-                                                             V *__restrict__ y_val) {
+                                                             V *__restrict__ y_val, int64_t ntiles,
+                                                             int64_t *host_back) {
     __shared__ int32_t scratch[kSvTileBlock / kWave];
     constexpr int PER = kSvTile / kSvTileBlock;   // consecutive positions per thread
+    // the total and the error word behind it, to the host
+    if (host_back != nullptr && blockIdx.x == 0 && threadIdx.x < 2) host_back[threadIdx.x] = tile_pre[ntiles + threadIdx.x];
     const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kSvTile + static_cast<int64_t>(threadIdx.x) * PER;
     bool f[PER];
     int c = 0;

@@ -282,9 +282,63 @@ Layout plan(const wingspan_csr *A, const wingspan_csr *B, const Opts &o, size_t 
 }
 
 // ---------------------------------------------------------------------------
+// Read-backs. The kernels write what the host waits for (bins, totals) straight
+// into pinned host memory, so a read-back costs a stream synchronization and no
+// copy (a copy to pageable memory adds about 15 us, in calls that take 100).
+// Calls take a buffer from a pool for their duration and give it back: as many
+// exist as calls have ever run at once. A call that ends before it has waited
+// for its kernels (an error) waits for them before it gives the buffer back.
+// ---------------------------------------------------------------------------
+constexpr size_t kHostBackBytes = 16384;
+std::mutex g_back_mu;
+std::vector<char *> g_back_free;
+
+struct HostBack {
+    char *p = nullptr;
+    hipStream_t st = nullptr;
+    bool pending = false;
+    HostBack() = default;
+    HostBack(const HostBack &) = delete;
+    HostBack &operator=(const HostBack &) = delete;
+    ~HostBack() {
+        if (p == nullptr) return;
+        if (pending) (void)hipStreamSynchronize(st);
+        std::lock_guard<std::mutex> lk(g_back_mu);
+        g_back_free.push_back(p);
+    }
+    // false: none to be had (the caller copies instead)
+    bool take(hipStream_t stream) {
+        st = stream;
+        {
+            std::lock_guard<std::mutex> lk(g_back_mu);
+            if (!g_back_free.empty()) {
+                p = g_back_free.back();
+                g_back_free.pop_back();
+                return true;
+            }
+        }
+        void *q = nullptr;
+        if (hipHostMalloc(&q, kHostBackBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        p = static_cast<char *>(q);
+        return true;
+    }
+    // the buffer as kernels write it (null without one), from now on awaited
+    template <typename T>
+    T *to(size_t off = 0) {
+        if (p == nullptr) return nullptr;
+        pending = true;
+        return reinterpret_cast<T *>(p + off);
+    }
+};
+
+// ---------------------------------------------------------------------------
 // Per-call context.
 // ---------------------------------------------------------------------------
 struct Ctx {
+    HostBack back;
     hipStream_t st;
     int64_t nrows_a = 0;
     int dtype_f64 = -1;   // numeric value type: 1 double, 0 float, -1 unknown (symbolic)
@@ -393,6 +447,20 @@ void set_merge(const Ctx &c, const wingspan_csr *B, BinCfg *cfg) {
     if (cfg->numeric && limit > most && c.L.rank_mode && c.L.nwin > 0) cfg->merge_long = static_cast<int32_t>(limit);
 }
 
+// Waits for the stream and gives `bytes` at device address `dev`, which kernels
+// have written to the read-back buffer at `off` too where there is one.
+wingspan_status read_back(Ctx &c, void *dst, const void *dev, size_t bytes, size_t off = 0) {
+    if (c.back.p != nullptr) {
+        HIP_TRY(hipStreamSynchronize(c.st));
+        c.back.pending = false;
+        std::memcpy(dst, c.back.p + off, bytes);
+        return WINGSPAN_OK;
+    }
+    HIP_TRY(hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, c.st));
+    HIP_TRY(hipStreamSynchronize(c.st));
+    return WINGSPAN_OK;
+}
+
 // How the numeric phase bins rows (by C's exact row counts).
 BinCfg numeric_bin_cfg(const Ctx &c, const wingspan_csr *B) {
     BinCfg cfg{};
@@ -498,18 +566,19 @@ wingspan_status side_stream(SideStream **out) {
 // to add up those before it.
 constexpr int64_t kScanOneBlock = 4096;
 template <typename In>
-wingspan_status run_scan(Ctx &c, In in, int64_t n, int64_t *out, bool one_block = false, uint64_t *csum = nullptr) {
+wingspan_status run_scan(Ctx &c, In in, int64_t n, int64_t *out, bool one_block = false, uint64_t *csum = nullptr,
+                         int64_t *host_total = nullptr) {
     const int64_t nb = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
     const dim3 grid(static_cast<unsigned>(nb));
     if (one_block && n <= kScanOneBlock) {
-        scan_one_block<In><<<1, 1024, 0, c.st>>>(in, n, out, csum);
+        scan_one_block<In><<<1, 1024, 0, c.st>>>(in, n, out, csum, host_total);
     } else if (nb <= kScanOwnTiles) {
         if (nb > 1) scan_tile_sums<In><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials);
-        scan_tiles<In, true><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials, nb, out, csum);
+        scan_tiles<In, true><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials, nb, out, csum, host_total);
     } else {
         scan_tile_sums<In><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials);
         scan_partials<<<1, 1024, 0, c.st>>>(c.partials, nb);
-        scan_tiles<In, false><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials, nb, out, csum);
+        scan_tiles<In, false><<<grid, kScanBlock, 0, c.st>>>(in, n, c.partials, nb, out, csum, host_total);
     }
     LAUNCH_CHECK("scan");
     return WINGSPAN_OK;
@@ -531,12 +600,12 @@ wingspan_status launch_window_table(Ctx &c, const wingspan_csr *B, hipStream_t s
 // The rows into bins: counts, offsets (ctrl, cleared before) and perm. m > 0.
 wingspan_status launch_bins(Ctx &c, const int32_t *a_rp, const RowProducts &rp, const int64_t *c_rp, int64_t m,
                             const BinCfg &cfg, Control *ctrl, int32_t *perm, int32_t *row_nnz, int32_t *slot_of_row,
-                            Stamp *stamp = nullptr, const Stamp &value = Stamp{}) {
+                            int32_t *host_ctrl = nullptr, Stamp *stamp = nullptr, const Stamp &value = Stamp{}) {
     int64_t nb = std::min<int64_t>((m + kBinBlock - 1) / kBinBlock, kBinBlocks);
     nb = std::max<int64_t>(1, std::min<int64_t>(nb, c.L.pool_bytes / int64_t(sizeof(int32_t) * kNumBins)));
     const unsigned grid = static_cast<unsigned>(nb);
     bin_count<<<grid, kBinBlock, 0, c.st>>>(a_rp, rp, c_rp, m, cfg, ctrl, row_nnz, slot_of_row, c.bin, c.hist);
-    bin_scatter<<<grid, kBinBlock, 0, c.st>>>(c.bin, m, c.hist, ctrl, perm, stamp, value, c.ctrl);
+    bin_scatter<<<grid, kBinBlock, 0, c.st>>>(c.bin, m, c.hist, ctrl, perm, stamp, value, c.ctrl, host_ctrl);
     LAUNCH_CHECK("binning");
     return WINGSPAN_OK;
 }
@@ -564,19 +633,22 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
     if (numeric && c.L.cache_rows > 0) {
         // The symbolic phase on the same workspace may have binned the rows by this C.row_ptr already: check
         // its stamp (with C.row_ptr's checksum) and take its bins if they were made with these settings
-        rowptr_checksum<<<kRpParts, 1024, 0, c.st>>>(c_rp, m, c.ctrl);
+        const size_t host_ctrl = c.L.off_ctrl - c.L.off_stamp, host_ctrl_num = c.L.off_ctrl_num - c.L.off_stamp;
+        rowptr_checksum<<<kRpParts, 1024, 0, c.st>>>(c_rp, m, c.ctrl, c.stamp, c.ctrl_num, c.back.to<char>(),
+                                                     static_cast<int64_t>(host_ctrl),
+                                                     static_cast<int64_t>(host_ctrl_num));
         LAUNCH_CHECK("stamp");
-        // the stamp, the control block and the kept binning, adjacent in the workspace, in one copy
+        // the stamp, the control block and the kept binning, adjacent in the workspace, in one read-back
         static_assert(sizeof(Stamp) <= kAlign * 2, "stamp region");
-        const size_t span = c.L.off_ctrl_num + sizeof(Control) - c.L.off_stamp;
+        static_assert(kAlign * 2 + 2 * (sizeof(Control) + kAlign) <= kHostBackBytes, "read-back buffer");
+        const size_t span = host_ctrl_num + sizeof(Control);
         thread_local std::vector<char> back;
         back.resize(span);
-        HIP_TRY(hipMemcpyAsync(back.data(), c.ws + c.L.off_stamp, span, hipMemcpyDeviceToHost, c.st));
-        HIP_TRY(hipStreamSynchronize(c.st));
+        if ((s = read_back(c, back.data(), c.ws + c.L.off_stamp, span)) != WINGSPAN_OK) return s;
         Control kept;
         std::memcpy(&c.host_stamp, back.data(), sizeof(Stamp));
-        std::memcpy(&c.host, back.data() + (c.L.off_ctrl - c.L.off_stamp), sizeof(Control));
-        std::memcpy(&kept, back.data() + (c.L.off_ctrl_num - c.L.off_stamp), sizeof(Control));
+        std::memcpy(&c.host, back.data() + host_ctrl, sizeof(Control));
+        std::memcpy(&kept, back.data() + host_ctrl_num, sizeof(Control));
         for (uint64_t part : c.host.rp_part) rp_sum += part;
         c.host.rp_sum = rp_sum;
         const BinCfg cfg = numeric_bin_cfg(c, B);
@@ -672,12 +744,14 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
     if (m > 0) {
         const RowProducts rp{have_pref ? nullptr : c.loc, c.partials, A->nnz, c.row_prod};
         s = launch_bins(c, A->row_ptr, rp, c_rp, m, cfg, c.ctrl, c.perm, row_nnz_out ? row_nnz_out : c.row_nnz,
-                        mode == kModeSymbolic && c.L.cache_rows > 0 ? c.slot_of_row : nullptr);
+                        mode == kModeSymbolic && c.L.cache_rows > 0 ? c.slot_of_row : nullptr, c.back.to<int32_t>());
         if (s != WINGSPAN_OK) return s;
+    } else if (c.back.p != nullptr) {
+        copy_words<<<1, 256, 0, c.st>>>(reinterpret_cast<const int32_t *>(c.ctrl), c.back.to<int32_t>(), words);
+        LAUNCH_CHECK("read back");
     }
     if ((s = timer_stop(c, kSlotAnalysis)) != WINGSPAN_OK) return s;
-    HIP_TRY(hipMemcpyAsync(&c.host, c.ctrl, sizeof(Control), hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
+    if ((s = read_back(c, &c.host, c.ctrl, sizeof(Control))) != WINGSPAN_OK) return s;
     c.host.rp_sum = rp_sum;
     const int64_t slab_limit = c.L.slab_cap / 2;
     if (c.host.spill_max_bound > slab_limit)
@@ -996,7 +1070,8 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
     if (s != WINGSPAN_OK) return s;
     if ((s = timer_stop(c, WINGSPAN_TIER_SPILL)) != WINGSPAN_OK) return s;
 
-    s = run_scan(c, CountIn{c.row_nnz}, A->nrows, c_rp, true, caching ? &c.ctrl->rp_sum : nullptr);
+    s = run_scan(c, CountIn{c.row_nnz}, A->nrows, c_rp, true, caching ? &c.ctrl->rp_sum : nullptr,
+                 c.back.to<int64_t>());
     if (s != WINGSPAN_OK) return s;
     if (caching) {
         // C.row_ptr is known: bin the rows as the numeric phase does (the dense rows' window table was built beside
@@ -1007,7 +1082,7 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
         Stamp t = make_stamp(c, A, B, std::min<int64_t>(cnt_dense, c.L.cache_rows));
         stamp_bins(t, ncfg, wtab);
         s = launch_bins(c, A->row_ptr, RowProducts{nullptr, nullptr, A->nnz, c.row_prod}, c_rp, A->nrows, ncfg,
-                        c.ctrl_num, c.perm_num, c.row_nnz, nullptr, c.stamp, t);
+                        c.ctrl_num, c.perm_num, c.row_nnz, nullptr, nullptr, c.stamp, t);
         if (s != WINGSPAN_OK) return s;
         if (wtab) {
             // the descriptions of the numeric phase's dense rows (their cache slots are this phase's)
@@ -1017,8 +1092,7 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
         }
     }
     int64_t total = 0;
-    HIP_TRY(hipMemcpyAsync(&total, c_rp + A->nrows, sizeof(int64_t), hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
+    if ((s = read_back(c, &total, c_rp + A->nrows, sizeof(int64_t))) != WINGSPAN_OK) return s;
     *c_nnz = total;
     stats.c_nnz_total = total;
     return WINGSPAN_OK;
@@ -1207,8 +1281,12 @@ wingspan_status sharded_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
     if (s != WINGSPAN_OK) return s;
     if ((s = timer_stop(c, WINGSPAN_TIER_SPILL)) != WINGSPAN_OK) return s;
 
-    HIP_TRY(hipMemcpyAsync(&c.host, c.ctrl, sizeof(Control), hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
+    if (c.back.p != nullptr) {
+        copy_words<<<1, 256, 0, c.st>>>(reinterpret_cast<const int32_t *>(c.ctrl), c.back.to<int32_t>(),
+                                        static_cast<int>(sizeof(Control) / 4));
+        LAUNCH_CHECK("read back");
+    }
+    if ((s = read_back(c, &c.host, c.ctrl, sizeof(Control))) != WINGSPAN_OK) return s;
     if (c.host.error_flags & kErrProbeExhausted)
         return fail(WINGSPAN_ERR_INCONSISTENT, "a row's hash table filled up (flags %d)", c.host.error_flags);
     const int64_t total = static_cast<int64_t>(c.host.pool_claimed);
@@ -1245,6 +1323,7 @@ wingspan_status setup(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, cons
     c.st = static_cast<hipStream_t>(stream);
     c.nrows_a = A->nrows;
     carve(c, ws);
+    if (budget == 0) c.back.take(c.st);   // (not for the entry point that allocates nothing)
     if (!c.o.dense_min_explicit && c.L.cache_rows > 0) c.o.dense_min_nnz = kCachedDenseMin;
     return WINGSPAN_OK;
 }
@@ -1398,7 +1477,7 @@ wingspan_status ew_scan_tiles(Ctx &c, const EwLayout &L, const EwTiles &T) {
     // one workgroup scans a few thousand tile counts, the tiled scan more (measured: 25 us for 16 K counts in
     // one workgroup)
     if (L.ntiles <= 2048) {
-        scan_one_block<EwTileIn><<<1, 1024, 0, c.st>>>(EwTileIn{T.tile_cnt}, L.ntiles, T.tile_off, nullptr);
+        scan_one_block<EwTileIn><<<1, 1024, 0, c.st>>>(EwTileIn{T.tile_cnt}, L.ntiles, T.tile_off, nullptr, nullptr);
         LAUNCH_CHECK("elementwise tile scan");
         return WINGSPAN_OK;
     }
@@ -1548,7 +1627,7 @@ wingspan_status sv_impl(Ctx &c, const wingspan_csr *At, const SvLayout &L, const
             sv_place<<<grid, kSvBinBlock, 0, c.st>>>(tmp_row, tmp_val, pref, static_cast<int>(nnz_x), err, nr, nc,
                                                      tab, gpos, srt_row, srt_val);
             int64_t *piece_pre = reinterpret_cast<int64_t *>(c.ws + L.off_piece_pre);
-            scan_one_block<SvPiecesIn><<<1, 1024, 0, c.st>>>(SvPiecesIn{gpos, nc}, nr, piece_pre, nullptr);
+            scan_one_block<SvPiecesIn><<<1, 1024, 0, c.st>>>(SvPiecesIn{gpos, nc}, nr, piece_pre, nullptr, nullptr);
             const int64_t pieces = nr + (At->nnz + kSvPieceMax - 1) / kSvPieceMax;   // at most
             sv_accumulate<<<static_cast<unsigned>(std::min<int64_t>(pieces, kSvBucketGrid)), kSvAccBlock, 0, c.st>>>(
                 srt_row, srt_val, err, nr, nc, gpos, piece_pre, flag, yval);
@@ -1564,8 +1643,9 @@ wingspan_status sv_impl(Ctx &c, const wingspan_csr *At, const SvLayout &L, const
     // coalesce the map tile by tile: counts, their scan (the total lands next to the error word), then y
     const unsigned nt = static_cast<unsigned>(L.ntiles);
     sv_tile_count<<<nt, kSvTileBlock, 0, c.st>>>(reinterpret_cast<const uint32_t *>(flag), m, tiles);
-    scan_one_block<SvTileIn><<<1, 1024, 0, c.st>>>(SvTileIn{tiles}, L.ntiles, tile_pre, nullptr);
-    sv_emit_tiles<V><<<nt, kSvTileBlock, 0, c.st>>>(flag, yval, tile_pre, m, y_cap, y_idx, y_val);
+    scan_one_block<SvTileIn><<<1, 1024, 0, c.st>>>(SvTileIn{tiles}, L.ntiles, tile_pre, nullptr, nullptr);
+    sv_emit_tiles<V><<<nt, kSvTileBlock, 0, c.st>>>(flag, yval, tile_pre, m, y_cap, y_idx, y_val, L.ntiles,
+                                                    c.back.to<int64_t>());
     LAUNCH_CHECK("spmspv emit");
     struct {
         int64_t total;
@@ -1573,8 +1653,7 @@ wingspan_status sv_impl(Ctx &c, const wingspan_csr *At, const SvLayout &L, const
         int32_t pad;
     } back{};
     static_assert(sizeof(back) == 16, "total then error word");
-    HIP_TRY(hipMemcpyAsync(&back, tile_pre + L.ntiles, sizeof(back), hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
+    if (wingspan_status s = read_back(c, &back, tile_pre + L.ntiles, sizeof(back)); s != WINGSPAN_OK) return s;
     if (back.err) return fail(WINGSPAN_ERR_INVALID_MATRIX, "x's indices are not strictly increasing in [0, %lld)",
                               (long long)n);
     *y_nnz = back.total;
@@ -1659,11 +1738,11 @@ wingspan_status op_count(Ctx &c, const wingspan_csr *At, const wingspan_csr *B, 
     c.partials = reinterpret_cast<int64_t *>(c.ws + L.off_partials);
     *P = 0;
     if (At->nrows == 0) return WINGSPAN_OK;
-    wingspan_status s = run_scan(c, OpProdIn{At->row_ptr, B->row_ptr}, At->nrows, pref);
+    if (c.back.p == nullptr) c.back.take(c.st);
+    wingspan_status s = run_scan(c, OpProdIn{At->row_ptr, B->row_ptr}, At->nrows, pref, true, nullptr,
+                                 c.back.to<int64_t>());
     if (s != WINGSPAN_OK) return s;
-    HIP_TRY(hipMemcpyAsync(P, pref + At->nrows, sizeof(int64_t), hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
-    return WINGSPAN_OK;
+    return read_back(c, P, pref + At->nrows, sizeof(int64_t));
 }
 
 template <typename V>
@@ -1726,9 +1805,9 @@ wingspan_status op_impl(Ctx &c, const wingspan_csr *At, const wingspan_csr *B, c
         run_col + std::max<int64_t>(P, 1));
     LAUNCH_CHECK("outer merge");
     // 3. C.row_ptr, then the rows gathered into CSR
-    if ((s = run_scan(c, CountIn{row_nnz}, m, c_rp)) != WINGSPAN_OK) return s;
-    HIP_TRY(hipMemcpyAsync(c_nnz, c_rp + m, sizeof(int64_t), hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
+    if (c.back.p == nullptr) c.back.take(c.st);
+    if ((s = run_scan(c, CountIn{row_nnz}, m, c_rp, true, nullptr, c.back.to<int64_t>())) != WINGSPAN_OK) return s;
+    if ((s = read_back(c, c_nnz, c_rp + m, sizeof(int64_t))) != WINGSPAN_OK) return s;
     if (*c_nnz > c_cap)
         return fail(WINGSPAN_ERR_INSUFFICIENT_CAPACITY, "C has %lld entries but c_capacity is %lld",
                     (long long)*c_nnz, (long long)c_cap);
@@ -2058,12 +2137,12 @@ wingspan_status wingspan_elementwise_structure(wingspan_ew_op op, const wingspan
             planned = true;
         }
     }
-    if ((s = run_scan(c, EwCountIn{A->row_ptr, B->row_ptr, T.dups, static_cast<int>(op)}, m, c_row_ptr_dev)) !=
-        WINGSPAN_OK)
+    c.back.take(c.st);
+    if ((s = run_scan(c, EwCountIn{A->row_ptr, B->row_ptr, T.dups, static_cast<int>(op)}, m, c_row_ptr_dev, true,
+                      nullptr, c.back.to<int64_t>())) != WINGSPAN_OK)
         return s;
     int64_t total = 0;
-    HIP_TRY(hipMemcpyAsync(&total, c_row_ptr_dev + m, sizeof(int64_t), hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
+    if ((s = read_back(c, &total, c_row_ptr_dev + m, sizeof(int64_t))) != WINGSPAN_OK) return s;
     *c_nnz = total;
     if (planned) ew_remember(ew_key_of(op, A, B, workspace_dev, workspace_bytes));
     return WINGSPAN_OK;
@@ -2134,6 +2213,7 @@ wingspan_status wingspan_spmspv(const wingspan_csr *At, wingspan_dtype dtype, co
     c.st = static_cast<hipStream_t>(stream);
     c.ws = static_cast<char *>(workspace_dev);
     c.partials = reinterpret_cast<int64_t *>(c.ws + L.off_partials);
+    c.back.take(c.st);
     if (dtype == WINGSPAN_F32)
         return sv_impl<float>(c, At, L, x_idx_dev, static_cast<const float *>(x_val_dev), nnz_x, y_idx_dev,
                               static_cast<float *>(y_val_dev), y_cap, y_nnz);
