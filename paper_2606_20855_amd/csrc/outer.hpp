@@ -6,26 +6,34 @@
 // A comes by its columns (At, the CSR arrays of A's transpose) and B by its
 // rows, so the rank-1 update of index k pairs row k of At with row k of B.
 // Its |At_k| * |B_k| products, over all k, are numbered flat (q over the
-// exclusive prefix pref of the per-k counts) and cut into chunks of kOpChunk:
-//   1. each workgroup forms its chunk's products, sorts them by (row, column)
-//      in LDS and sums equal coordinates: the workgroup's own partial C;
-//   2. coalesce: every partial entry moves to its row's bucket (the partial
-//      C's rows concatenated, in arbitrary order), then each row's bucket is
-//      sorted by column and equal columns summed: in registers up to 64
-//      entries, in LDS up to kOpRowCap, and beyond that as runs of kOpRowCap
-//      sorted in LDS then merged pairwise in global memory (merge path, each
-//      output tile merged in LDS);
-//   3. the compacted rows are scanned into C.row_ptr and gathered into CSR.
+// exclusive prefix pref of the per-k counts):
+//   1. claim: every entry of At (row i of A, index k) claims |B_k| places of row
+//      i's bucket, the merge level's per-row storage (one atomic per entry, whose
+//      old value is the entry's place);
+//   2. expand: chunks of kOpChunk products are formed and written to their
+//      places, so a bucket holds its row's partial entries as whole rows of B
+//      scaled, in arbitrary order;
+//   3. coalesce: each row's bucket is sorted by column and equal columns summed:
+//      in registers up to 256 entries, in LDS up to kOpRowCap, and beyond that as
+//      runs of kOpRowCap sorted in LDS then merged pairwise in global memory
+//      (merge path, each output tile merged in LDS);
+//   4. the compacted rows are scanned into C.row_ptr and gathered into CSR.
+// (Sorting and summing each chunk first, as a partial C per workgroup, halved the
+// entries the coalesce sees on a mesh but cost more than the rest together: 327
+// us of LDS bitonic sort and 101 us of moves for the 6.5 M products of a 512 x
+// 512 grid's square, against 83 us for claims and expansion.)
 // Products are formed and summed in double; values are rounded once.
 #pragma once
 
 #include "search.hpp"
+#include "tiers.hpp"
 
 namespace wsp {
 
-constexpr int kOpChunk = 2048;     // products per workgroup (its partial C)
-constexpr int kOpBlock = 1024;     // threads of the expand kernel
-constexpr int kOpStage = 1024;     // k indices a chunk stages in LDS
+constexpr int kOpChunk = 2048;     // products (expand) or entries of At (claim) per workgroup
+constexpr int kOpBlock = 256;      // threads of the claim and expand kernels
+constexpr int kOpStage = 2048;     // k indices a chunk stages in LDS
+constexpr int kOpMidCap = 256;     // longest row bucket sorted in one wave's registers
 constexpr int kOpRowCap = 4096;    // longest row bucket sorted whole in LDS; also the run and merge tile length
 constexpr int kOpRowBlock = 256;   // threads per long row in the coalesce
 constexpr int kOpHugeBlock = 1024; // threads per row past kOpRowCap
@@ -82,11 +90,62 @@ __device__ __forceinline__ int block_excl_scan(int x, int *scratch, int *total) 
     return before + incl - x;
 }
 
-// 1. A workgroup's partial C: products [q0, q0 + kOpChunk) formed, sorted by
-// key = row << 32 | column (row-major order), equal keys summed; written compacted at part_*[q0..)
-// with their count in part_len[chunk]; row_cnt[row] counts the entries each
-// row receives from all partial Cs (one atomic per run of a row in the
-// partial C, which its sort made contiguous).
+// Clears the rows' entry counts and the coalesce's counters.
+__global__ void __launch_bounds__(256) op_clear(int32_t *__restrict__ row_cnt, int64_t m, int32_t *counters) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i < m) row_cnt[i] = 0;
+    if (i < 4) counters[i] = 0;
+}
+
+// 1. Entry e of At, of index k, claims |B_k| places of its row's bucket:
+// place[e] (entries with products only); row_cnt ends at the buckets' sizes.
+__global__ void __launch_bounds__(kOpBlock) op_claim(const int32_t *__restrict__ at_rp,
+                                                     const int32_t *__restrict__ at_col,
+                                                     const int32_t *__restrict__ b_rp, int K, int64_t nnz,
+                                                     int32_t *__restrict__ row_cnt, int32_t *__restrict__ place) {
+    __shared__ int32_t s_rp[kOpStage];
+    __shared__ int s_t[2];
+    constexpr int PER = kOpChunk / kOpBlock;
+    const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kOpChunk;
+    const int64_t e1 = nnz - e0 < kOpChunk ? nnz : e0 + kOpChunk;
+    if (threadIdx.x < 2 * kWave) {
+        const int t = wave_last_le([=](int k) { return static_cast<int64_t>(at_rp[k]); }, 0, K - 1,
+                                   threadIdx.x < kWave ? e0 : e1 - 1);
+        if (lane_id() == 0) s_t[threadIdx.x / kWave] = t;
+    }
+    __syncthreads();
+    const int t0 = s_t[0], nt = s_t[1] - t0 + 1;
+    const bool staged = nt <= kOpStage;
+    if (staged)
+        for (int k = threadIdx.x; k < nt; k += kOpBlock) s_rp[k] = at_rp[t0 + k];
+    __syncthreads();
+    int row[PER], n[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t e = e0 + threadIdx.x + u * kOpBlock;
+        n[u] = 0;
+        row[u] = 0;
+        if (e < e1) {
+            int lo = 0, hi = nt - 1;   // the last index whose entries begin at or before e
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if ((staged ? s_rp[mid] : at_rp[t0 + mid]) <= e) lo = mid;
+                else hi = mid - 1;
+            }
+            row[u] = at_col[e];
+            n[u] = b_rp[t0 + lo + 1] - b_rp[t0 + lo];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (n[u] > 0) n[u] = atomicAdd(&row_cnt[row[u]], n[u]);
+        else n[u] = -1;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (n[u] >= 0) place[e0 + threadIdx.x + u * kOpBlock] = n[u];
+}
+
+// 2. Products [q0, q0 + kOpChunk) formed and written to their places.
 template <typename V>
 __global__ void __launch_bounds__(kOpBlock) op_expand(const int32_t *__restrict__ at_rp,
                                                       const int32_t *__restrict__ at_col,
@@ -95,183 +154,242 @@ __global__ void __launch_bounds__(kOpBlock) op_expand(const int32_t *__restrict_
                                                       const int32_t *__restrict__ b_col,
                                                       const V *__restrict__ b_val, int K,
                                                       const int64_t *__restrict__ pref, int64_t P,
-                                                      int64_t *__restrict__ part_key, double *__restrict__ part_val,
-                                                      int32_t *__restrict__ part_len, int32_t *__restrict__ row_cnt) {
-    __shared__ int64_t s_key[kOpChunk];
-    __shared__ double s_val[kOpChunk];
-    __shared__ int64_t c_key[kOpChunk];   // the partial C, compacted
-    __shared__ double c_val[kOpChunk];
+                                                      const int32_t *__restrict__ place,
+                                                      const int64_t *__restrict__ bucket_off,
+                                                      int32_t *__restrict__ bkt_col, double *__restrict__ bkt_val) {
     __shared__ int64_t s_pref[kOpStage];
     __shared__ int s_t[2];
-    __shared__ int s_scan[kOpBlock / kWave];
+    constexpr int PER = kOpChunk / kOpBlock;
     const int64_t q0 = static_cast<int64_t>(blockIdx.x) * kOpChunk;
-    if (q0 >= P) return;   // whole workgroup
     const int64_t q1 = P - q0 < kOpChunk ? P : q0 + kOpChunk;
-    if (threadIdx.x < kWave) {
-        const int t0 = wave_find_entry(pref, K, q0);
-        const int t1 = wave_find_entry(pref, K, q1 - 1);
-        if (threadIdx.x == 0) {
-            s_t[0] = t0;
-            s_t[1] = t1;
-        }
+    if (threadIdx.x < 2 * kWave) {
+        const int t = wave_find_entry(pref, K, threadIdx.x < kWave ? q0 : q1 - 1);
+        if (lane_id() == 0) s_t[threadIdx.x / kWave] = t;
     }
     __syncthreads();
     const int t0 = s_t[0];
     const int nt = s_t[1] - t0 + 1;
     const bool staged = nt <= kOpStage;
     if (staged)
-        for (int k = threadIdx.x; k < nt; k += blockDim.x) s_pref[k] = pref[t0 + k];
+        for (int k = threadIdx.x; k < nt; k += kOpBlock) s_pref[k] = pref[t0 + k];
     __syncthreads();
-    for (int s = threadIdx.x; s < kOpChunk; s += blockDim.x) {
-        const int64_t q = q0 + s;
-        int64_t key = kOpNoKey;
-        double v = 0.0;
-        if (q < q1) {
-            const int k = staged ? t0 + lds_find_entry(s_pref, nt, q) : t0 + lds_find_entry(pref + t0, nt, q);
-            const int64_t r = q - (staged ? s_pref[k - t0] : pref[k]);
-            const int64_t nb = b_rp[k + 1] - b_rp[k];   // > 0: index k has products
-            const int64_t ai = r / nb;
-            const int ia = at_rp[k] + static_cast<int>(ai);
-            const int jb = b_rp[k] + static_cast<int>(r - ai * nb);
-            key = static_cast<int64_t>(at_col[ia]) << 32 | static_cast<uint32_t>(b_col[jb]);
-            v = to_d(at_val[ia]) * to_d(b_val[jb]);
-        }
-        s_key[s] = key;
-        s_val[s] = v;
-    }
-    __syncthreads();
-    lds_bitonic(s_key, s_val, kOpChunk);
-    // heads of runs of equal keys, two slots per thread
-    constexpr int PER = kOpChunk / kOpBlock;
-    int heads = 0;
+    // every thread's products side by side: the loads of one step of all before the next
+    int ia[PER], jb[PER], j[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const int s = threadIdx.x * PER + u;
-        const int64_t kk = s_key[s];
-        heads += (kk != kOpNoKey && (s == 0 || s_key[s - 1] != kk)) ? 1 : 0;
+        const int64_t q = q0 + threadIdx.x + u * kOpBlock < q1 ? q0 + threadIdx.x + u * kOpBlock : q1 - 1;
+        const int k = staged ? t0 + lds_find_entry(s_pref, nt, q) : t0 + lds_find_entry(pref + t0, nt, q);
+        const uint32_t r = static_cast<uint32_t>(q - (staged ? s_pref[k - t0] : pref[k]));   // (P < 2^31)
+        const int b0 = b_rp[k];
+        const uint32_t nb = static_cast<uint32_t>(b_rp[k + 1] - b0);   // > 0: index k has products
+        const uint32_t ai = r / nb;
+        j[u] = static_cast<int>(r - ai * nb);
+        ia[u] = at_rp[k] + static_cast<int>(ai);
+        jb[u] = b0 + j[u];
     }
-    int total = 0;
-    int pos = block_excl_scan(heads, s_scan, &total);
+    int row[PER], pl[PER], col[PER];
+    V av[PER], bv[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const int s = threadIdx.x * PER + u;
-        const int64_t kk = s_key[s];
-        if (kk == kOpNoKey || (s > 0 && s_key[s - 1] == kk)) continue;
-        double sum = s_val[s];
-        for (int e = s + 1; e < kOpChunk && s_key[e] == kk; ++e) sum += s_val[e];
-        c_key[pos] = kk;
-        c_val[pos] = sum;
-        ++pos;
+        row[u] = at_col[ia[u]];
+        pl[u] = place[ia[u]];
+        col[u] = b_col[jb[u]];
+        av[u] = at_val[ia[u]];
+        bv[u] = b_val[jb[u]];
     }
-    __syncthreads();
-    for (int t = threadIdx.x; t < total; t += blockDim.x) {
-        const int64_t kk = c_key[t];
-        part_key[q0 + t] = kk;
-        part_val[q0 + t] = c_val[t];
-        const int64_t row = kk >> 32;
-        if (t == 0 || (c_key[t - 1] >> 32) != row) {
-            int e = t + 1;
-            while (e < total && (c_key[e] >> 32) == row) ++e;
-            atomicAdd(&row_cnt[row], e - t);
-        }
-    }
-    if (threadIdx.x == 0) part_len[blockIdx.x] = total;
-}
-
-// 2a. Each run of a row in a partial C claims that many slots of the row's
-// bucket (one atomic) and copies its entries there.
-__global__ void __launch_bounds__(256) op_bucket(const int64_t *__restrict__ part_key,
-                                                 const double *__restrict__ part_val,
-                                                 const int32_t *__restrict__ part_len,
-                                                 const int64_t *__restrict__ bucket_off, int32_t *__restrict__ row_fill,
-                                                 int32_t *__restrict__ bkt_col, double *__restrict__ bkt_val) {
-    __shared__ int32_t s_row[kOpChunk];
-    const int len = part_len[blockIdx.x];
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kOpChunk;
-    for (int t = threadIdx.x; t < len; t += blockDim.x) s_row[t] = static_cast<int32_t>(part_key[base + t] >> 32);
-    __syncthreads();
-    for (int t = threadIdx.x; t < len; t += blockDim.x) {
-        const int row = s_row[t];
-        if (t > 0 && s_row[t - 1] == row) continue;
-        int e = t + 1;
-        while (e < len && s_row[e] == row) ++e;
-        const int64_t pos = bucket_off[row] + atomicAdd(&row_fill[row], e - t);
-        for (int u = t; u < e; ++u) {
-            bkt_col[pos + (u - t)] = static_cast<int32_t>(part_key[base + u] & 0xffffffffll);
-            bkt_val[pos + (u - t)] = part_val[base + u];
+    int64_t at[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) at[u] = bucket_off[row[u]] + pl[u] + j[u];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (q0 + threadIdx.x + u * kOpBlock < q1) {
+            bkt_col[at[u]] = col[u];
+            bkt_val[at[u]] = to_d(av[u]) * to_d(bv[u]);
         }
     }
 }
 
-// 2b. Short buckets, S lanes per row (S = 32: buckets of at most 32 entries;
-// S = 64: 33 to 64, and the longer ones are listed: up to kOpRowCap from the
-// front of long_rows for op_merge_long (count in counters[0]), the rest from
-// its back for op_merge_huge (count in counters[2])): sorted in registers
-// (bitonic through lane shuffles within the S-lane group), equal columns
-// summed, written back compacted from the bucket's start (columns in bkt_col,
-// values rounded to V in out_val).
-
-template <int S, typename V>
+// 3a. Buckets of at most 32 entries, 32 lanes per row: (column, place) keys
+// sorted in registers, equal columns summed, written back compacted from the
+// bucket's start (columns in bkt_col, values rounded to V in out_val). Key as in
+// tiny_kernel.
+template <typename Key, typename V>
 __global__ void __launch_bounds__(256) op_merge_short(const int64_t *__restrict__ bucket_off, int64_t m,
                                                       int32_t *__restrict__ bkt_col,
                                                       const double *__restrict__ bkt_val, V *__restrict__ out_val,
-                                                      int32_t *__restrict__ row_nnz, int32_t *__restrict__ long_rows,
-                                                      int32_t *counters) {
-    static_assert(S == 32 || S == 64, "groups of 32 or 64 lanes");
+                                                      int32_t *__restrict__ row_nnz) {
+    constexpr int S = 32, LOG2S = 5;
     const int64_t row = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / S;
-    const int ln = lane_id() % S;
+    const int lane = lane_id(), ln = lane & (S - 1);
     const int64_t lo = row < m ? bucket_off[row] : 0;
     const int64_t len = row < m ? bucket_off[row + 1] - lo : 0;
-    // this kernel's rows: lengths (S/2, S] (and 0 .. S/2 too when S = 32)
-    const bool mine = row < m && len <= S && (S == 32 || len > S / 2);
-    if (S == 64 && row < m && len > S && ln == 0) {
-        if (len > kOpRowCap)
-            long_rows[m - 1 - atomicAdd(&counters[2], 1)] = static_cast<int32_t>(row);
-        else
-            long_rows[atomicAdd(&counters[0], 1)] = static_cast<int32_t>(row);
-    }
-    // a wave without a row of this kernel is done; in the others every group takes part in the shuffles
+    const bool mine = row < m && len <= S;
+    // a wave without a row of this kernel is done; in the others every lane takes part in the moves
     if (ballot(mine) == 0ull) return;
-    int key = mine && ln < len ? bkt_col[lo + ln] : 0x7fffffff;
-    double v = mine && ln < len ? bkt_val[lo + ln] : 0.0;
-    for (int k = 2; k <= S; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const int ok = __shfl_xor(key, j, S);
-            const double ov = __shfl_xor(v, j, S);
-            const bool lower = (ln & j) == 0;
-            const bool up = (ln & k) == 0;
-            // the lower lane of an ascending pair keeps the smaller key
-            const bool take = lower == up ? ok < key : ok > key;
-            if (take) {
-                key = ok;
-                v = ov;
-            }
+    const bool live = mine && ln < len;
+    const int col = live ? bkt_col[lo + ln] : 0;
+    const double v0 = live ? bkt_val[lo + ln] : 0.0;
+    Key x[1] = {live ? static_cast<Key>(static_cast<uint32_t>(col)) << LOG2S | static_cast<Key>(ln) : ~Key(0)};
+    bitonic_sort<S, 2, 1>(x, ln);
+    const uint32_t c = static_cast<uint32_t>(x[0] >> LOG2S);
+    const uint32_t prev = static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(c), kDppWaveShr1, 0xf, 0xf, false));
+    const bool head = live && (ln == 0 || prev != c);   // (sorted, the keys fill the first len lanes)
+    const uint64_t hm = ballot(head) & (0xffffffffull << (lane - ln));
+    double sum = __shfl(v0, static_cast<int>(x[0]) & (S - 1), S);
+    {
+        const uint64_t after = lane < kWave - 1 ? hm >> (lane + 1) : 0ull;
+        const int n = after ? __ffsll(static_cast<long long>(after)) : static_cast<int>(len) - ln;
+        double t = sum;
+        for (int d = 1; ballot(head && d < n) != 0ull; ++d) {
+            t = __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(t), 0x130, 0xf, 0xf, false),
+                                 __builtin_amdgcn_update_dpp(0, __double2loint(t), 0x130, 0xf, 0xf, false));
+            if (head && d < n) sum += t;
         }
     }
-    const int prev = __shfl_up(key, 1, S);
-    const bool head = mine && ln < len && (ln == 0 || prev != key);
-    const uint64_t hw = ballot(head);
-    const int gbase = lane_id() - ln;   // the group's first lane in the wave
-    const uint64_t hm = S == 64 ? hw : (hw >> gbase) & 0xffffffffull;
-    // sum each run: a head adds the values of the lanes after it with its key
-    double sum = v;
-    for (int d = 1; d < S; ++d) {
-        const int ok = __shfl_down(key, d, S);
-        const double ov = __shfl_down(v, d, S);
-        const bool more = ln + d < len && ok == key;
-        if (ballot(head && more) == 0ull) break;
-        if (head && more) sum += ov;
-    }
     if (head) {
-        const int pos = __popcll(hm & ((1ull << ln) - 1ull));
-        bkt_col[lo + pos] = key;
+        const int pos = __popcll(hm & ((1ull << lane) - 1ull));
+        bkt_col[lo + pos] = static_cast<int32_t>(c);
         out_val[lo + pos] = static_cast<V>(sum);
     }
     if (mine && ln == 0) row_nnz[row] = __popcll(hm);
 }
 
-// 2c. Long buckets (65 .. kOpRowCap entries), a workgroup per row, rows taken
-// grid-stride from the list op_merge_short made: the bucket is sorted in LDS
+// Bitonic sort of 64 R keys held R per lane (key i in register i / 64 of lane
+// i % 64), ascending: distances below 64 across lanes, the others between
+// registers.
+template <int J, int R>
+__device__ __forceinline__ void wave_sort_lanes(uint64_t (&x)[R], int ln, int k) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool up = k >= kWave ? ((r * kWave) & k) == 0 : (ln & k) == 0;
+        bitonic_step<J>(x[r], ln, ((ln & J) == 0) == up);
+    }
+    if constexpr (J > 1) wave_sort_lanes<J / 2, R>(x, ln, k);
+}
+template <int K, int R>
+__device__ __forceinline__ void wave_sort(uint64_t (&x)[R], int ln) {
+    if constexpr (K > kWave) {
+#pragma unroll
+        for (int j = K / 2; j >= kWave; j >>= 1) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int p = r ^ (j / kWave);
+                if (p > r) {
+                    const bool swap = ((r * kWave) & K) == 0 ? x[p] < x[r] : x[r] < x[p];
+                    const uint64_t a = x[r], b = x[p];
+                    x[r] = swap ? b : a;
+                    x[p] = swap ? a : b;
+                }
+            }
+        }
+        wave_sort_lanes<kWave / 2, R>(x, ln, K);
+    } else {
+        wave_sort_lanes<K / 2, R>(x, ln, K);
+    }
+    if constexpr (K < kWave * R) wave_sort<2 * K, R>(x, ln);
+}
+
+// One bucket of at most 64 R entries, by one wave: s_val holds 64 R doubles.
+template <int R, typename V>
+__device__ __forceinline__ void op_merge_wave(int64_t lo, int len, int32_t *__restrict__ bkt_col,
+                                              const double *__restrict__ bkt_val, V *__restrict__ out_val,
+                                              int32_t *__restrict__ nnz, double *s_val, int ln) {
+    uint64_t x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kWave + ln;
+        x[r] = i < len ? static_cast<uint64_t>(static_cast<uint32_t>(bkt_col[lo + i])) << 32 | i : ~0ull;
+    }
+    wave_sort<2, R>(x, ln);
+    double v[R];
+    uint64_t heads[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kWave + ln;
+        v[r] = i < len ? bkt_val[lo + static_cast<int>(x[r] & 0xffffffffu)] : 0.0;
+        s_val[i] = v[r];
+        const int c = static_cast<int>(x[r] >> 32);
+        int prev = __builtin_amdgcn_update_dpp(0, c, kDppWaveShr1, 0xf, 0xf, false);
+        if (ln == 0) prev = r > 0 ? __builtin_amdgcn_readlane(static_cast<int>(x[r > 0 ? r - 1 : 0] >> 32), kWave - 1) : -1;
+        heads[r] = ballot(i < len && prev != c);
+    }
+    wave_lds_fence();
+    int before = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kWave + ln;
+        if ((heads[r] >> ln) & 1ull) {
+            // the entries up to the next head
+            int end = len;
+#pragma unroll
+            for (int t = R - 1; t > r; --t)
+                if (heads[t]) end = t * kWave + __ffsll(static_cast<long long>(heads[t])) - 1;
+            const uint64_t after = ln < kWave - 1 ? heads[r] >> (ln + 1) : 0ull;
+            if (after) end = i + __ffsll(static_cast<long long>(after));
+            double sum = v[r];
+            for (int q = i + 1; q < end; ++q) sum += s_val[q];
+            const int pos = before + __popcll(heads[r] & ((1ull << ln) - 1ull));
+            bkt_col[lo + pos] = static_cast<int32_t>(x[r] >> 32);
+            out_val[lo + pos] = static_cast<V>(sum);
+        }
+        before += __popcll(heads[r]);
+    }
+    if (ln == 0) *nnz = before;
+    wave_lds_fence();
+}
+
+// 3b. Buckets of 33 to kOpMidCap entries, a wave per row; a workgroup looks at
+// 64 rows and lists the longer ones (one atomic for all of them): up to kOpRowCap
+// from the front of long_rows for op_merge_long (count in counters[0]), the rest
+// from its back for op_merge_huge (counters[2]).
+template <typename V>
+__global__ void __launch_bounds__(256) op_merge_mid(const int64_t *__restrict__ bucket_off, int64_t m,
+                                                    int32_t *__restrict__ bkt_col,
+                                                    const double *__restrict__ bkt_val, V *__restrict__ out_val,
+                                                    int32_t *__restrict__ row_nnz, int32_t *__restrict__ long_rows,
+                                                    int32_t *counters) {
+    __shared__ double s_val[256 / kWave][kOpMidCap];
+    const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
+    const int ln = lane_id();
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kWave;
+    const int64_t row = row0 + ln;
+    const int64_t lo = row < m ? bucket_off[row] : 0;
+    const int64_t len = row < m ? bucket_off[row + 1] - lo : 0;
+    if (wv == 0) {
+        const uint64_t below = (1ull << ln) - 1ull;
+        const uint64_t lng = ballot(len > kOpMidCap && len <= kOpRowCap), huge = ballot(len > kOpRowCap);
+        if (lng) {
+            int at = 0;
+            if (ln == 0) at = atomicAdd(&counters[0], static_cast<int>(__popcll(lng)));
+            at = uniform(at);
+            if ((lng >> ln) & 1ull) long_rows[at + __popcll(lng & below)] = static_cast<int32_t>(row);
+        }
+        if (huge) {
+            int at = 0;
+            if (ln == 0) at = atomicAdd(&counters[2], static_cast<int>(__popcll(huge)));
+            at = uniform(at);
+            if ((huge >> ln) & 1ull) long_rows[m - 1 - at - __popcll(huge & below)] = static_cast<int32_t>(row);
+        }
+    }
+    uint64_t mid = ballot(len > 32 && len <= kOpMidCap);
+    for (int i = 0; mid != 0ull; ++i) {
+        const int l = __ffsll(static_cast<long long>(mid)) - 1;
+        mid &= mid - 1;
+        if ((i & (256 / kWave - 1)) != wv) continue;
+        const int64_t rlo = static_cast<int64_t>(
+            static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lo >> 32), l))) << 32 |
+            static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lo), l)));
+        const int n = __builtin_amdgcn_readlane(static_cast<int>(len), l);
+        int32_t *nnz = row_nnz + row0 + l;
+        if (n <= kWave) op_merge_wave<1, V>(rlo, n, bkt_col, bkt_val, out_val, nnz, s_val[wv], ln);
+        else if (n <= 2 * kWave) op_merge_wave<2, V>(rlo, n, bkt_col, bkt_val, out_val, nnz, s_val[wv], ln);
+        else op_merge_wave<4, V>(rlo, n, bkt_col, bkt_val, out_val, nnz, s_val[wv], ln);
+    }
+}
+
+// 3c. Long buckets (kOpMidCap + 1 .. kOpRowCap entries), a workgroup per row, rows taken
+// grid-stride from the list op_merge_mid made: the bucket is sorted in LDS
 // and compacted as in op_merge_short.
 template <typename V>
 __global__ void __launch_bounds__(kOpRowBlock) op_merge_long(const int64_t *__restrict__ bucket_off,
@@ -341,8 +459,8 @@ __device__ __forceinline__ int lds_upper_bound(const int32_t *k, int n, int32_t 
     return lo;
 }
 
-// 2d. Buckets longer than kOpRowCap, a workgroup per row, rows taken
-// grid-stride from the back of long_rows (op_merge_short lists them there):
+// 3d. Buckets longer than kOpRowCap, a workgroup per row, rows taken
+// grid-stride from the back of long_rows (op_merge_mid lists them there):
 //   runs of kOpRowCap entries are sorted in LDS into buffer X; then runs are
 //   merged pairwise, X to Y and back, doubling their length until one is left:
 //   each output tile of kOpRowCap entries takes its share of the two runs

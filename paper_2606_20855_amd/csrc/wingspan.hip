@@ -1671,14 +1671,14 @@ constexpr int64_t kOpLongGrid = 2048;   // coalesce workgroups for long rows at 
 constexpr int64_t kOpHugeGrid = 512;    // the same for rows past kOpRowCap (one or two workgroups per CU)
 
 struct OpLayout {
-    size_t off_ctr, off_pref, off_partials, off_part_key, off_part_val, off_part_len, off_row_cnt, off_row_fill,
+    size_t off_ctr, off_pref, off_partials, off_part_key, off_part_val, off_place, off_row_cnt,
         off_bucket, off_row_nnz, off_long, off_bkt_col, off_bkt_val, off_out_val, total;
 };
 
 OpLayout op_plan(const wingspan_csr *At, const wingspan_csr *B, int64_t P) {
     OpLayout L{};
     const int64_t K = std::max<int64_t>(At->nrows, 1), m = std::max<int64_t>(At->ncols, 1);
-    const int64_t p = std::max<int64_t>(P, 1), chunks = (p + kOpChunk - 1) / kOpChunk;
+    const int64_t p = std::max<int64_t>(P, 1);
     size_t off = 0;
     L.off_ctr = off;
     off += align_up(sizeof(int32_t) * 4);
@@ -1687,15 +1687,13 @@ OpLayout op_plan(const wingspan_csr *At, const wingspan_csr *B, int64_t P) {
     L.off_partials = off;
     const int64_t n = std::max<int64_t>(K, m) + 1;
     off += align_up(sizeof(int64_t) * ((n + kScanTile - 1) / kScanTile + 2));
-    L.off_part_key = off;   // after the bucket step: two int32 column arrays of p for the long-row merge
+    L.off_part_key = off;   // two int32 column arrays of p and one of values for the long-row merge
     off += align_up(sizeof(int64_t) * p);
     L.off_part_val = off;
     off += align_up(sizeof(double) * p);
-    L.off_part_len = off;
-    off += align_up(sizeof(int32_t) * chunks);
+    L.off_place = off;
+    off += align_up(sizeof(int32_t) * std::max<int64_t>(At->nnz, 1));
     L.off_row_cnt = off;
-    off += align_up(sizeof(int32_t) * m);
-    L.off_row_fill = off;
     off += align_up(sizeof(int32_t) * m);
     L.off_bucket = off;
     off += align_up(sizeof(int64_t) * (m + 1));
@@ -1754,9 +1752,8 @@ wingspan_status op_impl(Ctx &c, const wingspan_csr *At, const wingspan_csr *B, c
     const int64_t *pref = reinterpret_cast<const int64_t *>(at(L.off_pref));
     int64_t *part_key = reinterpret_cast<int64_t *>(at(L.off_part_key));
     double *part_val = reinterpret_cast<double *>(at(L.off_part_val));
-    int32_t *part_len = reinterpret_cast<int32_t *>(at(L.off_part_len));
+    int32_t *place = reinterpret_cast<int32_t *>(at(L.off_place));
     int32_t *row_cnt = reinterpret_cast<int32_t *>(at(L.off_row_cnt));
-    int32_t *row_fill = reinterpret_cast<int32_t *>(at(L.off_row_fill));
     int64_t *bucket = reinterpret_cast<int64_t *>(at(L.off_bucket));
     int32_t *row_nnz = reinterpret_cast<int32_t *>(at(L.off_row_nnz));
     int32_t *long_rows = reinterpret_cast<int32_t *>(at(L.off_long));
@@ -1770,41 +1767,42 @@ wingspan_status op_impl(Ctx &c, const wingspan_csr *At, const wingspan_csr *B, c
         LAUNCH_CHECK("outer empty");
         return WINGSPAN_OK;
     }
-    fill_i32<<<1, 64, 0, c.st>>>(ctr, 4, 0);
-    fill_i32<<<blocks_for(m, 256), 256, 0, c.st>>>(row_cnt, m, 0);
-    fill_i32<<<blocks_for(m, 256), 256, 0, c.st>>>(row_fill, m, 0);
+    op_clear<<<blocks_for(std::max<int64_t>(m, 4), 256), 256, 0, c.st>>>(row_cnt, m, ctr);
     LAUNCH_CHECK("outer clear");
-    const int64_t chunks = (P + kOpChunk - 1) / kOpChunk;
-    // 1. the workgroups' partial Cs
+    // 1. every entry of At claims its places of its row's bucket
     if (P > 0) {
-        op_expand<V><<<static_cast<unsigned>(chunks), kOpBlock, 0, c.st>>>(
-            At->row_ptr, At->col_idx, static_cast<const V *>(At->val), B->row_ptr, B->col_idx,
-            static_cast<const V *>(B->val), static_cast<int>(K), pref, P, part_key, part_val, part_len, row_cnt);
-        LAUNCH_CHECK("outer expand");
+        op_claim<<<blocks_for(At->nnz, kOpChunk), kOpBlock, 0, c.st>>>(At->row_ptr, At->col_idx, B->row_ptr,
+                                                                       static_cast<int>(K), At->nnz, row_cnt, place);
+        LAUNCH_CHECK("outer claim");
     }
-    // 2. coalesce: row buckets, then each bucket sorted and compacted
-    wingspan_status s = run_scan(c, CountIn{row_cnt}, m, bucket);
+    // 2. the products, into the buckets
+    wingspan_status s = run_scan(c, CountIn{row_cnt}, m, bucket, true);
     if (s != WINGSPAN_OK) return s;
     if (P > 0) {
-        op_bucket<<<static_cast<unsigned>(chunks), 256, 0, c.st>>>(part_key, part_val, part_len, bucket, row_fill,
-                                                                   bkt_col, bkt_val);
-        LAUNCH_CHECK("outer bucket");
+        op_expand<V><<<blocks_for(P, kOpChunk), kOpBlock, 0, c.st>>>(
+            At->row_ptr, At->col_idx, static_cast<const V *>(At->val), B->row_ptr, B->col_idx,
+            static_cast<const V *>(B->val), static_cast<int>(K), pref, P, place, bucket, bkt_col, bkt_val);
+        LAUNCH_CHECK("outer expand");
     }
-    op_merge_short<32, V><<<blocks_for(m, 256 / 32), 256, 0, c.st>>>(bucket, m, bkt_col, bkt_val, out_val, row_nnz,
-                                                                      long_rows, ctr);
-    op_merge_short<64, V><<<blocks_for(m, 256 / 64), 256, 0, c.st>>>(bucket, m, bkt_col, bkt_val, out_val, row_nnz,
-                                                                      long_rows, ctr);
+    // 3. coalesce: each bucket sorted and compacted
+    if (B->ncols < (int64_t(1) << 32) / 32)
+        op_merge_short<uint32_t, V><<<blocks_for(m, 256 / 32), 256, 0, c.st>>>(bucket, m, bkt_col, bkt_val, out_val,
+                                                                               row_nnz);
+    else
+        op_merge_short<uint64_t, V><<<blocks_for(m, 256 / 32), 256, 0, c.st>>>(bucket, m, bkt_col, bkt_val, out_val,
+                                                                               row_nnz);
+    op_merge_mid<V><<<blocks_for(m, kWave), 256, 0, c.st>>>(bucket, m, bkt_col, bkt_val, out_val, row_nnz, long_rows,
+                                                            ctr);
     op_merge_long<V><<<static_cast<unsigned>(std::min<int64_t>(m, kOpLongGrid)), kOpRowBlock, 0, c.st>>>(
         bucket, bkt_col, bkt_val, out_val, row_nnz, long_rows, ctr);
-    // rows past kOpRowCap: the partial Cs are no longer needed, so their arrays
-    // hold the sorted runs (X: columns in part_key's first half, values in
+    // rows past kOpRowCap: their own arrays hold the sorted runs (X: columns in part_key's first half, values in
     // part_val; Y: columns in its second half, values in bkt_val)
     int32_t *run_col = reinterpret_cast<int32_t *>(part_key);
     op_merge_huge<V><<<static_cast<unsigned>(std::min<int64_t>(m, kOpHugeGrid)), kOpHugeBlock, 0, c.st>>>(
         bucket, m, bkt_col, bkt_val, out_val, row_nnz, long_rows, ctr, run_col, part_val,
         run_col + std::max<int64_t>(P, 1));
     LAUNCH_CHECK("outer merge");
-    // 3. C.row_ptr, then the rows gathered into CSR
+    // 4. C.row_ptr, then the rows gathered into CSR
     if (c.back.p == nullptr) c.back.take(c.st);
     if ((s = run_scan(c, CountIn{row_nnz}, m, c_rp, true, nullptr, c.back.to<int64_t>())) != WINGSPAN_OK) return s;
     if ((s = read_back(c, c_nnz, c_rp + m, sizeof(int64_t))) != WINGSPAN_OK) return s;
