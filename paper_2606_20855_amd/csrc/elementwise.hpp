@@ -13,13 +13,16 @@
 // along. A tile's shares of A and of B are contiguous runs of their entry
 // arrays, so a workgroup loads both with coalesced reads into LDS as
 // (row, column) keys and matches them there:
-//   ew_tile_count: the coordinates both sides store, per tile (and per row,
-//                  for C's row pointer);
-//   ew_tile_write: each entry's place in C, from its rank among the other
-//                  side's share and the common coordinates before it, after
-//                  the tile's first place (a scan of the tiles' counts).
+//   ew_tile_count: merges the tile: C's entries from it, a two-bit code per
+//                  merged entry (which side it is from, whether the other side
+//                  stores its coordinate too), and each row's place in the tile;
+//   ew_row_ptr:    C's row pointer, from the rows' places and the scan of the
+//                  tiles' counts;
+//   ew_tile_write: C's entries of a tile from the codes alone (popcounts give
+//                  each entry's places in A, B and C), no keys merged again.
 // Long and short rows balance by themselves; nothing but the entries, the
-// row pointers and C is read or written at the size of the inputs.
+// row pointers and C is read or written at the size of the inputs (the codes
+// are half a byte per entry).
 #pragma once
 
 #include "search.hpp"
@@ -28,7 +31,6 @@ namespace wsp {
 
 constexpr int kEwTile = 2048;    // merged entries per tile (one more when a common coordinate straddles)
 constexpr int kEwBlock = 256;
-constexpr int kEwRows = 1024;    // rows whose common coordinates a tile counts in LDS (more: global atomics)
 constexpr int kEwPer = (kEwTile + 1 + kEwBlock - 1) / kEwBlock;   // consecutive tile positions per thread
 enum EwOp { kEwAdd = 0, kEwMul = 1 };
 constexpr int64_t kEwEnd = 0x7fffffffffffffffll;   // above every (row, column) key
@@ -124,20 +126,16 @@ __device__ __forceinline__ uint32_t block_excl_umax(uint32_t x, int *scratch) {
 }
 
 // Loads a tile as (row, column) keys in LDS, A's share at [0, na) and B's at
-// [na, na + nb) (with VALS, values in double beside them): the columns, with
-// coalesced reads, into the keys' low halves, and, at the same time, the row
+// [na, na + nb): the columns, with coalesced reads, into the keys' low halves, and, at the same time, the row
 // pointers of the tile's rows. Then each row that starts inside a share marks
 // its first position in the key's high half (row r0 + k as k + 1 in A's
 // share, nr + k + 1 in B's, so one max-scan over both shares serves and B's
 // marks exceed all of A's), and an exclusive max-scan over the positions,
 // kEwPer consecutive ones per thread, replaces the marks by the rows. All
 // threads call it.
-template <bool VALS, typename V>
 __device__ __forceinline__ void ew_load_tile(const EwTile &T, const int32_t *__restrict__ a_rp,
-                                             const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
-                                             const int32_t *__restrict__ b_rp, const int32_t *__restrict__ b_col,
-                                             const V *__restrict__ b_val, int64_t *s_key, double *s_val,
-                                             int *scratch) {
+                                             const int32_t *__restrict__ a_col, const int32_t *__restrict__ b_rp,
+                                             const int32_t *__restrict__ b_col, int64_t *s_key, int *scratch) {
     uint32_t *half = reinterpret_cast<uint32_t *>(s_key);   // [2p] column, [2p + 1] mark, then row
     const int n = T.na + T.nb;
     const uint32_t nr = static_cast<uint32_t>(T.nr);
@@ -153,27 +151,17 @@ __device__ __forceinline__ void ew_load_tile(const EwTile &T, const int32_t *__r
     // position p of the tile (A's share, then B's), kEwPer per thread strided by the block: all loads
     // issued before the first is waited for
     int32_t col[kEwPer];
-    double val[kEwPer];
 #pragma unroll
     for (int u = 0; u < kEwPer; ++u) {
         const int p = threadIdx.x + u * kEwBlock;
         col[u] = 0;
-        val[u] = 0.0;
-        if (p < T.na) {
-            col[u] = a_col[T.ia0 + p];
-            if (VALS) val[u] = to_d(a_val[T.ia0 + p]);
-        } else if (p < n) {
-            col[u] = b_col[T.ib0 + (p - T.na)];
-            if (VALS) val[u] = to_d(b_val[T.ib0 + (p - T.na)]);
-        }
+        if (p < T.na) col[u] = a_col[T.ia0 + p];
+        else if (p < n) col[u] = b_col[T.ib0 + (p - T.na)];
     }
 #pragma unroll
     for (int u = 0; u < kEwPer; ++u) {
         const int p = threadIdx.x + u * kEwBlock;
-        if (p < n) {
-            s_key[p] = static_cast<uint32_t>(col[u]);
-            if (VALS) s_val[p] = val[u];
-        }
+        if (p < n) s_key[p] = static_cast<uint32_t>(col[u]);
     }
     __syncthreads();
     // a non-empty row starting inside a share is the only one to mark that position
@@ -222,11 +210,26 @@ __device__ __forceinline__ int ew_split(const int64_t *s_key, int na, int nb, in
     return lo;
 }
 
-// Per tile: tile_cnt[t] = C's entries from the tile (the shares' sizes less
-// the common coordinates for the sum, the common coordinates for the
-// product). With PER_ROW, also each row's common coordinates added to
-// dups[row] (zeroed by the caller).
-template <bool PER_ROW>
+// A thread's codes: two bits for each of its kEwPer consecutive merged entries,
+// bit 0: the entry is B's, bit 1: its coordinate is common to both sides. (A's
+// half of a common coordinate comes first.)
+constexpr uint32_t kEwBit = 0x55555555u & ((1u << (2 * kEwPer)) - 1u);
+static_assert(2 * kEwPer <= 32, "a thread's codes in one word");
+// The low bits of the codes of the first cnt entries.
+__device__ __forceinline__ uint32_t ew_valid(int cnt) {
+    return cnt >= kEwPer ? kEwBit : (cnt <= 0 ? 0u : kEwBit & ((1u << (2 * cnt)) - 1u));
+}
+// The entries kept in C, of those in `valid`: for the sum all but the B half of
+// a common coordinate, for the product its A half.
+__device__ __forceinline__ uint32_t ew_kept(uint32_t codes, uint32_t valid, int op) {
+    const uint32_t b = codes & valid, c = (codes >> 1) & valid;
+    return op == kEwAdd ? valid & ~(b & c) : c & ~b;
+}
+
+// Per tile: tile_cnt[t] = C's entries from the tile, the threads' codes, and for
+// every row r that starts in the tile (rows without entries too) row_at[r] = C's
+// entries of the tile before the row (rows may be null: the caller has C's row
+// pointer). Each thread walks kEwPer positions of the merged order.
 __global__ void __launch_bounds__(kEwBlock) ew_tile_count(const int32_t *__restrict__ a_rp,
                                                           const int32_t *__restrict__ a_col,
                                                           const int32_t *__restrict__ b_rp,
@@ -234,149 +237,210 @@ __global__ void __launch_bounds__(kEwBlock) ew_tile_count(const int32_t *__restr
                                                           const int64_t *__restrict__ split_a,
                                                           const int64_t *__restrict__ split_b,
                                                           const int32_t *__restrict__ split_r, int op,
-                                                          int32_t *__restrict__ tile_cnt, int32_t *__restrict__ dups) {
+                                                          int32_t *__restrict__ tile_cnt,
+                                                          uint32_t *__restrict__ codes_out,
+                                                          int32_t *__restrict__ row_at) {
     __shared__ int64_t s_key[kEwTile + 1];
-    __shared__ int32_t s_cnt[PER_ROW ? kEwRows : 1];
+    __shared__ uint32_t s_kept[kEwBlock];   // a thread's kept entries, and C's entries before the thread
+    __shared__ int32_t s_before[kEwBlock];
     __shared__ int32_t scratch[kEwBlock / kWave];
     const EwTile T = ew_tile_of(split_a, split_b, split_r);
-    const bool local = PER_ROW && T.nr <= kEwRows;
-    if (local)
-        for (int k = threadIdx.x; k < T.nr; k += blockDim.x) s_cnt[k] = 0;
-    ew_load_tile<false, float>(T, a_rp, a_col, nullptr, b_rp, b_col, nullptr, s_key, nullptr, scratch);
+    ew_load_tile(T, a_rp, a_col, b_rp, b_col, s_key, scratch);
     const int n = T.na + T.nb;
     const int d = threadIdx.x * kEwPer;
-    int c = 0;
+    uint32_t codes = 0;
     if (d < n) {
         int i = ew_split(s_key, T.na, T.nb, d), j = d - i;
         int64_t ka = i < T.na ? s_key[i] : kEwEnd, kb = j < T.nb ? s_key[T.na + j] : kEwEnd;
-        const int steps = n - d < kEwPer ? n - d : kEwPer;
-        for (int u = 0; u < steps; ++u) {
-            if (ka <= kb) {
-                if (ka == kb) {
-                    ++c;
-                    if (PER_ROW) {
-                        const int row = static_cast<int>(ka >> 32);
-                        if (local) atomicAdd(&s_cnt[row - T.r0], 1);
-                        else atomicAdd(&dups[row], 1);
-                    }
-                }
-                ++i;
-                ka = i < T.na ? s_key[i] : kEwEnd;
-            } else {
+        int64_t prev_a = i > 0 ? s_key[i - 1] : -1;
+#pragma unroll
+        for (int u = 0; u < kEwPer; ++u) {
+            if (d + u >= n) continue;
+            const bool from_b = ka > kb;
+            const bool common = from_b ? prev_a == kb : ka == kb;
+            codes |= (static_cast<uint32_t>(from_b) | static_cast<uint32_t>(common) << 1) << (2 * u);
+            if (from_b) {
                 ++j;
                 kb = j < T.nb ? s_key[T.na + j] : kEwEnd;
+            } else {
+                prev_a = ka;
+                ++i;
+                ka = i < T.na ? s_key[i] : kEwEnd;
             }
         }
     }
-    c = block_sum<kEwBlock>(c, scratch);   // (its barriers also order the LDS counts)
-    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = op == kEwAdd ? n - c : c;
-    if (local)
-        for (int k = threadIdx.x; k < T.nr; k += blockDim.x)
-            if (s_cnt[k]) atomicAdd(&dups[T.r0 + k], s_cnt[k]);
+    codes_out[static_cast<int64_t>(blockIdx.x) * kEwBlock + threadIdx.x] = codes;
+    const uint32_t kept = ew_kept(codes, ew_valid(n - d), op);
+    int total;
+    const int before = block_excl_scan<kEwBlock>(static_cast<int>(__popc(kept)), &total, scratch);
+    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = total;
+    if (row_at == nullptr) return;
+    s_kept[threadIdx.x] = kept;
+    s_before[threadIdx.x] = before;
+    __syncthreads();
+    for (int k = threadIdx.x; k < T.nr; k += kEwBlock) {
+        // the row's first place in the tile; rows of earlier and later tiles are theirs, but for rows that start
+        // where the tile ends: the next tile begins at the last of them, and its count before each is 0
+        const int64_t p = (a_rp[T.r0 + k] - T.ia0) + (b_rp[T.r0 + k] - T.ib0);
+        if (p == n) row_at[T.r0 + k] = 0;
+        if (p < 0 || p >= n) continue;
+        const int t = static_cast<int>(p) / kEwPer, u = static_cast<int>(p) - t * kEwPer;
+        row_at[T.r0 + k] = s_before[t] + static_cast<int>(__popc(s_kept[t] & ((1u << (2 * u)) - 1u)));
+    }
 }
 
-// Entries of C's rows: |A_r| + |B_r| - dups_r (sum) or dups_r (product).
-struct EwCountIn {
-    const int32_t *a_rp, *b_rp, *dups;
-    int op;
-    __device__ __forceinline__ int64_t operator()(int64_t i) const {
-        const int64_t d = dups[i];
-        return op == kEwAdd ? static_cast<int64_t>(a_rp[i + 1] - a_rp[i]) + (b_rp[i + 1] - b_rp[i]) - d : d;
-    }
-};
+// C's row pointer: row r starts in the tile its first merged position lies in
+// (a boundary that moved past the B half of a common coordinate moved inside a
+// row). The last thread also hands the total to the host (host_total may be
+// null).
+__global__ void __launch_bounds__(256) ew_row_ptr(const int32_t *__restrict__ a_rp, const int32_t *__restrict__ b_rp,
+                                                  int64_t nrows, int64_t total_in, int64_t ntiles,
+                                                  const int64_t *__restrict__ tile_off,
+                                                  const int32_t *__restrict__ row_at, int64_t *__restrict__ c_rp,
+                                                  int64_t *host_total) {
+    const int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (r > nrows) return;
+    const int64_t p = static_cast<int64_t>(a_rp[r]) + b_rp[r];
+    int64_t c = 0;   // rows before the first entry (the first tile begins at the last of them)
+    if (p >= total_in) c = tile_off[ntiles];
+    else if (p > 0) c = tile_off[p / kEwTile] + row_at[r];
+    c_rp[r] = c;
+    if (r == nrows && host_total != nullptr) *host_total = c;
+}
+
+// The same where a side stores nothing: the other side's rows (sum) or none.
+__global__ void __launch_bounds__(256) ew_row_ptr_one_side(const int32_t *__restrict__ a_rp,
+                                                           const int32_t *__restrict__ b_rp, int64_t nrows, int op,
+                                                           int64_t *__restrict__ c_rp, int64_t *host_total) {
+    const int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (r > nrows) return;
+    const int64_t c = op == kEwAdd ? static_cast<int64_t>(a_rp[r]) + b_rp[r] : 0;
+    c_rp[r] = c;
+    if (r == nrows && host_total != nullptr) *host_total = c;
+}
 
 struct EwTileIn {
     const int32_t *cnt;
     __device__ __forceinline__ int64_t operator()(int64_t t) const { return cnt[t]; }
 };
 
-// C's entries from a tile, from tile_off[t] on: each thread walks kEwPer
-// consecutive positions of the tile's merged order (from a merge-path split),
-// keeping, for the sum, every entry but the B half of a common coordinate (the
-// A half takes a + b) and, for the product, the A half of each common
-// coordinate (a * b). The kept entries' values are then read (all loads of a
-// thread issued together, overlapping the scan of the kept counts that places
-// them), formed in double and rounded once, and the tile's part of C is
-// staged in LDS and written with coalesced stores.
+// C's entries from a tile, from tile_off[t] on: each thread's codes and one scan
+// give its entries' places in A's share, B's share and C; values are formed in
+// double and rounded once, and the tile's part of C is staged in LDS and written
+// with coalesced stores. The sum needs every entry: both shares are read with
+// coalesced loads issued before the codes are looked at, and the codes' owners
+// leave each entry's place in C in LDS. The product reads the common entries
+// alone, by the threads that own their codes.
+//
+// Bound by HBM (the sum of R-MAT 20 and its shuffled copy, double: 32 M entries
+// in and out, 780 MB: merging the keys again in this kernel 175 us, from the codes
+// 137 us, with each thread reading its own entries 228 us; the product of
+// R-MAT 18 with its pattern, float: 46 us, now 26 us).
 template <typename V, int OP>
-__global__ void __launch_bounds__(kEwBlock) ew_tile_write(const int32_t *__restrict__ a_rp,
-                                                          const int32_t *__restrict__ a_col,
+__global__ void __launch_bounds__(kEwBlock) ew_tile_write(const int32_t *__restrict__ a_col,
                                                           const V *__restrict__ a_val,
-                                                          const int32_t *__restrict__ b_rp,
                                                           const int32_t *__restrict__ b_col,
                                                           const V *__restrict__ b_val,
                                                           const int64_t *__restrict__ split_a,
                                                           const int64_t *__restrict__ split_b,
-                                                          const int32_t *__restrict__ split_r,
+                                                          const uint32_t *__restrict__ codes_in,
                                                           const int64_t *__restrict__ tile_off,
                                                           int32_t *__restrict__ c_col, V *__restrict__ c_val) {
-    __shared__ int64_t s_key[kEwTile + 1];
+    __shared__ V s_oval[kEwTile + 1];
     __shared__ int32_t s_ocol[kEwTile + 1];
+    __shared__ int32_t s_place[OP == kEwAdd ? kEwTile + 1 : 1];
     __shared__ int32_t scratch[kEwBlock / kWave];
-    const EwTile T = ew_tile_of(split_a, split_b, split_r);
-    ew_load_tile<false, V>(T, a_rp, a_col, nullptr, b_rp, b_col, nullptr, s_key, nullptr, scratch);
-    const int n = T.na + T.nb;
-    const int d = threadIdx.x * kEwPer;
-    int32_t oc[kEwPer];
-    int ai[kEwPer], bi[kEwPer];   // the kept entry's A and B share indices (-1: that side stores nothing)
-    int c = 0;
-    int i = 0, j = 0;
-    if (d < n) {
-        i = ew_split(s_key, T.na, T.nb, d);
-        j = d - i;
-    }
-    // the current A and B keys (kEwEnd past a share's end) and the last A key before j's entry
-    int64_t ka = i < T.na ? s_key[i] : kEwEnd, kb = j < T.nb ? s_key[T.na + j] : kEwEnd;
-    int64_t prev_a = i > 0 ? s_key[i - 1] : -1;
+    const int t = blockIdx.x;
+    const int64_t ia0 = split_a[t], ib0 = split_b[t];
+    const int na = static_cast<int>(split_a[t + 1] - ia0);
+    const int n = na + static_cast<int>(split_b[t + 1] - ib0);
+    const int64_t base = tile_off[t];
+    const uint32_t codes = codes_in[static_cast<int64_t>(t) * kEwBlock + threadIdx.x];
+    // the sum: both shares' entries (A's, then B's), strided by the workgroup
+    int32_t col[OP == kEwAdd ? kEwPer : 1];
+    V val[OP == kEwAdd ? kEwPer : 1];
+    if constexpr (OP == kEwAdd) {
 #pragma unroll
-    for (int u = 0; u < kEwPer; ++u) {
-        oc[u] = 0;
-        ai[u] = -1;
-        bi[u] = -1;
-        bool keep = false;
-        if (d + u < n) {
-            if (ka <= kb) {
-                const bool common = ka == kb;
-                keep = OP == kEwAdd || common;
-                oc[u] = static_cast<int32_t>(ka & 0xffffffffll);
-                ai[u] = keep ? i : -1;
-                bi[u] = keep && common ? j : -1;
-                prev_a = ka;
-                ++i;
-                ka = i < T.na ? s_key[i] : kEwEnd;
-            } else {
-                keep = OP == kEwAdd && prev_a != kb;   // else the B half of a common coordinate
-                oc[u] = static_cast<int32_t>(kb & 0xffffffffll);
-                bi[u] = keep ? j : -1;
-                ++j;
-                kb = j < T.nb ? s_key[T.na + j] : kEwEnd;
+        for (int u = 0; u < kEwPer; ++u) {
+            const int e = threadIdx.x + u * kEwBlock;
+            col[u] = 0;
+            val[u] = V(0);
+            if (e < na) {
+                col[u] = a_col[ia0 + e];
+                val[u] = a_val[ia0 + e];
+            } else if (e < n) {
+                col[u] = b_col[ib0 + (e - na)];
+                val[u] = b_val[ib0 + (e - na)];
             }
         }
-        c += keep;
     }
-    double av[kEwPer], bv[kEwPer];
-#pragma unroll
-    for (int u = 0; u < kEwPer; ++u) {
-        av[u] = ai[u] >= 0 ? to_d(a_val[T.ia0 + ai[u]]) : 0.0;
-        bv[u] = bi[u] >= 0 ? to_d(b_val[T.ib0 + bi[u]]) : 0.0;
-    }
+    const int d = threadIdx.x * kEwPer;
+    const uint32_t valid = ew_valid(n - d);
+    const uint32_t kept = ew_kept(codes, valid, OP);
+    const int from_a = __popc(valid & ~codes);
+    // places in A's share and in C: one scan of both counts (at most 2049 each)
     int tot;
-    int p = block_excl_scan<kEwBlock>(c, &tot, scratch);   // (its barriers end every thread's walk)
-    // the tile's entries of C staged in LDS in order (values over the keys), then written coalesced
-    V *s_oval = reinterpret_cast<V *>(s_key);
+    const int at = block_excl_scan<kEwBlock>(static_cast<int>(__popc(kept)) | from_a << 16, &tot, scratch);
+    int p = at & 0xffff;
+    int i = at >> 16, j = (d < n ? d : n) - i;
+    tot &= 0xffff;
+    if constexpr (OP == kEwAdd) {
+        // every entry's place in C; the B half of a common coordinate: ~(the place of the entry before it, its A half)
 #pragma unroll
-    for (int u = 0; u < kEwPer; ++u) {
-        if (ai[u] >= 0 || bi[u] >= 0) {
-            double v;
-            if (OP == kEwMul) v = av[u] * bv[u];
-            else v = ai[u] >= 0 && bi[u] >= 0 ? av[u] + bv[u] : (ai[u] >= 0 ? av[u] : bv[u]);
-            s_ocol[p] = oc[u];
-            s_oval[p] = static_cast<V>(v);
-            ++p;
+        for (int u = 0; u < kEwPer; ++u) {
+            if (((valid >> (2 * u)) & 1u) == 0u) continue;
+            const bool keep = ((kept >> (2 * u)) & 1u) != 0u, from_b = ((codes >> (2 * u)) & 1u) != 0u;
+            s_place[from_b ? na + j : i] = keep ? p : ~(p - 1);
+            p += keep;
+            i += !from_b;
+            j += from_b;
+        }
+        __syncthreads();
+        int at_c[kEwPer];
+#pragma unroll
+        for (int u = 0; u < kEwPer; ++u) {
+            const int e = threadIdx.x + u * kEwBlock;
+            at_c[u] = e < n ? s_place[e] : -1;
+            if (e < n && at_c[u] >= 0) {
+                s_ocol[at_c[u]] = col[u];
+                s_oval[at_c[u]] = val[u];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kEwPer; ++u) {
+            const int e = threadIdx.x + u * kEwBlock;
+            if (e < n && at_c[u] < 0)   // (a + b in double, rounded once)
+                s_oval[~at_c[u]] = static_cast<V>(to_d(s_oval[~at_c[u]]) + to_d(val[u]));
+        }
+    } else {
+        int32_t oc[kEwPer];
+        double av[kEwPer], bv[kEwPer];
+#pragma unroll
+        for (int u = 0; u < kEwPer; ++u) {
+            const uint32_t c = (codes >> (2 * u)) & 3u;
+            oc[u] = 0;
+            av[u] = 0.0;
+            bv[u] = 0.0;
+            if (((kept >> (2 * u)) & 1u) != 0u) {
+                // A's half of a common coordinate: B's is the next of B's share
+                oc[u] = a_col[ia0 + i];
+                av[u] = to_d(a_val[ia0 + i]);
+                bv[u] = to_d(b_val[ib0 + j]);
+            }
+            i += (c & 1u) ? 0 : 1;
+            j += (c & 1u) ? 1 : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kEwPer; ++u) {
+            if (((kept >> (2 * u)) & 1u) != 0u) {
+                s_ocol[p] = oc[u];
+                s_oval[p] = static_cast<V>(av[u] * bv[u]);
+                ++p;
+            }
         }
     }
     __syncthreads();
-    const int64_t base = tile_off[blockIdx.x];
 #pragma unroll
     for (int u = 0; u < kEwPer; ++u) {
         const int e = threadIdx.x + u * kEwBlock;

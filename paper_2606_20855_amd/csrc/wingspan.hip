@@ -1384,7 +1384,8 @@ void ew_remember(const EwPlanKey &key) {
 }
 
 struct EwLayout {
-    size_t off_dups, off_split_a, off_split_b, off_split_r, off_tile_cnt, off_tile_off, off_partials, total;
+    size_t off_row_at, off_split_a, off_split_b, off_split_r, off_tile_cnt, off_tile_off, off_codes, off_partials,
+        total;
     int64_t ntiles;
 };
 
@@ -1397,7 +1398,7 @@ EwLayout ew_plan(const wingspan_csr *A, const wingspan_csr *B) {
     L.ntiles = ew_tiles(A, B);
     const int64_t nb = L.ntiles + 1;   // boundaries
     size_t off = 0;
-    L.off_dups = off;
+    L.off_row_at = off;
     off += align_up(sizeof(int32_t) * m);
     L.off_split_a = off;
     off += align_up(sizeof(int64_t) * nb);
@@ -1409,6 +1410,8 @@ EwLayout ew_plan(const wingspan_csr *A, const wingspan_csr *B) {
     off += align_up(sizeof(int32_t) * nb);
     L.off_tile_off = off;
     off += align_up(sizeof(int64_t) * (nb + 1));
+    L.off_codes = off;
+    off += align_up(sizeof(uint32_t) * kEwBlock * L.ntiles);
     L.off_partials = off;
     const int64_t n = std::max<int64_t>(m + 1, nb);
     off += align_up(sizeof(int64_t) * ((n + kScanTile - 1) / kScanTile + 2));
@@ -1441,7 +1444,8 @@ wingspan_status ew_workspace(const wingspan_csr *A, const wingspan_csr *B, void 
 
 struct EwTiles {
     int64_t *split_a, *split_b, *tile_off;
-    int32_t *split_r, *tile_cnt, *dups;
+    int32_t *split_r, *tile_cnt, *row_at;
+    uint32_t *codes;
 };
 
 EwTiles ew_arrays(Ctx &c, const EwLayout &L) {
@@ -1451,37 +1455,30 @@ EwTiles ew_arrays(Ctx &c, const EwLayout &L) {
     T.split_r = reinterpret_cast<int32_t *>(c.ws + L.off_split_r);
     T.tile_cnt = reinterpret_cast<int32_t *>(c.ws + L.off_tile_cnt);
     T.tile_off = reinterpret_cast<int64_t *>(c.ws + L.off_tile_off);
-    T.dups = reinterpret_cast<int32_t *>(c.ws + L.off_dups);
+    T.row_at = reinterpret_cast<int32_t *>(c.ws + L.off_row_at);
+    T.codes = reinterpret_cast<uint32_t *>(c.ws + L.off_codes);
     c.partials = reinterpret_cast<int64_t *>(c.ws + L.off_partials);
     return T;
 }
 
-// The tiles' boundaries, then their counts (with PER_ROW also each row's
-// common coordinates, into T.dups, which the caller zeroed). nrows >= 1 and
-// ntiles >= 1.
-template <bool PER_ROW>
+// The tiles' boundaries, then their counts and codes (with `rows` also each
+// row's place in its tile). nrows >= 1 and ntiles >= 1.
 wingspan_status ew_count_tiles(Ctx &c, int op, const wingspan_csr *A, const wingspan_csr *B, const EwLayout &L,
-                               const EwTiles &T) {
+                               const EwTiles &T, bool rows) {
     const int m = static_cast<int>(A->nrows);
     ew_tile_splits<<<blocks_for((L.ntiles + 1) * kWave, 256), 256, 0, c.st>>>(
         A->row_ptr, A->col_idx, B->row_ptr, B->col_idx, m, L.ntiles, T.split_a, T.split_b, T.split_r);
     LAUNCH_CHECK("elementwise splits");
-    ew_tile_count<PER_ROW><<<static_cast<unsigned>(L.ntiles), kEwBlock, 0, c.st>>>(
-        A->row_ptr, A->col_idx, B->row_ptr, B->col_idx, T.split_a, T.split_b, T.split_r, op, T.tile_cnt, T.dups);
+    ew_tile_count<<<static_cast<unsigned>(L.ntiles), kEwBlock, 0, c.st>>>(
+        A->row_ptr, A->col_idx, B->row_ptr, B->col_idx, T.split_a, T.split_b, T.split_r, op, T.tile_cnt, T.codes,
+        rows ? T.row_at : nullptr);
     LAUNCH_CHECK("elementwise count");
     return WINGSPAN_OK;
 }
 
 // Each tile's first place in C, from the tile counts.
 wingspan_status ew_scan_tiles(Ctx &c, const EwLayout &L, const EwTiles &T) {
-    // one workgroup scans a few thousand tile counts, the tiled scan more (measured: 25 us for 16 K counts in
-    // one workgroup)
-    if (L.ntiles <= 2048) {
-        scan_one_block<EwTileIn><<<1, 1024, 0, c.st>>>(EwTileIn{T.tile_cnt}, L.ntiles, T.tile_off, nullptr, nullptr);
-        LAUNCH_CHECK("elementwise tile scan");
-        return WINGSPAN_OK;
-    }
-    return run_scan(c, EwTileIn{T.tile_cnt}, L.ntiles, T.tile_off);
+    return run_scan(c, EwTileIn{T.tile_cnt}, L.ntiles, T.tile_off, true);
 }
 
 // The values; `planned`: the workspace holds this problem's tiling from an earlier call.
@@ -1493,19 +1490,17 @@ wingspan_status ew_values_impl(Ctx &c, int op, const wingspan_csr *A, const wing
     const EwTiles T = ew_arrays(c, L);
     wingspan_status s;
     if (!planned) {
-        if ((s = ew_count_tiles<false>(c, op, A, B, L, T)) != WINGSPAN_OK) return s;
+        if ((s = ew_count_tiles(c, op, A, B, L, T, false)) != WINGSPAN_OK) return s;
         if ((s = ew_scan_tiles(c, L, T)) != WINGSPAN_OK) return s;
     }
     const V *av = static_cast<const V *>(A->val), *bv = static_cast<const V *>(B->val);
     const unsigned grid = static_cast<unsigned>(L.ntiles);
     if (op == WINGSPAN_OP_ADD)
-        ew_tile_write<V, kEwAdd><<<grid, kEwBlock, 0, c.st>>>(A->row_ptr, A->col_idx, av, B->row_ptr, B->col_idx, bv,
-                                                              T.split_a, T.split_b, T.split_r, T.tile_off, c_col,
-                                                              c_val);
+        ew_tile_write<V, kEwAdd><<<grid, kEwBlock, 0, c.st>>>(A->col_idx, av, B->col_idx, bv, T.split_a, T.split_b,
+                                                              T.codes, T.tile_off, c_col, c_val);
     else
-        ew_tile_write<V, kEwMul><<<grid, kEwBlock, 0, c.st>>>(A->row_ptr, A->col_idx, av, B->row_ptr, B->col_idx, bv,
-                                                              T.split_a, T.split_b, T.split_r, T.tile_off, c_col,
-                                                              c_val);
+        ew_tile_write<V, kEwMul><<<grid, kEwBlock, 0, c.st>>>(A->col_idx, av, B->col_idx, bv, T.split_a, T.split_b,
+                                                              T.codes, T.tile_off, c_col, c_val);
     LAUNCH_CHECK("elementwise write");
     return WINGSPAN_OK;
 }
@@ -2125,20 +2120,21 @@ wingspan_status wingspan_elementwise_structure(wingspan_ew_op op, const wingspan
     const int m = static_cast<int>(A->nrows);
     bool planned = false;
     ew_forget(workspace_dev, workspace_bytes);
-    if (m > 0) {
-        fill_i32<<<blocks_for(m, 256), 256, 0, c.st>>>(T.dups, m, 0);
-        LAUNCH_CHECK("elementwise clear");
-        // per-row common coordinates (none when a side is empty), and the tiles' places in C for the values
-        if (A->nnz > 0 && B->nnz > 0) {
-            if ((s = ew_count_tiles<true>(c, op, A, B, L, T)) != WINGSPAN_OK) return s;
-            if ((s = ew_scan_tiles(c, L, T)) != WINGSPAN_OK) return s;
-            planned = true;
-        }
-    }
     c.back.take(c.st);
-    if ((s = run_scan(c, EwCountIn{A->row_ptr, B->row_ptr, T.dups, static_cast<int>(op)}, m, c_row_ptr_dev, true,
-                      nullptr, c.back.to<int64_t>())) != WINGSPAN_OK)
-        return s;
+    int64_t *host_total = c.back.to<int64_t>();
+    if (m > 0 && A->nnz > 0 && B->nnz > 0) {
+        // the tiles, their places in C (for the values, too) and C's row pointer from them
+        if ((s = ew_count_tiles(c, op, A, B, L, T, true)) != WINGSPAN_OK) return s;
+        if ((s = ew_scan_tiles(c, L, T)) != WINGSPAN_OK) return s;
+        ew_row_ptr<<<blocks_for(int64_t(m) + 1, 256), 256, 0, c.st>>>(A->row_ptr, B->row_ptr, m, A->nnz + B->nnz,
+                                                                      L.ntiles, T.tile_off, T.row_at, c_row_ptr_dev,
+                                                                      host_total);
+        planned = true;
+    } else {
+        ew_row_ptr_one_side<<<blocks_for(int64_t(m) + 1, 256), 256, 0, c.st>>>(A->row_ptr, B->row_ptr, m, op,
+                                                                               c_row_ptr_dev, host_total);
+    }
+    LAUNCH_CHECK("elementwise row pointer");
     int64_t total = 0;
     if ((s = read_back(c, &total, c_row_ptr_dev + m, sizeof(int64_t))) != WINGSPAN_OK) return s;
     *c_nnz = total;
