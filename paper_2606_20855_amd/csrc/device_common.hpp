@@ -37,7 +37,8 @@ constexpr int kBinSpill0 = kBinDense0 + kNumClasses;   // 37..52
 constexpr int kNumBins = kBinSpill0 + kNumClasses;     // 53
 constexpr int kMaxBins = 64;
 
-constexpr int kRpParts = 64;
+// workgroups of C.row_ptr's checksum, and its parts: as many as keep the control block's size at ten 256-byte lines
+constexpr int kRpParts = 48;
 
 enum : int32_t {
     kErrProbeExhausted = 1,   // a hash table filled up (structure larger than C.row_ptr says)
@@ -85,6 +86,8 @@ struct Control {
     int64_t stat_annz[kMaxBins];
     int64_t stat_cnnz[kMaxBins];
 };
+
+static_assert(sizeof(Control) <= 2560, "the static scratch's limit counts on it");
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 

@@ -286,12 +286,15 @@ Layout plan(const wingspan_csr *A, const wingspan_csr *B, const Opts &o, size_t 
 // into pinned host memory, so a read-back costs a stream synchronization and no
 // copy (a copy to pageable memory adds about 15 us, in calls that take 100).
 // Calls take a buffer from a pool for their duration and give it back: as many
-// exist as calls have ever run at once. A call that ends before it has waited
-// for its kernels (an error) waits for them before it gives the buffer back.
+// exist as calls have ever run at once, at most kHostBackMax (a call past them
+// copies). A call that ends before it has waited for its kernels (an error)
+// waits for them before it gives the buffer back.
 // ---------------------------------------------------------------------------
 constexpr size_t kHostBackBytes = 16384;
+constexpr int kHostBackMax = 64;
 std::mutex g_back_mu;
 std::vector<char *> g_back_free;
+int g_back_made = 0;
 
 struct HostBack {
     char *p = nullptr;
@@ -316,10 +319,14 @@ struct HostBack {
                 g_back_free.pop_back();
                 return true;
             }
+            if (g_back_made == kHostBackMax) return false;
+            ++g_back_made;
         }
         void *q = nullptr;
         if (hipHostMalloc(&q, kHostBackBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
             (void)hipGetLastError();
+            std::lock_guard<std::mutex> lk(g_back_mu);
+            --g_back_made;
             return false;
         }
         p = static_cast<char *>(q);
