@@ -95,7 +95,9 @@ typedef struct {
                                means 2048 when the structure cache applies (1024 in its
                                symbolic phase if B has at most 262144 columns) and in a
                                single pass whose B has at most 262144 columns, else only
-                               rows too large for the LDS hash tables */
+                               rows too large for the LDS hash tables; with 0 and more
+                               than 262144 columns, rows of few A entries and up to 2048
+                               products per 262144 columns are merged instead */
     int32_t timing;         /* 1: time each tier's kernels with HIP events on `stream`
                                (the call then synchronizes the stream before returning) */
     int32_t wide_offsets;   /* 1: the dense tier forms B's entry offsets in 64 bits even
@@ -262,9 +264,9 @@ wingspan_status wingspan_spgemm_row_products(const wingspan_csr *A, const wingsp
  * beforehand is the sum over rows of min(products of the row, B.ncols)).
  * Nothing is ever written past pool_capacity.
  *
- * Dense rows (beyond the LDS hash tables) take the rank-indexed kernel only
- * when B.ncols <= 262144, where a row's entry count is known before its first
- * write; wider problems send them to the global spill tier.
+ * Dense rows (beyond the LDS hash tables) take the rank-indexed kernel. Where
+ * B.ncols <= 262144 a row's entry count is known before its first write; rows
+ * of wider problems are counted first, region by region.
  * ------------------------------------------------------------------------ */
 wingspan_status wingspan_spgemm_sharded(const wingspan_csr *A, const wingspan_csr *B, wingspan_dtype dtype,
                                         int64_t *row_off_dev, int32_t *row_nnz_dev, int32_t *pool_col_dev,
@@ -369,8 +371,8 @@ wingspan_status wingspan_spmspv(const wingspan_csr *At, wingspan_dtype dtype, co
 /* ------------------------------------------------------------------------
  * Outer-product SpGEMM, C = A B as the sum over k of the rank-1 updates
  * A[:, k] B[k, :] (the paper's outer-product SpGEMM program, Section 5.1,
- * which runs k in parallel and guards C with a merge level: each worker
- * builds its own partial C and a coalesce step recombines them, Section 4.3).
+ * which runs k in parallel and guards C with a merge level; here a bucket of
+ * partial entries per row, which a coalesce step sorts and sums, Section 4.3).
  * The result equals the Gustavson path's C (same structure; values within
  * the rounding of a different summation order).
  *
