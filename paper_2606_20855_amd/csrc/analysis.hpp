@@ -30,11 +30,27 @@ struct CountIn {
     __device__ __forceinline__ int64_t operator()(int64_t i) const { return cnt[i]; }
 };
 
+// Where an input ends that only the device knows (In::end()): past it the
+// tiled scan reads nothing and writes nothing (no total at out[n] either); up
+// to and with it out is written as ever. Other inputs end at n.
+template <typename In>
+__device__ __forceinline__ auto scan_end(const In &in, int64_t, int) -> decltype(in.end()) {
+    return in.end();
+}
+template <typename In>
+__device__ __forceinline__ int64_t scan_end(const In &, int64_t n, long) {
+    return n;
+}
+
 template <typename In>
 __global__ void __launch_bounds__(kScanBlock) scan_tile_sums(In in, int64_t n, int64_t *partials) {
     __shared__ int64_t red[kScanBlock / kWave];
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanTile;
     int64_t s = 0;
+    if (base >= scan_end(in, n, 0)) {
+        if (threadIdx.x == 0) partials[blockIdx.x] = 0;
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         const int64_t idx = base + static_cast<int64_t>(i) * kScanBlock + threadIdx.x;
@@ -96,6 +112,7 @@ __global__ void __launch_bounds__(kScanBlock) scan_tiles(In in, int64_t n, const
                                                          int64_t *host_total) {
     __shared__ int64_t wsum[kScanBlock / kWave];
     int64_t first = 0;
+    if (static_cast<int64_t>(blockIdx.x) * kScanTile > scan_end(in, n, 0)) return;
     if constexpr (OWN) {
         for (int64_t i = threadIdx.x; i < blockIdx.x; i += kScanBlock) first += partials[i];
         first = block_sum<kScanBlock>(first, wsum);

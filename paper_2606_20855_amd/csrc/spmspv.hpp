@@ -153,6 +153,8 @@ constexpr int kSvRangeShift = 12;
 constexpr int kSvRange = 1 << kSvRangeShift;
 constexpr int kSvBin = 4096;
 constexpr int kSvBinBlock = 256;
+// Chunks of P products: tab's and gpos's rows are this long, a row per range.
+__device__ __forceinline__ int64_t sv_chunks(int64_t P) { return (P + kSvBin - 1) / kSvBin; }
 constexpr int kSvBinPer = kSvBin / kSvBinBlock;
 constexpr int kSvBinStage = 2048;     // x entries a binning chunk stages in LDS
 constexpr int kSvMaxRanges = 2048;    // y of at most 8 M positions takes the bucketed scatter
@@ -201,7 +203,7 @@ __global__ void __launch_bounds__(kSvBinBlock) sv_bin(const int32_t *__restrict_
                                                       const int32_t *__restrict__ x_idx,
                                                       const V *__restrict__ x_val, int nnz_x,
                                                       const int64_t *__restrict__ pref, const int32_t *err,
-                                                      int nranges, int64_t nc, int32_t *__restrict__ tab,
+                                                      int nranges, int32_t *__restrict__ tab,
                                                       int32_t *__restrict__ tmp_row, double *__restrict__ tmp_val) {
     __shared__ int32_t s_cnt[kSvMaxRanges + 1];
     __shared__ int32_t s_own[kSvBin];   // each product's x entry (relative to the chunk's first)
@@ -214,7 +216,7 @@ __global__ void __launch_bounds__(kSvBinBlock) sv_bin(const int32_t *__restrict_
     int32_t *s_row = reinterpret_cast<int32_t *>(s_mem);
     double *s_val = reinterpret_cast<double *>(s_mem + kSvBin * sizeof(int32_t));
     if (*err != 0) return;   // whole grid
-    const int64_t P = pref[nnz_x];
+    const int64_t P = pref[nnz_x], nc = sv_chunks(P);
     // chunks taken grid-stride: the grid is sized for the most products x could select
     for (int64_t c = blockIdx.x; c * kSvBin < P; c += gridDim.x) {
     const int64_t q0 = c * kSvBin;
@@ -370,17 +372,17 @@ __global__ void __launch_bounds__(kSvBinBlock) sv_bin(const int32_t *__restrict_
     }
 }
 
-// tab read in range-major order for the scan; chunks past the product count
-// (the grid is sized by At's entries) count nothing.
+// tab in range-major order for the scan, which is sized by At's entries: it
+// ends with the chunks there are (x 10% stored on R-MAT 20: 101 K counts of 1 M;
+// with places for every chunk there could be, its two launches took 15 us, now
+// 10.7; the call 133 and 138 us in two comparisons, now 131 and 130).
 struct SvTabIn {
     const int32_t *tab;
     const int64_t *pref;
-    int nnz_x;
-    int64_t nc;
-    __device__ __forceinline__ int64_t operator()(int64_t i) const {
-        const int64_t c = i % nc;
-        return c * kSvBin < pref[nnz_x] ? tab[i] : 0;
-    }
+    int nnz_x, nranges;
+    int64_t most;   // chunks at most (an x refused for its order may count more products than At has entries)
+    __device__ __forceinline__ int64_t end() const { return nranges * min(sv_chunks(pref[nnz_x]), most); }
+    __device__ __forceinline__ int64_t operator()(int64_t i) const { return i < end() ? tab[i] : 0; }
 };
 
 // Chunk c's runs to their places in the range-sorted order: entry e of the
@@ -389,7 +391,7 @@ struct SvTabIn {
 __global__ void __launch_bounds__(kSvBinBlock) sv_place(const int32_t *__restrict__ tmp_row,
                                                         const double *__restrict__ tmp_val,
                                                         const int64_t *__restrict__ pref, int nnz_x,
-                                                        const int32_t *err, int nranges, int64_t nc,
+                                                        const int32_t *err, int nranges,
                                                         const int32_t *__restrict__ tab,
                                                         const int64_t *__restrict__ gpos,
                                                         int32_t *__restrict__ s_row_out,
@@ -397,7 +399,7 @@ __global__ void __launch_bounds__(kSvBinBlock) sv_place(const int32_t *__restric
     __shared__ int64_t s_dst[kSvMaxRanges];   // gpos of each range's run minus its first entry in the chunk
     __shared__ int32_t scratch[kSvBinBlock / kWave];
     if (*err != 0) return;
-    const int64_t P = pref[nnz_x];
+    const int64_t P = pref[nnz_x], nc = sv_chunks(P);
     for (int64_t c = blockIdx.x; c * kSvBin < P; c += gridDim.x) {
     const int64_t q0 = c * kSvBin;
     const int n = static_cast<int>(P - q0 < kSvBin ? P - q0 : kSvBin);
@@ -436,9 +438,11 @@ struct SvRangeStart {
 
 // The pieces of range r: its sorted products cut into runs of kSvPieceMax.
 struct SvPiecesIn {
-    const int64_t *gpos;
-    int64_t nc;
+    const int64_t *gpos, *pref;
+    int nnz_x;
+    int64_t most;   // chunks at most
     __device__ __forceinline__ int64_t operator()(int64_t r) const {
+        const int64_t nc = min(sv_chunks(pref[nnz_x]), most);
         const int64_t len = gpos[(r + 1) * nc] - gpos[r * nc];
         return (len + kSvPieceMax - 1) / kSvPieceMax;
     }
@@ -450,7 +454,8 @@ struct SvPiecesIn {
 // atomics; the flags set. yval and the flags start at zero.
 __global__ void __launch_bounds__(kSvAccBlock) sv_accumulate(const int32_t *__restrict__ s_row_in,
                                                              const double *__restrict__ s_val_in,
-                                                             const int32_t *err, int nranges, int64_t nc,
+                                                             const int32_t *err, int nranges,
+                                                             const int64_t *__restrict__ pref, int nnz_x,
                                                              const int64_t *__restrict__ gpos,
                                                              const int64_t *__restrict__ piece_pre,
                                                              uint8_t *__restrict__ flag, double *__restrict__ yval) {
@@ -463,7 +468,7 @@ __global__ void __launch_bounds__(kSvAccBlock) sv_accumulate(const int32_t *__re
         acc[t] = 0.0;
         touched[t] = 0;
     }
-    const SvRangeStart rs{gpos, nc};
+    const SvRangeStart rs{gpos, sv_chunks(pref[nnz_x])};
     for (int64_t g = blockIdx.x; g < npieces; g += gridDim.x) {
         if (threadIdx.x < kWave) {
             // the range holding piece g (a range without pieces starts where the next one does)

@@ -1621,18 +1621,19 @@ wingspan_status sv_impl(Ctx &c, const wingspan_csr *At, const SvLayout &L, const
             double *srt_val = reinterpret_cast<double *>(c.ws + L.off_srt_val);
             const unsigned grid = static_cast<unsigned>(std::min<int64_t>(nc, kSvBucketGrid));
             sv_bin<V><<<grid, kSvBinBlock, 0, c.st>>>(At->row_ptr, At->col_idx, static_cast<const V *>(At->val),
-                                                      x_idx, x_val, static_cast<int>(nnz_x), pref, err, nr, nc, tab,
+                                                      x_idx, x_val, static_cast<int>(nnz_x), pref, err, nr, tab,
                                                       tmp_row, tmp_val);
             LAUNCH_CHECK("spmspv bin");
-            if ((s = run_scan(c, SvTabIn{tab, pref, static_cast<int>(nnz_x), nc}, nr * nc, gpos)) != WINGSPAN_OK)
+            if ((s = run_scan(c, SvTabIn{tab, pref, static_cast<int>(nnz_x), nr, nc}, nr * nc, gpos)) != WINGSPAN_OK)
                 return s;
-            sv_place<<<grid, kSvBinBlock, 0, c.st>>>(tmp_row, tmp_val, pref, static_cast<int>(nnz_x), err, nr, nc,
-                                                     tab, gpos, srt_row, srt_val);
+            sv_place<<<grid, kSvBinBlock, 0, c.st>>>(tmp_row, tmp_val, pref, static_cast<int>(nnz_x), err, nr, tab,
+                                                     gpos, srt_row, srt_val);
             int64_t *piece_pre = reinterpret_cast<int64_t *>(c.ws + L.off_piece_pre);
-            scan_one_block<SvPiecesIn><<<1, 1024, 0, c.st>>>(SvPiecesIn{gpos, nc}, nr, piece_pre, nullptr, nullptr);
+            const SvPiecesIn per_range{gpos, pref, static_cast<int>(nnz_x), nc};
+            scan_one_block<SvPiecesIn><<<1, 1024, 0, c.st>>>(per_range, nr, piece_pre, nullptr, nullptr);
             const int64_t pieces = nr + (At->nnz + kSvPieceMax - 1) / kSvPieceMax;   // at most
             sv_accumulate<<<static_cast<unsigned>(std::min<int64_t>(pieces, kSvBucketGrid)), kSvAccBlock, 0, c.st>>>(
-                srt_row, srt_val, err, nr, nc, gpos, piece_pre, flag, yval);
+                srt_row, srt_val, err, nr, pref, static_cast<int>(nnz_x), gpos, piece_pre, flag, yval);
             LAUNCH_CHECK("spmspv accumulate");
         } else if (At->nnz > 0) {
             const int64_t chunks = (At->nnz + kSvChunk - 1) / kSvChunk;
