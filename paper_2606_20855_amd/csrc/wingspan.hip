@@ -636,6 +636,9 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
     // after a symbolic phase in the same call row_prod holds the counts, unless the dense rows' descriptions of the
     // kept binning took its place
     if (c.L.cache_rows > 0) have_pref = false;
+    // the arrays below are written over what a symbolic phase kept in this workspace, whatever layout its stamp
+    // names: the stamp is cleared unless it is this call's own
+    bool stale = true;
     uint64_t rp_sum = 0;
     if (numeric && c.L.cache_rows > 0) {
         // The symbolic phase on the same workspace may have binned the rows by this C.row_ptr already: check
@@ -660,8 +663,8 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
         c.host.rp_sum = rp_sum;
         const BinCfg cfg = numeric_bin_cfg(c, B);
         const Stamp &h = c.host_stamp;
-        const bool match = stamp_matches(c, A, B) && h.num_bins == 1;
-        if (match && !c.o.validate && h.nb_dense_min_nnz == cfg.dense_min_nnz && h.nb_tiny_max == cfg.tiny_max &&
+        stale = !stamp_matches(c, A, B);
+        if (!stale && h.num_bins == 1 && !c.o.validate && h.nb_dense_min_nnz == cfg.dense_min_nnz && h.nb_tiny_max == cfg.tiny_max &&
             h.nb_hash_log2_max == cfg.hash_log2_max && h.nb_force_spill == cfg.force_spill &&
             h.nb_dense_ok == cfg.dense_ok && h.nb_merge_runs == cfg.merge_runs &&
             h.nb_merge_places == cfg.merge_places && h.nb_merge_over_dense == cfg.merge_over_dense &&
@@ -680,7 +683,7 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
             return WINGSPAN_OK;
         }
         // not kept for this call: bin here, over the kept descriptions of the dense rows
-        if (h.num_bins == 1) {
+        if (!stale && h.num_bins == 1) {
             drop_kept_bins<<<1, 1, 0, c.st>>>(c.stamp);
             LAUNCH_CHECK("stamp");
         }
@@ -705,11 +708,11 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
             return fail(WINGSPAN_ERR_INVALID_MATRIX, "A or B is not canonical CSR");
     }
     if (!have_pref) {
-        // the lengths' prefixes; in the symbolic phase and the single pass the structure cache (and what the
-        // symbolic phase keeps for the numeric one) is being rewritten: invalid until a symbolic phase completes
+        // the lengths' prefixes, and the stamp cleared: in the symbolic phase and the single pass the structure cache
+        // (and what the symbolic phase keeps for the numeric one) is invalid until a symbolic phase completes
         brow_tile_prefix<<<blocks_for(std::max<int64_t>(A->nnz, 1), kScanTile), kScanBlock, 0, c.st>>>(
             A->col_idx, B->row_ptr, A->nnz, c.loc, c.partials, reinterpret_cast<int32_t *>(c.ctrl),
-            numeric ? nullptr : reinterpret_cast<int32_t *>(c.ctrl_num), words, numeric ? nullptr : c.stamp);
+            numeric ? nullptr : reinterpret_cast<int32_t *>(c.ctrl_num), words, stale ? c.stamp : nullptr);
         LAUNCH_CHECK("row products");
     }
     if (numeric && c.dtype_f64 >= 0 && !c.L.rank_mode) {

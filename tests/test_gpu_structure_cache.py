@@ -221,3 +221,38 @@ def test_cache_budget_bounds_the_cached_rows(cache_mib, cached):
     assert num["rows"]["dense"] == 64
     assert num["structure_cache_rows"] == cached
     assert_matches(got, oracle.spgemm(A, B), A.val.dtype, what=f"cache budget {cache_mib} MiB")
+
+
+@pytest.mark.parametrize("between", [dict(cache_mib=-1), dict(dense_min_nnz=-1), dict(window_cols=1024),
+                                     dict(cache_mib=-1, validate=1), "other matrices"])
+def test_numeric_of_another_layout_between(between):
+    # a numeric call writes its rows' counts, bins and window table over what the symbolic phase kept, at its own
+    # layout's places, whether or not that layout has a cache: the kept state is gone for the call after it. Rows of
+    # 2048 to 5461 entries: dense with the cache, in the LDS tiers without (so that only the binning writes there)
+    import torch
+    from paper_2606_20855_amd import wingspan as ws
+    A = matgen.er(150, 3000, 60, seed=71, dtype=np.float32, dist="open01")
+    B = matgen.er(3000, 20_000, 60, seed=72, dtype=np.float32, dist="open01")
+    A2 = matgen.er(400, 3000, 50, seed=73, dtype=np.float32, dist="open01")
+    opts2 = {} if between == "other matrices" else between
+    dA, dB, d2 = _dev(A), _dev(B), _dev(A2)
+    nbytes = max(ws.wingspan_spgemm_workspace_size(d.desc(), dB.desc(), d.dtype_code, ws.make_options(**o))
+                 for d in (dA, d2) for o in ({}, opts2))
+    wsb = torch.zeros(nbytes, dtype=torch.uint8, device="cuda:0")
+    ref = oracle.spgemm(A, B)
+    count = np.diff(ref.row_ptr)
+    assert count.min() >= 2048 and count.max() <= 5461
+    c_rp, nnz = _symbolic(dA, dB, wsb, nbytes, {})
+    if between == "other matrices":
+        other, _ = _workspace(d2, dB, {})
+        rp2, nnz2 = _symbolic(d2, dB, other, other.numel(), {})
+        got, num = _numeric(d2, dB, rp2, nnz2, wsb, nbytes, {})
+        assert_matches(got, oracle.spgemm(A2, B), A2.val.dtype, what="between")
+    else:
+        got, num = _numeric(dA, dB, c_rp, nnz, wsb, nbytes, between)
+        assert_matches(got, ref, A.val.dtype, what="between")
+    assert num["structure_cache_rows"] == 0
+    for _ in range(2):
+        got, num = _numeric(dA, dB, c_rp, nnz, wsb, nbytes, {})
+        assert num["rows"]["dense"] == 150 and num["structure_cache_rows"] == 0
+        assert_matches(got, ref, A.val.dtype, what=f"after {between}")
