@@ -171,7 +171,11 @@ wingspan_status wingspan_spgemm_symbolic(const wingspan_csr *A, const wingspan_c
  * numeric call on the same workspace whose A, B, layout and c_row_ptr_dev
  * match the stamp takes those column sets instead of recomputing them (it
  * then reads B's column indices once per product instead of twice); any other
- * call recomputes them. Calls that change A's or B's pattern in place must run
+ * call recomputes them, and a call of this library that is given the same
+ * workspace for other work ends the stamp. What the caller itself writes into
+ * the workspace between the two phases (or has written by calls that are given
+ * other parts of it) is not noticed: run the symbolic phase again after that.
+ * Calls that change A's or B's pattern in place must run
  * the symbolic phase again, as C.row_ptr itself requires. */
 wingspan_status wingspan_spgemm_numeric(const wingspan_csr *A, const wingspan_csr *B,
                                         wingspan_dtype dtype, const int64_t *c_row_ptr_dev,

@@ -670,6 +670,11 @@ __global__ void __launch_bounds__(1024) rowptr_checksum(const int64_t *__restric
     }
 }
 
+// Ends the stamp of another problem or layout (one thread).
+__global__ void clear_stamp_unless(Stamp *stamp, const Stamp own) {
+    if (threadIdx.x == 0 && blockIdx.x == 0 && !stamp->same_problem(own)) stamp->magic = 0;
+}
+
 // The numeric binning the stamp describes is no longer what the workspace
 // holds (one thread).
 __global__ void drop_kept_bins(Stamp *stamp) {

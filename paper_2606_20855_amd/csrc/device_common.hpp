@@ -50,7 +50,9 @@ enum : int32_t {
 // numeric phase: the column sets (bitmaps) of dense rows. It names the inputs
 // and the layout it was made for and a checksum of C.row_ptr; the numeric
 // phase uses the bitmaps only if all of them match its own call. magic is 0
-// while a symbolic phase is running or after it failed.
+// while a symbolic phase is running or after it failed, and once a call has
+// written over the kept state: every entry point leaves a stamp at the start of
+// its workspace only if it is the stamp's own numeric phase or writes elsewhere.
 struct Stamp {
     uint64_t magic;
     uint64_t a_rp, a_col, b_rp, b_col;
@@ -65,6 +67,14 @@ struct Stamp {
     int64_t nb_dense_min_nnz;
     int32_t nb_tiny_max, nb_hash_log2_max, nb_force_spill, nb_dense_ok, nb_merge_runs, nb_merge_places,
         nb_merge_over_dense, nb_merge_long;
+
+    // the same inputs and layout
+    __host__ __device__ bool same_problem(const Stamp &t) const {
+        return a_rp == t.a_rp && a_col == t.a_col && b_rp == t.b_rp && b_col == t.b_col && a_nrows == t.a_nrows &&
+               a_ncols == t.a_ncols && a_nnz == t.a_nnz && b_nrows == t.b_nrows && b_ncols == t.b_ncols &&
+               b_nnz == t.b_nnz && off_slot == t.off_slot && off_cache == t.off_cache && row_words == t.row_words &&
+               cache_rows == t.cache_rows;
+    }
 };
 constexpr uint64_t kStampMagic = 0x57535f5354525543ull;
 

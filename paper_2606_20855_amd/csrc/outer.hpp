@@ -90,11 +90,14 @@ __device__ __forceinline__ int block_excl_scan(int x, int *scratch, int *total) 
     return before + incl - x;
 }
 
-// Clears the rows' entry counts and the coalesce's counters.
-__global__ void __launch_bounds__(256) op_clear(int32_t *__restrict__ row_cnt, int64_t m, int32_t *counters) {
+// Clears the rows' entry counts, the coalesce's counters and the product
+// prefix's first word (0 already, unless At has no rows).
+__global__ void __launch_bounds__(256) op_clear(int32_t *__restrict__ row_cnt, int64_t m, int32_t *counters,
+                                                int64_t *pref) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < m) row_cnt[i] = 0;
     if (i < 4) counters[i] = 0;
+    if (i == 0) pref[0] = 0;
 }
 
 // 1. Entry e of At, of index k, claims |B_k| places of its row's bucket:

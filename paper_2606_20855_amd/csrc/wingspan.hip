@@ -501,12 +501,7 @@ void stamp_bins(Stamp &t, const BinCfg &cfg, bool wtab) {
 bool stamp_matches(const Ctx &c, const wingspan_csr *A, const wingspan_csr *B) {
     if (c.L.cache_rows <= 0) return false;
     const Stamp &h = c.host_stamp;
-    const Stamp t = make_stamp(c, A, B);
-    return h.magic == kStampMagic && h.a_rp == t.a_rp && h.a_col == t.a_col && h.b_rp == t.b_rp &&
-           h.b_col == t.b_col && h.a_nrows == t.a_nrows && h.a_ncols == t.a_ncols && h.a_nnz == t.a_nnz &&
-           h.b_nrows == t.b_nrows && h.b_ncols == t.b_ncols && h.b_nnz == t.b_nnz && h.off_slot == t.off_slot &&
-           h.off_cache == t.off_cache && h.row_words == t.row_words && h.cache_rows == t.cache_rows &&
-           h.rp_sum == c.host.rp_sum;
+    return h.magic == kStampMagic && h.same_problem(make_stamp(c, A, B)) && h.rp_sum == c.host.rp_sum;
 }
 
 // HIP events for optional per-tier timing, created once per thread.
@@ -1394,7 +1389,7 @@ void ew_remember(const EwPlanKey &key) {
 }
 
 struct EwLayout {
-    size_t off_row_at, off_split_a, off_split_b, off_split_r, off_tile_cnt, off_tile_off, off_codes, off_partials,
+    size_t off_split_a, off_row_at, off_split_b, off_split_r, off_tile_cnt, off_tile_off, off_codes, off_partials,
         total;
     int64_t ntiles;
 };
@@ -1408,10 +1403,10 @@ EwLayout ew_plan(const wingspan_csr *A, const wingspan_csr *B) {
     L.ntiles = ew_tiles(A, B);
     const int64_t nb = L.ntiles + 1;   // boundaries
     size_t off = 0;
+    L.off_split_a = off;   // first: its first word, always 0, ends a stamp that a symbolic phase left here
+    off += align_up(sizeof(int64_t) * nb);
     L.off_row_at = off;
     off += align_up(sizeof(int32_t) * m);
-    L.off_split_a = off;
-    off += align_up(sizeof(int64_t) * nb);
     L.off_split_b = off;
     off += align_up(sizeof(int64_t) * nb);
     L.off_split_r = off;
@@ -1536,7 +1531,7 @@ SvLayout sv_plan(const wingspan_csr *At, int64_t nnz_x) {
     const int64_t m = std::max<int64_t>(At->ncols, 1), nx = std::max<int64_t>(nnz_x, 0);
     L.ntiles = (m + kSvTile - 1) / kSvTile;
     size_t off = 0;
-    // first the tiles' prefix, its total (y's entry count) last, then the error word: the total and the error
+    // first the tiles' prefix (whose first word, always 0, ends a stamp that a symbolic phase left here), its total (y's entry count) last, then the error word: the total and the error
     // word are read back in one copy. (Measured: the scatter runs about 20% slower with these small arrays
     // placed just past the map's accumulators.)
     L.off_tile_pre = off;
@@ -1677,7 +1672,7 @@ constexpr int64_t kOpLongGrid = 2048;   // coalesce workgroups for long rows at 
 constexpr int64_t kOpHugeGrid = 512;    // the same for rows past kOpRowCap (one or two workgroups per CU)
 
 struct OpLayout {
-    size_t off_ctr, off_pref, off_partials, off_part_key, off_part_val, off_place, off_row_cnt,
+    size_t off_pref, off_ctr, off_partials, off_part_key, off_part_val, off_place, off_row_cnt,
         off_bucket, off_row_nnz, off_long, off_bkt_col, off_bkt_val, off_out_val, total;
 };
 
@@ -1686,10 +1681,10 @@ OpLayout op_plan(const wingspan_csr *At, const wingspan_csr *B, int64_t P) {
     const int64_t K = std::max<int64_t>(At->nrows, 1), m = std::max<int64_t>(At->ncols, 1);
     const int64_t p = std::max<int64_t>(P, 1);
     size_t off = 0;
+    L.off_pref = off;   // first: its first word, always 0, ends a stamp that a symbolic phase left here
+    off += align_up(sizeof(int64_t) * (K + 1));
     L.off_ctr = off;
     off += align_up(sizeof(int32_t) * 4);
-    L.off_pref = off;
-    off += align_up(sizeof(int64_t) * (K + 1));
     L.off_partials = off;
     const int64_t n = std::max<int64_t>(K, m) + 1;
     off += align_up(sizeof(int64_t) * ((n + kScanTile - 1) / kScanTile + 2));
@@ -1755,7 +1750,7 @@ wingspan_status op_impl(Ctx &c, const wingspan_csr *At, const wingspan_csr *B, c
     const int64_t K = At->nrows, m = At->ncols;
     auto at = [&](size_t off) { return c.ws + off; };
     int32_t *ctr = reinterpret_cast<int32_t *>(at(L.off_ctr));
-    const int64_t *pref = reinterpret_cast<const int64_t *>(at(L.off_pref));
+    int64_t *pref = reinterpret_cast<int64_t *>(at(L.off_pref));
     int64_t *part_key = reinterpret_cast<int64_t *>(at(L.off_part_key));
     double *part_val = reinterpret_cast<double *>(at(L.off_part_val));
     int32_t *place = reinterpret_cast<int32_t *>(at(L.off_place));
@@ -1773,7 +1768,7 @@ wingspan_status op_impl(Ctx &c, const wingspan_csr *At, const wingspan_csr *B, c
         LAUNCH_CHECK("outer empty");
         return WINGSPAN_OK;
     }
-    op_clear<<<blocks_for(std::max<int64_t>(m, 4), 256), 256, 0, c.st>>>(row_cnt, m, ctr);
+    op_clear<<<blocks_for(std::max<int64_t>(m, 4), 256), 256, 0, c.st>>>(row_cnt, m, ctr, pref);
     LAUNCH_CHECK("outer clear");
     // 1. every entry of At claims its places of its row's bucket
     if (P > 0) {
@@ -2015,6 +2010,8 @@ wingspan_status wingspan_spgemm_row_products(const wingspan_csr *A, const wingsp
     Ctx c{};
     if ((s = setup(c, A, B, nullptr, workspace_dev, workspace_bytes, stream)) != WINGSPAN_OK) return s;
     if (A->nrows == 0) return WINGSPAN_OK;
+    // the arrays below belong to no kept state of this problem and layout, but to any part of another's
+    clear_stamp_unless<<<1, 1, 0, c.st>>>(c.stamp, make_stamp(c, A, B));
     // the analysis pass of both phases: B-row lengths scanned over A's entries, then per-row differences
     brow_tile_prefix<<<blocks_for(std::max<int64_t>(A->nnz, 1), kScanTile), kScanBlock, 0, c.st>>>(
         A->col_idx, B->row_ptr, A->nnz, c.loc, c.partials, nullptr, nullptr, 0, nullptr);

@@ -256,3 +256,70 @@ def test_numeric_of_another_layout_between(between):
         got, num = _numeric(dA, dB, c_rp, nnz, wsb, nbytes, {})
         assert num["rows"]["dense"] == 150 and num["structure_cache_rows"] == 0
         assert_matches(got, ref, A.val.dtype, what=f"after {between}")
+
+
+@pytest.mark.parametrize("between", ["row_products", "row_products_other", "ew_structure", "ew_values", "outer_products",
+                                     "outer", "outer_empty", "spmspv", "sharded_to_csr"])
+def test_other_calls_between_the_phases(between):
+    # every entry point that is handed the workspace ends the kept state it writes over, also where its own arrays
+    # are small (few rows) or it runs without the call that usually comes first
+    import torch
+    from paper_2606_20855_amd import wingspan as ws
+    A = matgen.rmat(11, 16, seed=65, dtype=np.float32)
+    dA = _dev(A)
+    ref = oracle.spgemm(A, A)
+    wsb, nbytes = _workspace(dA, dA, DENSE)
+    c_rp, nnz = _symbolic(dA, dA, wsb, nbytes, DENSE)
+    # a short wide pair: 30 rows of 400 entries each
+    X = matgen.er(30, 100_000, 400, seed=66, dtype=np.float32, dist="open01")
+    Y = matgen.er(30, 100_000, 400, seed=67, dtype=np.float32, dist="open01")
+    dX, dY = _dev(X), _dev(Y)
+    p, h = wsb.data_ptr(), torch.cuda.current_stream().cuda_stream
+    out = torch.empty(1 << 20, dtype=torch.int64, device="cuda:0")
+    if between == "row_products":
+        ws.wingspan_spgemm_row_products(dA.desc(), dA.desc(), out.data_ptr(), p, nbytes, h)
+        assert np.array_equal(out[:A.nrows].cpu().numpy(), oracle.row_products(A, A))
+    elif between == "row_products_other":
+        E = matgen.er(600, A.nrows, 40, seed=68, dtype=np.float32, dist="open01")
+        dE = _dev(E)
+        need = ws.wingspan_spgemm_workspace_size(dE.desc(), dA.desc(), dE.dtype_code)
+        assert need <= nbytes
+        ws.wingspan_spgemm_row_products(dE.desc(), dA.desc(), out.data_ptr(), p, nbytes, h)
+    elif between in ("ew_structure", "ew_values"):
+        own = torch.empty(nbytes, dtype=torch.uint8, device="cuda:0")
+        first = wsb if between == "ew_structure" else own
+        rp = torch.empty(31, dtype=torch.int64, device="cuda:0")
+        n = ws.wingspan_elementwise_structure(ws.OP_ADD, dX.desc(), dY.desc(), rp.data_ptr(), first.data_ptr(),
+                                              nbytes, h)
+        col = torch.empty(n, dtype=torch.int32, device="cuda:0")
+        val = torch.empty(n, dtype=torch.float32, device="cuda:0")
+        if between == "ew_values":
+            ws.wingspan_elementwise_values(ws.OP_ADD, dX.desc(), dY.desc(), dX.dtype_code, rp.data_ptr(),
+                                           col.data_ptr(), val.data_ptr(), p, nbytes, h)
+    elif between == "outer_products":
+        P = ws.wingspan_outer_products(dX.desc(), dY.desc(), p, nbytes, h)
+        assert P == 30 * 400 * 400
+    elif between in ("outer", "outer_empty"):
+        T = matgen.random_sparse(0 if between == "outer_empty" else 20, 50, 0.3, 69, np.float32)
+        dT = _dev(T)
+        P = 0 if T.nrows == 0 else ws.wingspan_outer_products(dT.desc(), dT.desc(), out.data_ptr(), out.numel() * 8, h)
+        col = torch.empty(max(P, 1), dtype=torch.int32, device="cuda:0")
+        val = torch.empty(max(P, 1), dtype=torch.float32, device="cuda:0")
+        ws.wingspan_spgemm_outer(dT.desc(), dT.desc(), dT.dtype_code, out.data_ptr(), col.data_ptr(), val.data_ptr(),
+                                 max(P, 1), p, nbytes, h)
+    elif between == "spmspv":
+        xi = torch.arange(0, 30, 3, dtype=torch.int32, device="cuda:0")
+        xv = torch.ones(10, dtype=torch.float32, device="cuda:0")
+        yv = torch.empty(100_000, dtype=torch.float32, device="cuda:0")
+        ws.wingspan_spmspv(dX.desc(), dX.dtype_code, xi.data_ptr(), xv.data_ptr(), 10, out.data_ptr(), yv.data_ptr(),
+                           100_000, p, nbytes, h)
+    else:
+        S = ws.spgemm_sharded(dX, _dev(matgen.er(100_000, 50, 2, seed=70, dtype=np.float32, dist="open01")))
+        ws.wingspan_sharded_to_csr(30, S.nnz, S.row_off.data_ptr(), S.row_nnz.data_ptr(), S.pool_col.data_ptr(),
+                                   S.pool_val.data_ptr(), dX.dtype_code, out.data_ptr(), out[100:].data_ptr(),
+                                   out[1 << 19:].data_ptr(), p, nbytes, h)
+    got, num = _numeric(dA, dA, c_rp, nnz, wsb, nbytes, DENSE)
+    assert num["rows"]["dense"] > 0
+    # (one tile of rows is scanned without writing to the workspace)
+    assert (num["structure_cache_rows"] > 0) == (between in ("row_products", "sharded_to_csr"))
+    assert_matches(got, ref, A.val.dtype, what=f"after {between}")
