@@ -1316,7 +1316,7 @@ wingspan_status finish_timing(int phase) {
 }
 
 wingspan_status setup(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, const wingspan_options *opt,
-                      void *ws, size_t ws_bytes, void *stream, size_t budget = 0) {
+                      void *ws, size_t ws_bytes, void *stream, size_t budget = 0, bool reads_back = true) {
     wingspan_status s = parse_opts(opt, &c.o);
     if (s != WINGSPAN_OK) return s;
     c.L = plan(A, B, c.o, budget);
@@ -1328,7 +1328,8 @@ wingspan_status setup(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, cons
     c.st = static_cast<hipStream_t>(stream);
     c.nrows_a = A->nrows;
     carve(c, ws);
-    if (budget == 0) c.back.take(c.st);   // (not for the entry point that allocates nothing)
+    // (not for the entry point that allocates nothing, nor for one that never waits and may be captured)
+    if (budget == 0 && reads_back) c.back.take(c.st);
     if (!c.o.dense_min_explicit && c.L.cache_rows > 0) c.o.dense_min_nnz = kCachedDenseMin;
     return WINGSPAN_OK;
 }
@@ -2008,7 +2009,7 @@ wingspan_status wingspan_spgemm_row_products(const wingspan_csr *A, const wingsp
     if (s != WINGSPAN_OK) return s;
     if (A->nrows > 0 && !row_products_dev) return fail(WINGSPAN_ERR_INVALID_ARGUMENT, "row_products_dev is NULL");
     Ctx c{};
-    if ((s = setup(c, A, B, nullptr, workspace_dev, workspace_bytes, stream)) != WINGSPAN_OK) return s;
+    if ((s = setup(c, A, B, nullptr, workspace_dev, workspace_bytes, stream, 0, false)) != WINGSPAN_OK) return s;
     if (A->nrows == 0) return WINGSPAN_OK;
     // the arrays below belong to no kept state of this problem and layout, but to any part of another's
     clear_stamp_unless<<<1, 1, 0, c.st>>>(c.stamp, make_stamp(c, A, B));
