@@ -2011,13 +2011,11 @@ wingspan_status wingspan_spgemm_row_products(const wingspan_csr *A, const wingsp
     Ctx c{};
     if ((s = setup(c, A, B, nullptr, workspace_dev, workspace_bytes, stream, 0, false)) != WINGSPAN_OK) return s;
     if (A->nrows == 0) return WINGSPAN_OK;
-    // the arrays below belong to no kept state of this problem and layout, but to any part of another's
-    clear_stamp_unless<<<1, 1, 0, c.st>>>(c.stamp, make_stamp(c, A, B));
     // the analysis pass of both phases: B-row lengths scanned over A's entries, then per-row differences
     brow_tile_prefix<<<blocks_for(std::max<int64_t>(A->nnz, 1), kScanTile), kScanBlock, 0, c.st>>>(
         A->col_idx, B->row_ptr, A->nnz, c.loc, c.partials, nullptr, nullptr, 0, nullptr);
     row_products_kernel<<<blocks_for(A->nrows, 256), 256, 0, c.st>>>(A->row_ptr, A->nnz, c.loc, c.partials, A->nrows,
-                                                                     row_products_dev);
+                                                                     row_products_dev, c.stamp, make_stamp(c, A, B));
     LAUNCH_CHECK("row products");
     return WINGSPAN_OK;
 }

@@ -25,9 +25,11 @@ def _a(lens, k, seed):
 
 @pytest.mark.parametrize("lens", [
     [2048], [2048, 2048], [0, 2047, 1, 0, 2048, 0], [2049], [1, 2047, 2048, 0], [5000, 0, 1192], [100, 9000, 0, 3],
-    [0, 0, 0], [1], [4096, 4096, 1]], ids=str)
+    [0, 0, 0], [1], [4096, 4096, 1],
+    # rows of 16 and 17 tiles and more, several in a wave and in one of its lanes' rows that follow no other
+    [32767, 1, 34816, 34817, 0, 5, 40000], [1] * 63 + [39999] + [2] * 64 + [35000, 0, 36000]], ids=str)
 def test_row_products_around_tiles(lens):
-    B = matgen.er(10_000, 50, 1, seed=2)
+    B = matgen.er(40_000, 50, 1, seed=2)
     keep = np.random.default_rng(3).random(B.nrows) < 0.5   # half of B's rows are empty
     bp = np.concatenate([[0], np.cumsum(keep)]).astype(np.int32)
     B = matgen.CSR(B.nrows, 50, bp, B.col_idx[keep], B.val[keep])
@@ -58,6 +60,44 @@ def test_row_counts(m, opts):
     assert np.array_equal(got.row_ptr, rp) and np.array_equal(got.col_idx, 3 * ci)
     assert np.all(got.val == 0.5)
     assert num["rows"]["tiny"] == int(np.sum(lens > 0)) and num["c_nnz_total"] == rp[-1]
+
+
+def _rows_of_one_entry_each(rows, per):
+    """A of `rows` full rows of `per` entries, B of `per` rows of one entry: every row of A has `per` products."""
+    import torch
+    from paper_2606_20855_amd import wingspan as ws
+    t = dict(device="cuda:0", dtype=torch.int32)
+    n = rows * per
+    one = torch.ones(1, device="cuda:0").expand(n)   # (values are not read)
+    A = ws.DeviceCSR(rows, per, torch.arange(rows + 1, **t) * per, torch.arange(per, **t).repeat(rows), one)
+    B = ws.DeviceCSR(per, 64, torch.arange(per + 1, **t), torch.arange(per, **t) % 64, one[:per])
+    return A, B
+
+
+def test_long_rows_cost_what_short_ones_do():
+    # a row's products over many tiles of A's entries are added up by a whole wave: one row of 8 M entries takes about
+    # as long as 64 rows of 125 K (a lane alone: seven times as long)
+    import torch
+    from paper_2606_20855_amd import wingspan as ws
+    took = []
+    for rows, per in ((64, 125_000), (1, 8_000_000)):
+        A, B = _rows_of_one_entry_each(rows, per)
+        wsb, nbytes = ws.allocate_workspace(A, B)
+        out = torch.zeros(rows, dtype=torch.int64, device="cuda:0")
+        best = float("inf")
+        for _ in range(6):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(5):
+                ws.wingspan_spgemm_row_products(A.desc(), B.desc(), out.data_ptr(), wsb.data_ptr(), nbytes,
+                                                torch.cuda.current_stream().cuda_stream)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 5)
+        assert torch.all(out == per)
+        took.append(best)
+    print(f"64 rows {took[0] * 1e3:.0f} us, one row {took[1] * 1e3:.0f} us")
+    assert took[1] < 1.8 * took[0]
 
 
 # run in a process of its own: the library's first call that could take a read-back buffer must be the captured one
