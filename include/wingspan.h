@@ -416,6 +416,9 @@ wingspan_status wingspan_spgemm_outer(const wingspan_csr *At, const wingspan_csr
  * 2 = single pass (wingspan_spgemm_sharded). */
 wingspan_status wingspan_last_stats(int phase, wingspan_phase_stats *out);
 
+/* How many of that call's rows[WINGSPAN_TIER_HASH] were merged instead of hashed. */
+wingspan_status wingspan_last_merged_rows(int phase, int64_t *rows);
+
 /* Message for the last non-OK status on this thread ("" if none). */
 const char *wingspan_last_error(void);
 

@@ -68,6 +68,7 @@ constexpr size_t kAlign = 256;
 
 thread_local std::string g_err;
 thread_local wingspan_phase_stats g_stats[3];   // symbolic, numeric, single pass
+thread_local int64_t g_merged[3];               // their merged rows
 
 wingspan_status fail(wingspan_status s, const char *fmt, ...) {
     char buf[512];
@@ -787,6 +788,8 @@ void fill_stats(const Ctx &c, int phase) {
         st.c_nnz[t] += c.host.stat_cnnz[b];
     }
     for (int b = 0; b < kNumBins; ++b) st.total_products += c.host.stat_products[b];
+    g_merged[phase] = 0;
+    for (int b = kBinMerge0; b < kBinMerge0 + kNumMerge; ++b) g_merged[phase] += c.host.bin_count[b];
 }
 
 // Whether every byte offset of B's columns and values fits in 32 bits, so the
@@ -1866,6 +1869,13 @@ extern "C" {
 int wingspan_abi_version(void) { return WINGSPAN_ABI_VERSION; }
 
 const char *wingspan_last_error(void) { return g_err.c_str(); }
+
+wingspan_status wingspan_last_merged_rows(int phase, int64_t *rows) {
+    if (phase < 0 || phase > 2 || !rows)
+        return fail(WINGSPAN_ERR_INVALID_ARGUMENT, "phase must be 0, 1 or 2 and rows non-NULL");
+    *rows = g_merged[phase];
+    return WINGSPAN_OK;
+}
 
 wingspan_status wingspan_last_stats(int phase, wingspan_phase_stats *out) {
     if (phase < 0 || phase > 2 || !out) return fail(WINGSPAN_ERR_INVALID_ARGUMENT, "bad phase or NULL out");

@@ -111,6 +111,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.wingspan_last_error.restype = ctypes.c_char_p
     lib.wingspan_last_stats.argtypes = [i32, P(wingspan_phase_stats)]
     lib.wingspan_last_stats.restype = i32
+    lib.wingspan_last_merged_rows.argtypes = [i32, P(i64)]
+    lib.wingspan_last_merged_rows.restype = i32
     lib.wingspan_spgemm_workspace_size.argtypes = [csr_p, csr_p, i32, opt_p, P(sz)]
     lib.wingspan_spgemm_workspace_size.restype = i32
     lib.wingspan_spgemm_symbolic.argtypes = [csr_p, csr_p, vp, P(i64), vp, sz, vp, opt_p]
@@ -153,6 +155,7 @@ EXPORTED = (
     "wingspan_abi_version",
     "wingspan_last_error",
     "wingspan_last_stats",
+    "wingspan_last_merged_rows",
     "wingspan_spgemm_workspace_size",
     "wingspan_spgemm_symbolic",
     "wingspan_spgemm_numeric",
@@ -213,7 +216,14 @@ def wingspan_last_stats(phase: int) -> dict:
     out["total_products"] = st.total_products
     out["c_nnz_total"] = st.c_nnz_total
     out["structure_cache_rows"] = st.structure_cache_rows
+    out["merged_rows"] = wingspan_last_merged_rows(phase)
     return out
+
+
+def wingspan_last_merged_rows(phase: int) -> int:
+    n = ctypes.c_int64(0)
+    _check(load().wingspan_last_merged_rows(phase, ctypes.byref(n)))
+    return n.value
 
 
 def wingspan_spgemm_workspace_size(A: wingspan_csr, B: wingspan_csr, dtype: int, options=None) -> int:

@@ -179,8 +179,9 @@ def test_null_outputs():
 
 @pytest.mark.parametrize("phase", [-1, 3])
 def test_last_stats_bad_phase(phase):
-    got, _ = status_of(ws.wingspan_last_stats, phase)
-    assert got == "WINGSPAN_ERR_INVALID_ARGUMENT"
+    for call in (ws.wingspan_last_stats, ws.wingspan_last_merged_rows):
+        got, _ = status_of(call, phase)
+        assert got == "WINGSPAN_ERR_INVALID_ARGUMENT"
 
 
 def test_error_message_is_thread_local_and_cleared():

@@ -173,6 +173,11 @@ def test_dense_rows_across_regions(dtype, opts):
     assert num["rows"]["dense"] > 0
 
 
+# every row that fits a hash table takes it: rows of up to 64 A entries would be merged (the caps stay at their
+# default)
+HASHED = dict(max_lds_slots=16384)
+
+
 @pytest.mark.parametrize("r", [25, 50, 90])
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 def test_hash_rows_rank_emission_windows(r, dtype):
@@ -182,8 +187,8 @@ def test_hash_rows_rank_emission_windows(r, dtype):
     dist = "pm1" if dtype == np.float64 else "open01"
     A = matgen.er(64, 3000, r, seed=70 + r, dtype=dtype, dist=dist)
     B = matgen.er(3000, 200_000, 20, seed=69, dtype=dtype, dist=dist)
-    got, sym, num, ref = check(A, B, None, what=f"hash windows r={r}")
-    assert num["rows"]["hash"] == 64
+    got, sym, num, ref = check(A, B, HASHED, what=f"hash windows r={r}")
+    assert num["rows"]["hash"] == 64 and num["merged_rows"] == sym["merged_rows"] == 0
 
 
 @pytest.mark.parametrize("ncols,r", [(1_000_000, 25), (1_000_000, 50), (1_000_000, 90), (3_000_000, 50),
@@ -195,8 +200,8 @@ def test_hash_rows_bucket_emission(ncols, r, dtype):
     dist = "pm1" if dtype == np.float64 else "open01"
     A = matgen.er(64, 3000, r, seed=80 + r, dtype=dtype, dist=dist)
     B = matgen.er(3000, ncols, 20, seed=79, dtype=dtype, dist=dist)
-    got, sym, num, ref = check(A, B, None, what=f"hash buckets n={ncols} r={r}")
-    assert num["rows"]["hash"] == 64
+    got, sym, num, ref = check(A, B, HASHED, what=f"hash buckets n={ncols} r={r}")
+    assert num["rows"]["hash"] == 64 and num["merged_rows"] == sym["merged_rows"] == 0
 
 
 @pytest.mark.parametrize("r", [8, 20, 60])
@@ -207,8 +212,8 @@ def test_hash_rows_bucket_emission_skewed_columns(r, dtype):
     dist = "pm1" if dtype == np.float64 else "open01"
     B = matgen.rmat(14, 16, seed=84, dtype=dtype, dist=dist)
     A = matgen.er(200, B.nrows, r, seed=85 + r, dtype=dtype, dist=dist)
-    got, sym, num, ref = check(A, B, None, what=f"hash buckets skewed r={r}")
-    assert num["rows"]["hash"] > 0
+    got, sym, num, ref = check(A, B, HASHED, what=f"hash buckets skewed r={r}")
+    assert num["rows"]["hash"] > 0 and num["merged_rows"] == sym["merged_rows"] == 0
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])

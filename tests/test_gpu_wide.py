@@ -54,7 +54,7 @@ def test_wide(ncols, dtype):
         if opts is None:
             # (the rows of 2 long and of 40 and 64 short B rows fit the places in LDS at every width; the more regions,
             # the longer the rows merged piece by piece)
-            assert num["structure_cache_rows"] > 0 and num["rows"]["hash"] >= (4 if ncols < 4_000_000 else 9)
+            assert num["structure_cache_rows"] > 0 and num["merged_rows"] >= (4 if ncols < 4_000_000 else 9)
     dA, dB = ws.DeviceCSR.from_host(A, "cuda:0"), ws.DeviceCSR.from_host(B, "cuda:0")
     C = ws.sharded_to_csr(ws.spgemm_sharded(dA, dB))
     torch.cuda.synchronize()
