@@ -355,6 +355,7 @@ struct BinCfg {
     int32_t force_spill;
     int32_t dense_ok;       // the dense tier can take rows of this problem
     int32_t numeric;        // 0: symbolic bins, 1: numeric bins
+    int32_t merge_products; // 1: merged rows' products are formed (numeric phase, single pass), 0: counted
     int32_t merge_runs;     // rows of at most this many A entries ...
     int32_t merge_places;   // ... and this many places in LDS are merged (0: none),
     int32_t merge_over_dense;   // rows the dense tier would take up to this many places;
@@ -367,6 +368,43 @@ __device__ __forceinline__ int class_of(int64_t f) {
     int c = l - 10;
     c = c < 0 ? 0 : (c >= kNumClasses ? kNumClasses - 1 : c);
     return kNumClasses - 1 - c;
+}
+
+// Whether a row of f products, which takes `places` places merged, costs less
+// there than in an LDS hash table. Merging costs as its kernel's size (the next
+// power of two of the places) and a little per pass, hashing as the table's (l by
+// the products: columns that repeat make the table smaller but not the inserts
+// fewer). Short runs are what hashing is for: their padding makes the kernel
+// larger than the table (64 A entries of 2 products each: counted 5.7 ns a row
+// merged and 0.93 hashed, formed 6.4 and 2.5).
+//
+// Formed: equal sizes are merged, up to 512 places from 129 products on (where
+// the table's sorted emission takes 5 ns a row) and up to 256 below. At 2048
+// places and more the table costs less unless the padding is small (64 entries
+// of 16: merged 14.7 ns, hashed 11; 32 of 32: 12.8 and 13.1). C of so many
+// columns that the table's rank emission takes more than eight windows makes
+// hashing cost twice as much and more, so there the next size is merged too (2 M
+// columns, 48 entries of 6: 6.4 and 11.6 ns).
+// Counted: the table holds keys alone, so the padding counts for more: at most
+// 2.25 places per product, and from 2048 places on only where they are no more
+// than the products' power of two or a quarter above the products (48 entries of
+// 12: merged 5.9 ns, hashed 3.8; 8 of 128: 3.9 and 5.5).
+// Over 2 to 64 A entries of 1 to 256 products each, at 100 K to 2 M columns (1160
+// timed pairs), the choice costs 0.7% more than the better of the two on average
+// and 24% at most (merging all of them: 30% and 6 times).
+__device__ __forceinline__ bool merge_pays(int64_t f, int64_t places, const BinCfg &cfg) {
+    int lm = ceil_log2(places);
+    if (lm < kMergeLog2Min) lm = kMergeLog2Min;
+    if (cfg.merge_products) {
+        const int l = ceil_log2(f + (f >> 1));
+        const int least = f > 128 ? 9 : 8;
+        const int same = l > least ? l : least;
+        if (f > 128 && cfg.ncols > (int64_t(512) << l)) return lm <= same + 1;
+        return lm <= same && (lm < 11 || 20 * places <= 27 * f);
+    }
+    const int l = ceil_log2(2 * f);
+    return lm <= (l > kMergeLog2Min ? l : kMergeLog2Min) && 4 * places <= 9 * f &&
+           (lm < 11 || lm <= ceil_log2(f) || 4 * places <= 5 * f);
 }
 
 // f: products of the row; k: its A entries; c: output entries (numeric only);
@@ -392,13 +430,15 @@ __device__ __forceinline__ int choose_bin(int64_t f, int k, int64_t c, const Bin
     // entries has at least c products, so every row the numeric phase will prefer dense goes through the
     // symbolic bitmap kernel and leaves its column set in the structure cache)
     const bool dense_pref = cfg.dense_ok && (cfg.numeric ? c : f) >= cfg.dense_min_nnz;
+    const bool hash_fits = !cfg.force_spill && l <= cfg.hash_log2_max && !dense_pref;
     // merge rows, by the places they take in LDS
-    const int64_t places = f + int64_t(cfg.numeric ? kMergePadNum : kMergePadSym) * k;
-    if (k <= cfg.merge_runs && places <= (dense_pref ? cfg.merge_over_dense : cfg.merge_places)) {
+    const int64_t places = f + int64_t(cfg.merge_products ? kMergePadNum : kMergePadSym) * k;
+    if (k <= cfg.merge_runs && places <= (dense_pref ? cfg.merge_over_dense : cfg.merge_places) &&
+        (!hash_fits || merge_pays(f, places, cfg))) {
         const int lm = ceil_log2(places);
         return kBinMerge0 + (lm < kMergeLog2Min ? 0 : lm - kMergeLog2Min);
     }
-    if (!cfg.force_spill && l <= cfg.hash_log2_max && !dense_pref) return kBinHash0 + (l - kHashLog2Min);
+    if (hash_fits) return kBinHash0 + (l - kHashLog2Min);
     if (k <= cfg.merge_runs && f <= cfg.merge_long) return kBinMergeLong;
     if (!cfg.force_spill && cfg.dense_ok) return kBinDense0 + class_of(f);
     *bound = cfg.numeric ? c : (f < cfg.ncols ? f : cfg.ncols);

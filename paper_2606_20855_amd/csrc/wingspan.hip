@@ -421,10 +421,11 @@ Stamp make_stamp(const Ctx &c, const wingspan_csr *A, const wingspan_csr *B, int
 }
 
 // Which rows are merged (merge.hpp): those of up to 64 A entries whose
-// products fit 2^13 places of LDS, unless the options ask for the hash tables
-// (max_lds_slots) or the spill tier. They beat the hash tables at every number
-// of runs up to 64 (up to 4 runs, 16, 64 merged on the R-MAT graph of 2.5 M
-// vertices: the tier 11.5, 6.0 and 5.5 ms).
+// products fit 2^13 places of LDS and that cost less there than in a hash table
+// (merge_pays), unless the options ask for the hash tables (max_lds_slots) or
+// the spill tier. Rows of long runs do at every number of runs up to 64 (up to 4
+// runs, 16, 64 merged on the R-MAT graph of 2.5 M vertices: the tier 11.5, 6.0
+// and 5.5 ms).
 //
 // Rows the dense tier would take stay there where B's columns fit one region of
 // the rank kernel (R-MAT 18, rows up to 4096 places merged: 10.63 ms a step
@@ -439,11 +440,12 @@ Stamp make_stamp(const Ctx &c, const wingspan_csr *A, const wingspan_csr *B, int
 // 1.6 ms), never piece by piece (2.5 M vertices: 4.7 ms in all either way).
 constexpr int kMergeOverBitmap = 4096;
 constexpr int kMergePerRegion = 2048;
-void set_merge(const Ctx &c, const wingspan_csr *B, BinCfg *cfg) {
+void set_merge(const Ctx &c, const wingspan_csr *B, bool products, BinCfg *cfg) {
     const bool on = !c.o.force_spill && !c.o.lds_explicit;
     constexpr int most = 1 << kMergeLog2Max;
     cfg->merge_runs = on ? kMergeMaxRuns : 0;
     cfg->merge_places = on ? most : 0;
+    cfg->merge_products = products;
     cfg->merge_over_dense = cfg->merge_long = 0;
     const int64_t regions = (B->ncols + kRankRegionCols - 1) / kRankRegionCols;
     if (!on || c.o.dense_min_explicit || regions < 2) return;
@@ -479,7 +481,7 @@ BinCfg numeric_bin_cfg(const Ctx &c, const wingspan_csr *B) {
     cfg.hash_log2_max = c.o.hash_log2_max_num;
     cfg.dense_min_nnz = c.o.dense_min_nnz;
     cfg.dense_ok = c.L.nwin > 0;
-    set_merge(c, B, &cfg);
+    set_merge(c, B, true, &cfg);
     return cfg;
 }
 
@@ -732,7 +734,7 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
     cfg.force_spill = c.o.force_spill;
     cfg.hash_log2_max = mode == kModeSymbolic ? c.o.hash_log2_max_sym : c.o.hash_log2_max_num;
     cfg.dense_min_nnz = c.o.dense_min_nnz;
-    set_merge(c, B, &cfg);
+    set_merge(c, B, mode != kModeSymbolic, &cfg);
     if (mode == kModeNumeric) {
         cfg = numeric_bin_cfg(c, B);
     } else if (mode == kModeSymbolic) {
