@@ -1694,7 +1694,9 @@ OpLayout op_plan(const wingspan_csr *At, const wingspan_csr *B, int64_t P) {
     L.off_partials = off;
     const int64_t n = std::max<int64_t>(K, m) + 1;
     off += align_up(sizeof(int64_t) * ((n + kScanTile - 1) / kScanTile + 2));
-    L.off_part_key = off;   // two int32 column arrays of p and one of values for the long-row merge
+    // two int32 column arrays of p and one of values: the pieces' sums and sorted runs of buckets past kOpRowCap,
+    // which may hold every product (known only once the claims are made)
+    L.off_part_key = off;
     off += align_up(sizeof(int64_t) * p);
     L.off_part_val = off;
     off += align_up(sizeof(double) * p);
@@ -1800,14 +1802,15 @@ wingspan_status op_impl(Ctx &c, const wingspan_csr *At, const wingspan_csr *B, c
                                                                                row_nnz);
     op_merge_mid<V><<<blocks_for(m, kWave), 256, 0, c.st>>>(bucket, m, bkt_col, bkt_val, out_val, row_nnz, long_rows,
                                                             ctr);
-    op_merge_long<V><<<static_cast<unsigned>(std::min<int64_t>(m, kOpLongGrid)), kOpRowBlock, 0, c.st>>>(
-        bucket, bkt_col, bkt_val, out_val, row_nnz, long_rows, ctr);
-    // rows past kOpRowCap: their own arrays hold the sorted runs (X: columns in part_key's first half, values in
-    // part_val; Y: columns in its second half, values in bkt_val)
-    int32_t *run_col = reinterpret_cast<int32_t *>(part_key);
+    // rows past kOpRowCap: their own arrays hold the pieces' sums or the sorted runs (X: columns in part_key's first
+    // half, values in part_val; Y: columns in its second half, values in bkt_val)
+    int32_t *run_col = reinterpret_cast<int32_t *>(part_key), *run_col2 = run_col + std::max<int64_t>(P, 1);
+    const int nlong = static_cast<int>(std::min<int64_t>(m, kOpLongGrid));
+    const unsigned pieces = P > kOpRowCap && B->ncols <= kOpSumCols ? blocks_for(P, kOpPiece) : 0;
+    op_merge_long<V><<<nlong + pieces, kOpRowBlock, 0, c.st>>>(bucket, m, P, B->ncols, nlong, bkt_col, bkt_val, out_val,
+                                                               row_nnz, long_rows, ctr, run_col, part_val, run_col2);
     op_merge_huge<V><<<static_cast<unsigned>(std::min<int64_t>(m, kOpHugeGrid)), kOpHugeBlock, 0, c.st>>>(
-        bucket, m, bkt_col, bkt_val, out_val, row_nnz, long_rows, ctr, run_col, part_val,
-        run_col + std::max<int64_t>(P, 1));
+        bucket, m, B->ncols, bkt_col, bkt_val, out_val, row_nnz, long_rows, ctr, run_col, part_val, run_col2);
     LAUNCH_CHECK("outer merge");
     // 4. C.row_ptr, then the rows gathered into CSR
     if (c.back.p == nullptr) c.back.take(c.st);
