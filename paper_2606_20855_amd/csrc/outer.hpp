@@ -437,11 +437,11 @@ __device__ __forceinline__ void op_merge_wave(int64_t lo, int len, int32_t *__re
 }
 
 // 3b. Buckets of 33 to kOpMidCap entries, a wave per row; a workgroup looks at
-// 64 rows and lists the longer ones (one atomic for all of them): up to kOpRowCap
-// from the front of long_rows for op_merge_long (count in counters[0]), the rest
-// from its back for op_merge_huge (counters[2]).
+// `per` rows (at most 64, op_mid_rows) and lists the longer ones (one atomic for
+// all of them): up to kOpRowCap from the front of long_rows for op_merge_long
+// (count in counters[0]), the rest from its back for op_merge_huge (counters[2]).
 template <typename V>
-__global__ void __launch_bounds__(256) op_merge_mid(const int64_t *__restrict__ bucket_off, int64_t m,
+__global__ void __launch_bounds__(256) op_merge_mid(const int64_t *__restrict__ bucket_off, int64_t m, int per,
                                                     int32_t *__restrict__ bkt_col,
                                                     const double *__restrict__ bkt_val, V *__restrict__ out_val,
                                                     int32_t *__restrict__ row_nnz, int32_t *__restrict__ long_rows,
@@ -449,8 +449,8 @@ __global__ void __launch_bounds__(256) op_merge_mid(const int64_t *__restrict__ 
     __shared__ double s_val[256 / kWave][kOpMidCap];
     const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
     const int ln = lane_id();
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kWave;
-    const int64_t row = row0 + ln;
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * per;
+    const int64_t row = ln < per ? row0 + ln : m;
     const int64_t lo = row < m ? bucket_off[row] : 0;
     const int64_t len = row < m ? bucket_off[row + 1] - lo : 0;
     if (wv == 0) {

@@ -1677,6 +1677,15 @@ wingspan_status sv_impl(Ctx &c, const wingspan_csr *At, const SvLayout &L, const
 constexpr int64_t kOpLongGrid = 2048;   // coalesce workgroups for long rows at most (grid-stride beyond)
 constexpr int64_t kOpHugeGrid = 512;    // the same for rows past kOpRowCap (one or two workgroups per CU)
 
+// Rows per workgroup of op_merge_mid: 64, or as few as give 1024 workgroups, four at least (a row for each of its
+// waves). A wave takes 5 us for a row of 144 entries, one after the other: with 64 rows per workgroup 90 us for C of
+// 1000 and of 5000 rows, now 10 and 17 us (the calls 223 -> 144 and 247 -> 177 us).
+int op_mid_rows(int64_t m) {
+    int per = kWave;
+    while (per > 4 && m < int64_t(1024) * per) per /= 2;
+    return per;
+}
+
 struct OpLayout {
     size_t off_pref, off_ctr, off_partials, off_part_key, off_part_val, off_place, off_row_cnt,
         off_bucket, off_row_nnz, off_long, off_bkt_col, off_bkt_val, off_out_val, total;
@@ -1800,7 +1809,8 @@ wingspan_status op_impl(Ctx &c, const wingspan_csr *At, const wingspan_csr *B, c
     else
         op_merge_short<uint64_t, V><<<blocks_for(m, 256 / 32), 256, 0, c.st>>>(bucket, m, bkt_col, bkt_val, out_val,
                                                                                row_nnz);
-    op_merge_mid<V><<<blocks_for(m, kWave), 256, 0, c.st>>>(bucket, m, bkt_col, bkt_val, out_val, row_nnz, long_rows,
+    const int per = op_mid_rows(m);
+    op_merge_mid<V><<<blocks_for(m, per), 256, 0, c.st>>>(bucket, m, per, bkt_col, bkt_val, out_val, row_nnz, long_rows,
                                                             ctr);
     // rows past kOpRowCap: their own arrays hold the pieces' sums or the sorted runs (X: columns in part_key's first
     // half, values in part_val; Y: columns in its second half, values in bkt_val)

@@ -149,3 +149,39 @@ def test_a_small_c_costs_what_a_large_one_does(shape):
     print(f"{shape}: {took[0] * 1e3:.0f} us for {products[0]:.0f} products, spread {took[1] * 1e3:.0f} us for "
           f"{products[1]:.0f}")
     assert took[0] < 5 * took[1]
+
+
+@pytest.mark.parametrize("m", [1000, 5000])
+def test_few_rows_are_spread_over_waves(m):
+    # buckets of 144 entries, a wave each, against buckets of 9 (64 rows to a workgroup of four waves: 90 us more)
+    import torch
+    from paper_2606_20855_amd import wingspan as ws
+    took = []
+    for r in (3, 12):
+        T = ws.DeviceCSR.from_host(matgen.er(m, m, r, 91), "cuda:0")
+        best = float("inf")
+        for _ in range(20):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            ws.spgemm_outer(T, T)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]))
+        took.append(best)
+    print(f"{m} rows: {took[0] * 1e3:.0f} us, {took[1] * 1e3:.0f} us")
+    assert took[1] < took[0] + 0.075
+
+
+@pytest.mark.parametrize("m", [1, 3, 4, 5, 63, 64, 65, 1023, 8191, 8192, 16_385, 65_535, 65_536])
+def test_rows_of_a_workgroup(m):
+    # rows of 9, 36 and 300 products by turns, the last rows included, at every number of rows per workgroup
+    rng = np.random.default_rng(m)
+    sizes = [9, 36, 300]
+    B = _csr([np.sort(rng.choice(5000, s, replace=False)) for s in sizes for _ in range(40)], 5000, rng, np.float64)
+    pick = np.arange(m) % 3 * 40 + rng.integers(0, 40, m)
+    A = matgen.CSR(m, B.nrows, np.arange(m + 1, dtype=np.int32), pick.astype(np.int32), np.full(m, 2.0))
+    got = _outer(A, B)
+    lens = np.diff(B.row_ptr)[pick]
+    assert np.array_equal(np.diff(got.row_ptr), lens)
+    at = np.repeat(B.row_ptr[pick] - got.row_ptr[:-1], lens) + np.arange(len(got.col_idx))
+    assert np.array_equal(got.col_idx, B.col_idx[at]) and np.array_equal(got.val, 2.0 * B.val[at])
