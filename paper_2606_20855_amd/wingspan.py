@@ -492,6 +492,10 @@ def spgemm_sharded(A: DeviceCSR, B: DeviceCSR, options=None, stream=None, worksp
         raise TypeError("A and B must share a value dtype")
     dev = A.row_ptr.device
     if workspace is None:
+        # a single pass uses no structure cache: none is allocated for it
+        options = make_options(**options) if isinstance(options, dict) else options
+        options = wingspan_options.from_buffer_copy(options) if options is not None else make_options()
+        options.cache_mib = -1
         ws, nbytes = allocate_workspace(A, B, options)
     else:
         ws, nbytes = workspace, workspace.numel()

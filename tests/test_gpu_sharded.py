@@ -233,3 +233,22 @@ def test_rerun_reuses_buffers():
     c2 = ws.sharded_to_csr(S2).to_host()
     assert np.array_equal(c1.row_ptr, c2.row_ptr) and np.array_equal(c1.col_idx, c2.col_idx)
     assert_matches(c2, oracle.spgemm(A, A), A.val.dtype, what="rerun")
+
+
+@pytest.mark.parametrize("options", [None, dict(dense_min_nnz=300), "struct"])
+def test_a_single_pass_allocates_no_structure_cache(options, monkeypatch):
+    # its own workspace, without the cache it does not use, whatever options it is given (which stay as they are)
+    import torch
+    from paper_2606_20855_amd import wingspan as ws
+    A = matgen.rmat(11, 16, seed=21, dtype=np.float32)
+    dA = ws.DeviceCSR.from_host(A, "cuda:0")
+    options = ws.make_options(dense_min_nnz=300) if options == "struct" else options
+    sizes = []
+    real = ws.allocate_workspace
+    monkeypatch.setattr(ws, "allocate_workspace", lambda *a: sizes.append(real(*a)) or sizes[-1])
+    C = ws.sharded_to_csr(ws.spgemm_sharded(dA, dA, options=options))
+    torch.cuda.synchronize()
+    assert_matches(C.to_host(), oracle.spgemm(A, A), np.float32, what=f"{options}")
+    want = dict(cache_mib=-1) if options is None else dict(cache_mib=-1, dense_min_nnz=300)
+    assert [n for _, n in sizes] == [ws.wingspan_spgemm_workspace_size(dA.desc(), dA.desc(), dA.dtype_code, want)]
+    assert options is None or isinstance(options, dict) or options.cache_mib == 0
