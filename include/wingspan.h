@@ -143,7 +143,17 @@ typedef struct {
 } wingspan_phase_stats;
 
 /* Bytes of device workspace the calls below need for this A, B and options.
- * Depends only on the sizes, never on the data; pure host code. */
+ * Depends only on the sizes, never on the data; pure host code. So it holds
+ * what rows of the dense tier would need whether or not there are any:
+ *   - a table of B's entries per column window, 4 bytes times B.nrows times the
+ *     windows and one more: ceil(B.ncols / 8192) windows up to 1048576 columns,
+ *     and beyond at most 128 wider ones, up to 33554432 columns and 4 GiB;
+ *   - the structure cache, up to options->cache_mib (4 GiB by default).
+ * A and B of 2500000 rows and columns and 5000000 entries: 5.9 GiB, 0.7 GiB of
+ * them the table and 4 the cache. Matrices whose rows are all short (a mesh) can
+ * do without: cache_mib = -1 leaves out the cache (8% of the time of a product
+ * whose rows do use it), dense_min_nnz = -1 both (rows too long for LDS then take
+ * the spill tier, many times slower). */
 wingspan_status wingspan_spgemm_workspace_size(const wingspan_csr *A, const wingspan_csr *B,
                                                wingspan_dtype dtype,
                                                const wingspan_options *options,

@@ -82,6 +82,35 @@ def test_workspace_structure_cache_is_bounded():
     assert 0 < with_cache - without <= (4 << 30) + 2 * n * 4 + 1024
 
 
+@pytest.mark.parametrize("n", [1_048_576, 1_048_577, 2_500_000, 33_554_432, 33_554_433, 60_000_000])
+def test_workspace_of_many_columns_is_what_the_header_says(n):
+    # B's window table: windows of 8192 columns, from 1048577 columns on at most 128 wider ones, up to 33554432 columns
+    # and 4 GiB; the structure cache; dense_min_nnz = -1 drops both
+    rows = 1_000_000
+    A, B = desc(rows, rows, 2_000_000), desc(rows, n, 2_000_000)
+
+    def size(**kw):
+        return ws.wingspan_spgemm_workspace_size(A, B, ws.F32, ws.make_options(**kw) if kw else None)
+
+    width = 8192
+    while n > 128 * width:
+        width *= 2
+    windows = -(-n // width) if width <= 262_144 else 0
+    table = 4 * rows * (windows + 1) if windows else 0
+    assert table < 4 << 30
+    assert 0 <= size(cache_mib=-1) - size(dense_min_nnz=-1) - table < 1024
+    cache = size() - size(cache_mib=-1)
+    assert cache <= (4 << 30) + 8 * rows + 1024 and (cache > 3.9 * 2 ** 30) == (windows > 0)
+
+
+def test_workspace_of_a_large_mesh():
+    n = 2_500_000
+    A = desc(n, n, 2 * n)
+    gib = [ws.wingspan_spgemm_workspace_size(A, A, ws.F32, ws.make_options(**kw)) / 2 ** 30
+           for kw in ({}, dict(cache_mib=-1), dict(dense_min_nnz=-1))]
+    assert [round(g, 1) for g in gib] == [5.9, 1.9, 1.1]
+
+
 def test_workspace_follows_the_cache_budget():
     # options.cache_mib bounds the structure cache: one bitmap of ceil(ncols / 2048) * 256 bytes per row, at most
     # one per row of A; -1 keeps no cache (nor its two per-row tables)
