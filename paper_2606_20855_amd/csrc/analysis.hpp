@@ -7,8 +7,10 @@
 namespace wsp {
 
 // ---------------------------------------------------------------------------
-// Device-wide exclusive scan (int64 output) of a generated sequence, in three
-// launches: tile sums, a scan of the tile sums, and the tile scans.
+// Device-wide exclusive scan (int64 output) of a generated sequence: tile sums,
+// and tile scans that add up the sums before their tile (up to kScanOwnTiles
+// tiles; past them a third launch between the two scans the sums). One tile is
+// scanned in one launch, and short sequences by scan_one_block.
 // ---------------------------------------------------------------------------
 constexpr int kScanBlock = 256;
 constexpr int kScanItems = 8;
@@ -163,6 +165,66 @@ __global__ void __launch_bounds__(kScanBlock) scan_tiles(In in, int64_t n, const
     }
 }
 
+// The same exclusive scan in one workgroup of 1024 threads, for short
+// sequences of cheap inputs (one launch instead of two): thread t sums its
+// contiguous share, the workgroup scans the shares, and each thread writes its
+// share's prefixes. out[n] = total.
+template <typename In>
+__global__ void __launch_bounds__(1024) scan_one_block(In in, int64_t n, int64_t *out, uint64_t *csum,
+                                                       int64_t *host_total) {
+    __shared__ int64_t wsum[16];
+    const int64_t per = (n + 1023) / 1024;
+    const int64_t b = static_cast<int64_t>(threadIdx.x) * per;
+    const int64_t e = b + per < n ? b + per : n;
+    int64_t s = 0;
+    for (int64_t i0 = b; i0 < e; i0 += 8) {   // eight loads in flight at a time
+        int64_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = i0 + u < e ? in(i0 + u) : 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    const int ln = lane_id();
+    const int w = threadIdx.x / kWave;
+    int64_t incl = s;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t y = __shfl_up(incl, o, kWave);
+        if (ln >= o) incl += y;
+    }
+    if (ln == kWave - 1) wsum[w] = incl;
+    __syncthreads();
+    int64_t run = 0, tot = 0;
+    for (int i = 0; i < 16; ++i) {
+        run += i < w ? wsum[i] : 0;
+        tot += wsum[i];
+    }
+    run += incl - s;
+    uint64_t acc = 0;
+    for (int64_t i0 = b; i0 < e; i0 += 8) {
+        int64_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = i0 + u < e ? in(i0 + u) : 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (i0 + u < e) {
+                out[i0 + u] = run;
+                acc += static_cast<uint64_t>(run) * static_cast<uint64_t>(2 * (i0 + u) + 1);
+            }
+            run += v[u];
+        }
+    }
+    if (threadIdx.x == 0) {
+        out[n] = tot;
+        if (host_total != nullptr) *host_total = tot;
+        acc += static_cast<uint64_t>(tot) * static_cast<uint64_t>(2 * n + 1);
+    }
+    if (csum != nullptr) {
+        __syncthreads();
+        add_checksum<1024>(acc, csum, wsum);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Row product counts. One pass over A's entries gathers the lengths of the B
 // rows they select: loc[i] is the exclusive prefix of the lengths within entry
@@ -281,67 +343,6 @@ __global__ void __launch_bounds__(256) row_products_kernel(const int32_t *__rest
     if (i == 0 && !stamp->same_problem(own)) stamp->magic = 0;
     const int64_t f = row_products_of(i < m ? a_rp[i] : 0, i < m ? a_rp[i + 1] : 0, nnz, loc, tile_sum);
     if (i < m) out[i] = f;
-}
-
-// The same exclusive scan in one workgroup of 1024 threads, for short
-// sequences of cheap inputs (one launch instead of three): thread t sums its
-// contiguous share, the workgroup scans the shares, and each thread writes its
-// share's prefixes. out[n] = total.
-
-template <typename In>
-__global__ void __launch_bounds__(1024) scan_one_block(In in, int64_t n, int64_t *out, uint64_t *csum,
-                                                       int64_t *host_total) {
-    __shared__ int64_t wsum[16];
-    const int64_t per = (n + 1023) / 1024;
-    const int64_t b = static_cast<int64_t>(threadIdx.x) * per;
-    const int64_t e = b + per < n ? b + per : n;
-    int64_t s = 0;
-    for (int64_t i0 = b; i0 < e; i0 += 8) {   // eight loads in flight at a time
-        int64_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = i0 + u < e ? in(i0 + u) : 0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    const int ln = lane_id();
-    const int w = threadIdx.x / kWave;
-    int64_t incl = s;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int64_t y = __shfl_up(incl, o, kWave);
-        if (ln >= o) incl += y;
-    }
-    if (ln == kWave - 1) wsum[w] = incl;
-    __syncthreads();
-    int64_t run = 0, tot = 0;
-    for (int i = 0; i < 16; ++i) {
-        run += i < w ? wsum[i] : 0;
-        tot += wsum[i];
-    }
-    run += incl - s;
-    uint64_t acc = 0;
-    for (int64_t i0 = b; i0 < e; i0 += 8) {
-        int64_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = i0 + u < e ? in(i0 + u) : 0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (i0 + u < e) {
-                out[i0 + u] = run;
-                acc += static_cast<uint64_t>(run) * static_cast<uint64_t>(2 * (i0 + u) + 1);
-            }
-            run += v[u];
-        }
-    }
-    if (threadIdx.x == 0) {
-        out[n] = tot;
-        if (host_total != nullptr) *host_total = tot;
-        acc += static_cast<uint64_t>(tot) * static_cast<uint64_t>(2 * n + 1);
-    }
-    if (csum != nullptr) {
-        __syncthreads();
-        add_checksum<1024>(acc, csum, wsum);
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -618,11 +619,6 @@ __global__ void zero_words(int32_t *p, int64_t n) {
 }
 
 __global__ void fill_i64(int64_t *p, int64_t n, int64_t v) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-__global__ void fill_i32(int32_t *p, int64_t n, int32_t v) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
 }

@@ -164,20 +164,6 @@ __device__ __forceinline__ int group_incl_scan(int x) {
     return x;
 }
 
-// Within a group of W lanes holding a non-decreasing `incl`, the number of
-// lanes whose value is <= q. With incl the inclusive prefix of per-lane
-// lengths and q < incl[W-1], this is the lane that owns element q.
-template <int W>
-__device__ __forceinline__ int group_count_le(int incl, int q) {
-    int c = 0;
-#pragma unroll
-    for (int step = W / 2; step >= 1; step >>= 1) {
-        const int v = __shfl(incl, c + step - 1, W);
-        if (v <= q) c += step;
-    }
-    return c;
-}
-
 template <typename T>
 __device__ __forceinline__ T wave_sum(T x) {
 #pragma unroll

@@ -52,12 +52,6 @@ __global__ void __launch_bounds__(256) sv_clear(int32_t *__restrict__ flag_words
     if (i == 0) *err = 0;
 }
 
-// 1 where y is stored.
-struct SvFlagIn {
-    const uint8_t *flag;
-    __device__ __forceinline__ int64_t operator()(int64_t i) const { return flag[i] != 0 ? 1 : 0; }
-};
-
 // Scatters the P = pref[nnz_x] products into the map: yval[i] += A[i, j] * x_j
 // and flag[i] = 1 for each selected entry (i, j). Workgroups take chunks of
 // kSvChunk products, grid-stride, reading P (and the check of x, which stops
@@ -161,40 +155,6 @@ constexpr int kSvMaxRanges = 2048;    // y of at most 8 M positions takes the bu
 constexpr int kSvPieceMax = 16384;   // sorted products per accumulating workgroup at most
 constexpr int kSvAccBlock = 256;
 constexpr int kSvAccPer = 16;                       // products per thread and pass
-
-// Product q's row of y and value, for a chunk whose x entries [t0, t0 + nt)
-// are staged (s_pref, s_base, s_x) when nt <= kSvBinStage, else looked up in
-// global memory.
-template <typename V>
-__device__ __forceinline__ void sv_product(const int32_t *__restrict__ at_rp, const int32_t *__restrict__ at_row,
-                                           const V *__restrict__ at_val, const int32_t *__restrict__ x_idx,
-                                           const V *__restrict__ x_val, const int64_t *__restrict__ pref,
-                                           const int64_t *s_pref, const int64_t *s_base, const double *s_x, int t0,
-                                           int nt, bool staged, int64_t q, int *row, double *v) {
-    int64_t pos;
-    double xv;
-    if (staged) {
-        int lo = 0, hi = nt - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_pref[mid] <= q) lo = mid;
-            else hi = mid - 1;
-        }
-        pos = s_base[lo] + q;
-        xv = s_x[lo];
-    } else {
-        int lo = t0, hi = t0 + nt - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (pref[mid] <= q) lo = mid;
-            else hi = mid - 1;
-        }
-        pos = static_cast<int64_t>(at_rp[x_idx[lo]]) + (q - pref[lo]);
-        xv = to_d(x_val[lo]);
-    }
-    *row = at_row[pos];
-    *v = to_d(at_val[pos]) * xv;
-}
 
 template <typename V>
 __global__ void __launch_bounds__(kSvBinBlock) sv_bin(const int32_t *__restrict__ at_rp,

@@ -600,8 +600,6 @@ wingspan_status launch_window_table(Ctx &c, const wingspan_csr *B, hipStream_t s
     return WINGSPAN_OK;
 }
 
-// Product counts, optional validation, and binning. Ends with the control
-// block on the host.
 // The rows into bins: counts, offsets (ctrl, cleared before) and perm. m > 0.
 wingspan_status launch_bins(Ctx &c, const int32_t *a_rp, const RowProducts &rp, const int64_t *c_rp, int64_t m,
                             const BinCfg &cfg, Control *ctrl, int32_t *perm, int32_t *row_nnz, int32_t *slot_of_row,
@@ -621,6 +619,8 @@ wingspan_status launch_bins(Ctx &c, const int32_t *a_rp, const RowProducts &rp, 
 // doubles; row_nnz_out receives 0 for the rows without products).
 enum AnalysisMode { kModeSymbolic = 0, kModeNumeric = 1, kModeSharded = 2 };
 
+// Product counts, optional validation, and binning. Ends with the control
+// block on the host.
 wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, AnalysisMode mode,
                         const int64_t *c_rp, bool have_pref, int32_t *row_nnz_out = nullptr) {
     wingspan_status s;
@@ -662,9 +662,9 @@ wingspan_status analyze(Ctx &c, const wingspan_csr *A, const wingspan_csr *B, An
         const BinCfg cfg = numeric_bin_cfg(c, B);
         const Stamp &h = c.host_stamp;
         stale = !stamp_matches(c, A, B);
-        if (!stale && h.num_bins == 1 && !c.o.validate && h.nb_dense_min_nnz == cfg.dense_min_nnz && h.nb_tiny_max == cfg.tiny_max &&
-            h.nb_hash_log2_max == cfg.hash_log2_max && h.nb_force_spill == cfg.force_spill &&
-            h.nb_dense_ok == cfg.dense_ok && h.nb_merge_runs == cfg.merge_runs &&
+        if (!stale && h.num_bins == 1 && !c.o.validate && h.nb_dense_min_nnz == cfg.dense_min_nnz &&
+            h.nb_tiny_max == cfg.tiny_max && h.nb_hash_log2_max == cfg.hash_log2_max &&
+            h.nb_force_spill == cfg.force_spill && h.nb_dense_ok == cfg.dense_ok && h.nb_merge_runs == cfg.merge_runs &&
             h.nb_merge_places == cfg.merge_places && h.nb_merge_over_dense == cfg.merge_over_dense &&
             h.nb_merge_long == cfg.merge_long) {
             c.host = kept;
@@ -1537,8 +1537,8 @@ SvLayout sv_plan(const wingspan_csr *At, int64_t nnz_x) {
     const int64_t m = std::max<int64_t>(At->ncols, 1), nx = std::max<int64_t>(nnz_x, 0);
     L.ntiles = (m + kSvTile - 1) / kSvTile;
     size_t off = 0;
-    // first the tiles' prefix (whose first word, always 0, ends a stamp that a symbolic phase left here), its total (y's entry count) last, then the error word: the total and the error
-    // word are read back in one copy. (Measured: the scatter runs about 20% slower with these small arrays
+    // first the tiles' prefix (whose first word, always 0, ends a stamp that a symbolic phase left here), its total
+    // (y's entry count) last, then the error word: the total and the error word are read back in one copy. (Measured: the scatter runs about 20% slower with these small arrays
     // placed just past the map's accumulators.)
     L.off_tile_pre = off;
     L.off_err = off + sizeof(int64_t) * (L.ntiles + 1);
