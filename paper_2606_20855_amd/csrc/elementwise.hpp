@@ -229,7 +229,9 @@ __device__ __forceinline__ uint32_t ew_kept(uint32_t codes, uint32_t valid, int 
 // Per tile: tile_cnt[t] = C's entries from the tile, the threads' codes, and for
 // every row r that starts in the tile (rows without entries too) row_at[r] = C's
 // entries of the tile before the row (rows may be null: the caller has C's row
-// pointer). Each thread walks kEwPer positions of the merged order.
+// pointer). Each thread walks kEwPer positions of the merged order. Bound by VALU
+// issue (the sum of R-MAT 20 and its shuffled copy: 71 us, the VALU busy all the
+// time, 2.4 TB/s).
 __global__ void __launch_bounds__(kEwBlock) ew_tile_count(const int32_t *__restrict__ a_rp,
                                                           const int32_t *__restrict__ a_col,
                                                           const int32_t *__restrict__ b_rp,
@@ -332,10 +334,11 @@ struct EwTileIn {
 // leave each entry's place in C in LDS. The product reads the common entries
 // alone, by the threads that own their codes.
 //
-// Bound by HBM (the sum of R-MAT 20 and its shuffled copy, double: 32 M entries
-// in and out, 780 MB: merging the keys again in this kernel 175 us, from the codes
-// 137 us, with each thread reading its own entries 228 us; the product of
-// R-MAT 18 with its pattern, float: 46 us, now 26 us).
+// Bound by HBM, 5.9 TB/s fetched and written in the sum (the sum of R-MAT 20 and
+// its shuffled copy, double: 32 M entries in and out, 780 MB: merging the keys
+// again in this kernel 175 us, from the codes 137 us, with each thread reading
+// its own entries 228 us; the product of R-MAT 18 with its pattern, float: 46
+// us, now 26 us).
 template <typename V, int OP>
 __global__ void __launch_bounds__(kEwBlock) ew_tile_write(const int32_t *__restrict__ a_col,
                                                           const V *__restrict__ a_val,

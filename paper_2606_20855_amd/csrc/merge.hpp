@@ -3,14 +3,16 @@
 // they are merged in LDS, pairwise, instead of hashed and sorted again. Equal
 // columns are summed in the order of A's entries.
 //
-// Bound by VALU issue (three quarters of the kernels' time): the work of a
-// product is a merge step per pass, about 13 instructions, and ceil(log2(runs))
-// passes. Measured on rows of R-MAT graphs (edge factor 2 and 4, rows of 65 to
-// 8192 products, 1 to 64 runs, mostly 2 to 8), against LDS hash tables with
-// their sorted emission: 2.5 M columns, float, 435 M products 17.8 ms, here
-// 513 M products (with rows the tables were too small for) 4.2 ms; 1 M columns,
-// double, 121 M products 3.48 ms against 0.85 ms; counting only (symbolic),
-// 513 M products 3.7 ms against 1.85 ms.
+// Bound by VALU issue: the work of a product is a merge step per pass, about 13
+// instructions, and ceil(log2(runs)) passes (counters on the graphs below: the
+// VALU busy all the time where products are only counted, two thirds to nine
+// tenths of it where they are formed; the largest size, whose B values are
+// gathered at 3.8 to 5.1 TB/s, the least). Measured on rows of R-MAT graphs
+// (edge factor 2 and 4, rows of 65 to 8192 products, 1 to 64 runs, mostly 2 to
+// 8), against LDS hash tables with their sorted emission: 2.5 M columns, float,
+// 435 M products 17.8 ms, here 513 M products (with rows the tables were too
+// small for) 4.2 ms; 1 M columns, double, 121 M products 3.48 ms against 0.85
+// ms; counting only (symbolic), 513 M products 3.7 ms against 1.85 ms.
 #pragma once
 
 #include "tiers.hpp"

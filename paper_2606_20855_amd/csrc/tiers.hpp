@@ -54,15 +54,18 @@ struct Mats {
 // of each run of equal columns adds the run's products, in the order of A's
 // entries, and emits.
 //
-// Bound by B's gathers (short rows: 3.3 GB of lines fetched for 0.77 GB of
-// entries at the size below, 7 TB/s with C's writes) once the chain of dependent
-// loads (row, A.row_ptr, A.col, B.row_ptr, B) is hidden; the symbolic kernel by
-// VALU issue of the sort. R rows per segment put R chains in
-// flight; the sort moves keys alone, one register each, with DPP and permlane
-// swaps (no LDS crossbar), and the products follow with one permutation.
-// Measured on 1 M rows of 64 products (double, 8 A entries each): one row per
-// wave and (key, product) pairs through the LDS crossbar 1.09 ms numeric and
-// 0.55 ms symbolic; here 0.58 and 0.28 ms (one row per segment: 0.64 and 0.40).
+// Bound by VALU issue, which the sort takes most of (counters, a 512 x 512 mesh
+// squared: the VALU busy all the time, 1.8 TB/s), except where the selected rows
+// of B lie scattered and pass the caches: the numeric kernel at the size below
+// fetches 3.2 GB of lines for 0.77 GB of entries and runs at 7.1 TB/s with the
+// VALU 80% busy; its symbolic kernel, at 4.9 TB/s, is bound by the VALU. The
+// chain of dependent loads (row, A.row_ptr, A.col, B.row_ptr, B) is hidden: R
+// rows per segment put R chains in flight; the sort moves keys alone, one
+// register each, with DPP and permlane swaps (no LDS crossbar), and the products
+// follow with one permutation. Measured on 1 M rows of 64 products (double, 8 A
+// entries each): one row per wave and (key, product) pairs through the LDS
+// crossbar 1.09 ms numeric and 0.55 ms symbolic; here 0.58 and 0.28 ms (one row
+// per segment: 0.64 and 0.40).
 // ---------------------------------------------------------------------------
 
 // The value of lane l ^ J, within every aligned group of 2J lanes.
