@@ -880,6 +880,33 @@ void launch_hash(int log2t, unsigned grid, hipStream_t st, const Mats<V> &M, con
 #undef WS_HASH_CASE
 }
 
+// The hash rows, one launch per table size; few rows (fewer than fill the CUs twice) go along with those of the next
+// size, up to eight times theirs, as another launch costs more than larger tables do: small power-law graphs have a few
+// rows of every size, 5 us (counted) to 15 us a launch (R-MAT of 16669 vertices, 2 edges each: products of three sizes
+// 44 us in three launches). Not where options.max_lds_slots names the tables.
+constexpr int32_t kFewHashRows = 512;
+constexpr int kFewHashSizes = 3;
+template <typename V, bool NUM>
+void launch_hash_rows(const Ctx &c, hipStream_t st, const Mats<V> &M, const int32_t *perm, int64_t ncols,
+                      int32_t *row_nnz, RowSink out, int32_t *c_col, V *c_val, int32_t *launches) {
+    int first = -1;      // the bin whose rows are the first not launched yet (the bins' rows lie one behind the other)
+    int32_t rows = 0;
+    for (int i = 0; i < kNumHash; ++i) {
+        const int32_t nb = c.host.bin_count[kBinHash0 + i];
+        if (nb == 0) continue;
+        if (first < 0) first = i;
+        rows += nb;
+        int next = i + 1;
+        while (next < kNumHash && c.host.bin_count[kBinHash0 + next] == 0) ++next;
+        if (!c.o.lds_explicit && rows < kFewHashRows && next < kNumHash && next - first <= kFewHashSizes) continue;
+        launch_hash<V, NUM>(kHashLog2Min + i, static_cast<unsigned>(rows), st, M,
+                            perm + c.host.bin_offset[kBinHash0 + first], ncols, row_nnz, out, c_col, c_val, c.ctrl);
+        ++*launches;
+        first = -1;
+        rows = 0;
+    }
+}
+
 // The merge rows, one launch per size.
 template <typename V, bool NUM>
 void launch_merge(const Ctx &c, hipStream_t st, const Mats<V> &M, const int32_t *perm, int32_t *row_nnz, RowSink out,
@@ -1041,15 +1068,8 @@ wingspan_status symbolic_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr 
         if ((s = timer_stop(c, WINGSPAN_TIER_TINY)) != WINGSPAN_OK) return s;
 
         if ((s = timer_start(c, WINGSPAN_TIER_HASH)) != WINGSPAN_OK) return s;
-        for (int i = 0; i < kNumHash; ++i) {
-            const int b = kBinHash0 + i;
-            const int32_t nb = c.host.bin_count[b];
-            if (!nb) continue;
-            launch_hash<float, false>(kHashLog2Min + i, static_cast<unsigned>(nb), light_st, M,
-                                      perm + c.host.bin_offset[b], B->ncols, c.row_nnz, RowSink{}, nullptr, nullptr,
-                                      c.ctrl);
-            stats.launches[WINGSPAN_TIER_HASH]++;
-        }
+        launch_hash_rows<float, false>(c, light_st, M, perm, B->ncols, c.row_nnz, RowSink{}, nullptr, nullptr,
+                                       &stats.launches[WINGSPAN_TIER_HASH]);
         launch_merge<float, false>(c, light_st, M, perm, c.row_nnz, RowSink{}, nullptr, nullptr,
                                    &stats.launches[WINGSPAN_TIER_HASH]);
         LAUNCH_CHECK("hash symbolic");
@@ -1158,14 +1178,8 @@ wingspan_status numeric_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
         if ((s = timer_stop(c, WINGSPAN_TIER_TINY)) != WINGSPAN_OK) return s;
 
         if ((s = timer_start(c, WINGSPAN_TIER_HASH)) != WINGSPAN_OK) return s;
-        for (int i = 0; i < kNumHash; ++i) {
-            const int b = kBinHash0 + i;
-            const int32_t nb = c.host.bin_count[b];
-            if (!nb) continue;
-            launch_hash<V, true>(kHashLog2Min + i, static_cast<unsigned>(nb), light_st, M, perm + c.host.bin_offset[b],
-                                 B->ncols, nullptr, sink, c_col, c_val, c.ctrl);
-            stats.launches[WINGSPAN_TIER_HASH]++;
-        }
+        launch_hash_rows<V, true>(c, light_st, M, perm, B->ncols, nullptr, sink, c_col, c_val,
+                                  &stats.launches[WINGSPAN_TIER_HASH]);
         launch_merge<V, true>(c, light_st, M, perm, nullptr, sink, c_col, c_val,
                               &stats.launches[WINGSPAN_TIER_HASH]);
         LAUNCH_CHECK("hash numeric");
@@ -1257,14 +1271,8 @@ wingspan_status sharded_impl(Ctx &c, const wingspan_csr *A, const wingspan_csr *
     if ((s = timer_stop(c, WINGSPAN_TIER_TINY)) != WINGSPAN_OK) return s;
 
     if ((s = timer_start(c, WINGSPAN_TIER_HASH)) != WINGSPAN_OK) return s;
-    for (int i = 0; i < kNumHash; ++i) {
-        const int b = kBinHash0 + i;
-        const int32_t cnt = c.host.bin_count[b];
-        if (!cnt) continue;
-        launch_hash<V, true>(kHashLog2Min + i, static_cast<unsigned>(cnt), c.st, M, perm + c.host.bin_offset[b],
-                             B->ncols, nullptr, sink, pool_col, pool_val, c.ctrl);
-        stats.launches[WINGSPAN_TIER_HASH]++;
-    }
+    launch_hash_rows<V, true>(c, c.st, M, perm, B->ncols, nullptr, sink, pool_col, pool_val,
+                              &stats.launches[WINGSPAN_TIER_HASH]);
     launch_merge<V, true>(c, c.st, M, perm, nullptr, sink, pool_col, pool_val, &stats.launches[WINGSPAN_TIER_HASH]);
     LAUNCH_CHECK("hash single pass");
     if ((s = timer_stop(c, WINGSPAN_TIER_HASH)) != WINGSPAN_OK) return s;

@@ -204,6 +204,33 @@ def test_hash_rows_bucket_emission(ncols, r, dtype):
     assert num["rows"]["hash"] == 64 and num["merged_rows"] == sym["merged_rows"] == 0
 
 
+@pytest.mark.parametrize("rows,launches", [(10, (1, 2)), (600, (4, 6))])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_few_hash_rows_share_launches(rows, launches, dtype):
+    # rows of 70 A entries whose B rows hold 1 to 23 entries: tables of 2^8 to 2^11 slots (symbolic, the longest row by
+    # its bitmap) and 2^7 to 2^12 (numeric). Few rows of a size go along with larger ones, up to eight times its table
+    rng = np.random.default_rng(rows)
+    sizes, n = [1, 2, 3, 6, 12, 23], 100_000
+    cols = [np.sort(rng.choice(n, L, replace=False)) for L in sizes for _ in range(200)]
+    B = matgen.CSR(len(cols), n, np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32),
+                   np.concatenate(cols).astype(np.int32), None)
+    B.val = (1.0 - rng.random(len(B.col_idx))).astype(dtype)
+    picks = [200 * g + np.sort(rng.choice(200, 70, replace=False)) for g in range(len(sizes)) for _ in range(rows)]
+    A = matgen.CSR(len(picks), B.nrows, (70 * np.arange(len(picks) + 1)).astype(np.int32),
+                   np.concatenate(picks).astype(np.int32), None)
+    A.val = (1.0 - rng.random(len(A.col_idx))).astype(dtype)
+    _, sym, num, _ = check(A, B, None, what="few hash rows")
+    assert num["rows"]["hash"] == len(picks) and num["merged_rows"] == 0
+    assert (sym["launches"]["hash"], num["launches"]["hash"]) == launches
+    _, sym, num, _ = check(A, B, HASHED, what="hash rows by size")
+    assert (sym["launches"]["hash"], num["launches"]["hash"]) == (4, 6)
+    import torch
+    from paper_2606_20855_amd import wingspan as ws
+    C = ws.sharded_to_csr(ws.spgemm_sharded(ws.DeviceCSR.from_host(A, "cuda:0"), ws.DeviceCSR.from_host(B, "cuda:0")))
+    torch.cuda.synchronize()
+    assert_matches(C.to_host(), oracle.spgemm(A, B), dtype, what="single pass")
+
+
 @pytest.mark.parametrize("r", [8, 20, 60])
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 def test_hash_rows_bucket_emission_skewed_columns(r, dtype):
