@@ -484,14 +484,14 @@ __global__ void __launch_bounds__(kBinBlock) bin_count(const int32_t *__restrict
         const int64_t i = w0 + lane_id();
         const bool in = i < i1;
         const int32_t a0 = in ? a_rp[i] : 0, a1 = in ? a_rp[i + 1] : 0;
-        int64_t f = 0;
+        // (what does not depend on A's row is on its way with it)
+        const int64_t c = in && cfg.numeric ? c_rp[i + 1] - c_rp[i] : 0;
+        int64_t f = in && rp.loc == nullptr ? rp.row_prod[i] : 0;
         if (rp.loc != nullptr) {
             f = row_products_of(a0, a1, rp.nnz, rp.loc, rp.tile_sum);
             if (in) rp.row_prod[i] = f;
         }
         if (!in) continue;
-        if (rp.loc == nullptr) f = rp.row_prod[i];
-        const int64_t c = cfg.numeric ? (c_rp[i + 1] - c_rp[i]) : 0;
         int64_t bound;
         const int b = choose_bin(f, a1 - a0, c, cfg, &bound);
         // a whole wave of one bin (usual where rows are alike) adds its sums once instead of lane by lane to one

@@ -213,9 +213,7 @@ __device__ __forceinline__ uint32_t hash_slot(int32_t key, int log2t) {
 }
 
 __host__ __device__ __forceinline__ int ceil_log2(int64_t x) {
-    int l = 0;
-    while ((int64_t(1) << l) < x) ++l;
-    return l;
+    return x > 1 ? 64 - __builtin_clzll(static_cast<unsigned long long>(x - 1)) : 0;
 }
 
 // ---------------------------------------------------------------------------
