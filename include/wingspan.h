@@ -172,8 +172,9 @@ wingspan_status wingspan_spgemm_symbolic(const wingspan_csr *A, const wingspan_c
 /* Numeric phase: fills c_col_idx_dev (int32) and c_val_dev (dtype) for the
  * structure c_row_ptr_dev produced by the symbolic phase for the same A and B
  * patterns, so it can be re-run when the values of A or B change. Synchronizes
- * `stream` once (to size its kernel launches); the output kernels run
- * asynchronously. Writes never leave a row's range [c_row_ptr[i], c_row_ptr[i+1]).
+ * `stream` to size its kernel launches (once, or twice where what the symbolic
+ * phase kept does not serve it, and once more to validate); the output kernels
+ * run asynchronously. Writes never leave a row's range [c_row_ptr[i], c_row_ptr[i+1]).
  *
  * Structure cache: the symbolic phase keeps the column sets (bitmaps) of its
  * densest rows in the workspace, up to 4 GiB, with a stamp naming A and B
