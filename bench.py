@@ -319,7 +319,7 @@ def spmspv_pass(ws, torch, A, workload, dev, steps, warmup, seed, density=0.1):
 
 
 def outer_pass(ws, torch, workload, dev, steps, warmup):
-    """Outer-product SpGEMM (per-workgroup partial Cs merged by a coalesce
+    """Outer-product SpGEMM (partial entries in row buckets, summed by a coalesce
     step) on a workload, beside the two-phase Gustavson path on the same
     inputs. Each call is timed whole with HIP events (the outer call counts its
     products and reads back nnz(C); Gustavson runs symbolic then numeric)."""

@@ -1,4 +1,4 @@
-"""Outer-product SpGEMM (per-workgroup partial Cs merged by a coalesce step)
+"""Outer-product SpGEMM (partial entries in row buckets, summed by a coalesce step)
 on the GPU against the oracle's C = A B: the same product as the Gustavson
 path, so the structure must match bit for bit and the values within the
 tolerance of the sum of |products|."""
@@ -64,7 +64,7 @@ def test_er1000_and_laplacian():
 
 
 def test_rectangular_many_chunks():
-    # 64 K products over many workgroups' partial Cs
+    # 64 K products over many workgroups' chunks
     A, B = matgen.er_rect(4000, 2000, 4000, 4, 75)
     check(A, B, "er rect")
 
@@ -79,8 +79,8 @@ def test_identity_and_permutation_exact():
 
 
 def test_rows_past_the_lds_cap_exact():
-    # every row of the arrowhead's square gathers about n partial entries (n > 4096):
-    # runs sorted in LDS, one merge pass; integer sums are exact whatever the order
+    # every row of the arrowhead's square gathers about n partial entries (n > 4096), no
+    # fewer than C's columns: summed by pieces; integer sums are exact whatever the order
     A = matgen.arrowhead(5000)
     got, ref = check(A, A, "arrowhead 5000")
     assert np.array_equal(got.val, ref.val)
@@ -90,8 +90,7 @@ def test_rows_past_the_lds_cap_exact():
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 def test_long_row_of_few_columns(dtype):
     # row 0 of A is full over K = 200000 and B's rows have 3 of 50 columns: row 0 of C
-    # gathers ~50 entries from each of ~290 partial Cs, so runs of equal columns span
-    # merge tiles and compaction blocks
+    # gathers 600 K entries of 50 columns, summed over 74 pieces
     K = 200000
     rng = np.random.default_rng(81)
     a_rows = [np.zeros(K, np.int64), np.full(5, 1, np.int64), np.full(3, 2, np.int64)]
@@ -108,7 +107,8 @@ def test_long_row_of_few_columns(dtype):
 @pytest.mark.slow
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_rmat14_square(dtype):
-    # heavy-tailed rows: the largest gathers ~165 K partial entries (six merge passes)
+    # heavy-tailed rows: the largest gathers ~165 K partial entries (21 pieces), those of 4097
+    # to 16383 entries are sorted as runs and merged
     A = matgen.rmat(14, 16, seed=3, dtype=dtype)
     ref_prods = oracle.row_products(A, A)
     assert int(ref_prods.max()) > 100000 and int((ref_prods > 4096).sum()) > 500

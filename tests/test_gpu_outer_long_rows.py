@@ -81,6 +81,15 @@ def test_runs_of_equal_columns():
     _check(_csr(rows, B.nrows, rng, np.float64), B)
 
 
+def test_sorted_buckets_of_many_merge_passes():
+    # C of more columns than are summed by pieces: 2 to 42 runs sorted in LDS, one to six merge passes
+    rng = np.random.default_rng(6)
+    n = 100_000
+    B = _csr([np.sort(rng.choice(n, 50, replace=False)) for _ in range(3500)], n, rng, np.float64)
+    rows = [np.sort(rng.choice(B.nrows, want, replace=False)) for want in (82, 164, 170, 330, 700, 1400, 3400)]
+    _check(_csr(rows, B.nrows, rng, np.float64), B)
+
+
 @pytest.mark.parametrize("hot", [[0], [7, 2054, 4101], list(range(16)), list(range(0, 40_000, 2048))], ids=len)
 def test_rows_claimed_by_many_entries(hot):
     # every index has a few of the hot rows (among them rows of one slot of the claims' table) and one other
