@@ -623,7 +623,10 @@ __global__ void __launch_bounds__(kOpRowBlock) op_merge_long(const int64_t *__re
             for (int k = threadIdx.x; k < cols; k += kOpRowBlock) s_val[k] = 0.0;
             if (threadIdx.x < kOpRowCap / 32) bits[threadIdx.x] = 0u;
             __syncthreads();
-            for (int e = threadIdx.x; e < len; e += kOpRowBlock) op_add(bits, s_val, bkt_col[lo + e], bkt_val[lo + e]);
+            for (int e = threadIdx.x; e < len; e += kOpRowBlock) {
+                const int k = bkt_col[lo + e];   // (a column that is none of B's stays out of the LDS)
+                if (static_cast<uint32_t>(k) < static_cast<uint32_t>(cols)) op_add(bits, s_val, k, bkt_val[lo + e]);
+            }
             __syncthreads();
             const int n = op_emit_window(0, cols, bits, s_val, s_key + kOpRowCap / 32, s_scan, bkt_col + lo,
                                          out_val + lo);
